@@ -269,8 +269,59 @@ struct PwLaunch {
     bool rows;  // row-cooperative kernel (a.cw != 0)
     int big_body;  // body of pw_bigbatch_kernel that runs this plan, or -1
     int mode;
-    bool gemm;  // the kernel of wide layers (k loop outermost); never a member of a shared launch
+    bool gemm;  // the plan is the tile kernel (k loop outermost): never a member of a shared launch
+    // the tile kernel runs this layer when it is launched alone (always when gemm): its launch
+    bool tile;
+    PwArgs ta;
+    KernelFn tfn;
+    int tgrid;
+    size_t tlds;
 };
+
+// The tile kernel's pixel tiles per wavefront for a layer (2, 4 or 8), or 0 where the streaming kernel is
+// the faster one.  Times in us, batch 1 to 128 of 20 layer shapes of the three networks, tensors not in the
+// last-level cache.
+//
+// Choice of the tile.  A tile takes base + step * KS however few there are; with r tiles per compute
+// unit the layer takes 2.5 + r * (c0 + c1 * KS).  The constants are fits: 14x14 1024 -> 512 takes
+// 19.9 / 22.4 / 25.7 at batch 128 with 8 / 4 / 2 pixel tiles (196 to 1568 workgroup tiles), 12.4 / 9.6 / 10.8
+// at batch 32, 11.2 / 8.3 / 7.5 at batch 4.
+//
+// Where the streaming kernel stays:
+//   - channels that do not fill the 256 of a tile (waste above 4/3): 28x28 576 -> 192 7.5 against 8.0,
+//     56x56 256 -> 128 23 against 28, 960 -> 320 7.9 against 9.2;
+//   - deep layers with few pixels, which it spreads over more workgroups: 1024 -> 512 at 784 pixels 5.8 against
+//     7.5, at 3136 pixels 8.6 against 8.1; 1024 -> 1024 6.0 / 7.6 and 12.9 / 9.6; 2048 -> 1024 at 784 pixels
+//     11.9 against 12.7, at 1568 19.1 against 12.9: level at M*N*K of about 1.1e9 (1024 channels), 1.5e9 to
+//     2e9 (2048); up to 512 input channels the tile kernel is ahead down to one image (512 -> 1024 at 14x14
+//     5.8 against 5.5, 64 -> 384 4.6 against 3.4);
+//   - shallow layers with many pixels, which are nothing but streams: 56x56 64 -> 256 14.1 against 13.0 at
+//     batch 32 (784 tiles of 128 pixels), 22.1 against 23.9 at batch 64; 28x28 128 -> 384, a quarter of its
+//     tiles' work wasted, 9.3 against 8.2 at batch 32 (392 tiles), 12.3 against 13.8 at batch 64.
+static int gemm_plan(long long M, int cin, int cout)
+{
+    const int KS = (cin + 63) / 64;
+    const long long ct = (cout + 255) / 256;
+    if (3 * 256 * ct > 4 * (long long)cout) return 0;
+    if (KS > 8 && (double)M * cout * cin < 1.1e9 * (KS / 16.0 > 1.0 ? 0.7 * KS / 16.0 + 0.3 : 1.0)) return 0;
+    const long long t8 = (M + 127) / 128 * ct;
+    if (KS == 1 && t8 > 800) return 0;
+    if (KS == 2 && 256 * ct != cout && t8 > 400) return 0;
+    static const struct { int pt; double base, step, c0, c1; } kFit[] = {
+        {8, 4.3, 0.43, 3.7, 0.46}, {4, 3.4, 0.295, 1.8, 0.28}, {2, 3.1, 0.27, 1.2, 0.16}};
+    int best = 0;
+    double best_us = 0;
+    for (const auto &f : kFit) {
+        const double r = (double)((M + 16 * f.pt - 1) / (16 * f.pt) * ct) / kNumCU;
+        const double alone = f.base + f.step * KS, many = 2.5 + r * (f.c0 + f.c1 * KS);
+        const double us = alone > many ? alone : many;
+        if (best == 0 || us < best_us) {
+            best = f.pt;
+            best_us = us;
+        }
+    }
+    return best;
+}
 
 // Validate the arguments and fill the launch description.  mode: 0 = requantised int8
 // output, 1 = raw int32 accumulators.  shape_only: plan from the shape alone (no pointers,
@@ -436,21 +487,14 @@ static int pw_prepare(const int8_t *x, int n, int h, int w, int cin, const void 
     if (total > (1LL << 30)) return PROM_EUNSUPPORTED;
     L.grid = (int)((total + 7) / 8 * 8);
 
-    // Wide layers: the kernel with the k loop outermost.  With a thousand input channels the decoded
-    // weights of all k steps fit LDS only for two to four channel tiles per chunk, and every chunk
-    // streams the activations again; the tile kernel decodes per k step and does 32 MFMAs per 4
-    // activation loads.  Measured (batch 128, one launch per layer, cache-cold, us against the
-    // streaming kernel): 14x14 1024 -> 512 33 against 37, 1024 -> 1024 56 against 63; 7x7
-    // 1024 -> 2048 31 against 36, 2048 -> 1024 32 against 58.  With 512 and fewer input channels the
-    // streaming kernel is the faster one (14x14 512 -> 1024 26 against 43 us, 28x28 512 -> 512 45
-    // against 76), so the library takes the tile kernel from 1024 input channels on -- when its
-    // tiles fill the chip: a tile takes 6 us plus 0.65 us per k step however few there are, and with
-    // less than one tile per compute unit the streaming kernel, which spreads the pixels over more
-    // workgroups, is faster (batch 32: 14x14 1024 -> 512, 100 tiles, 13 against 19 us; 7x7
-    // 1024 -> 2048, 112 tiles, 13 against 20; 2048 -> 1024, 56 tiles, 19 against 26; 14x14
-    // 1024 -> 1024, 200 tiles, 22 against 20).  The two meet at about 180 tiles of 16 k steps and 80
-    // tiles of 32: tiles x k steps >= 2800.
-    L.gemm = false;
+    // The tile kernel (k loop outermost).  From 1024 input channels on, where its tiles fill the chip, and
+    // when the caller asks for it, it is the layer's plan, and the layer is not a member of a shared launch.
+    // (128 x 256 pieces of the output x k steps >= 2800 puts the line where a layer alone and a layer
+    // that shares the chip with others take the same time: ResNeXt-50's sequence at batch 32 keeps its layers
+    // of 56 to 112 pieces in the shared launch.)  Below that it runs the layers it is faster for when they
+    // are launched alone; their plan, and with it what they are in a shared launch, stays that of the
+    // streaming kernel.
+    L.gemm = L.tile = false;
     const int k_outer = plan ? plan->k_outer : 0;
     if (k_outer != 0 && k_outer != 1 && k_outer != -1) return PROM_EINVAL;
     const bool aligned16 = shape_only || ((((uintptr_t)x | (uintptr_t)y | (uintptr_t)residual) & 15) == 0 &&
@@ -460,38 +504,47 @@ static int pw_prepare(const int8_t *x, int n, int h, int w, int cin, const void 
         if (!gemm_ok || plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves || plan->workgroups)
             return PROM_EINVAL;
     }
-    const bool explicit_stream = plan && (plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves);
-    const long long gemm_tiles = ((M + 255) / 256) * ((cout + 127) / 128);
-    const bool gemm_pays = cin >= 1024 && cout >= 256 && gemm_tiles * (cin / 64) >= 2800;
-    if (gemm_ok && (k_outer == 1 || (k_outer == 0 && !explicit_stream && gemm_pays))) {
-        L.gemm = true;
-        L.rows = false;
-        a.cw = 0;
-        L.nt = 8;
-        L.pt = 4;
-        L.xmode = 16;
-        L.threads = 256;
-        L.lds = pw_gemm_lds_bytes();
-        L.fn = pw_gemm_select(a.mult_neg != nullptr);
-        L.big_body = -1;
-        a.n_chunks = (cout + 127) / 128;
-        a.units = (int)((M + 63) / 64);
-        a.wg_per_chunk = (int)((M + 255) / 256);
-        const long long tot = (long long)a.n_chunks * a.wg_per_chunk;
-        if (tot > (1LL << 30)) return PROM_EUNSUPPORTED;
-        L.grid = (int)((tot + 7) / 8 * 8);
+    const bool explicit_stream = plan && (plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves || plan->workgroups);
+    if (gemm_ok && k_outer != -1 && !explicit_stream) {
+        int pt = gemm_plan(M, cin, cout);
+        const long long pieces = ((M + 255) / 256) * ((cout + 127) / 128);
+        L.gemm = k_outer == 1 || (cin >= 1024 && cout >= 256 && pieces * (cin / 64) >= 2800);
+        L.tile = L.gemm || pt != 0;
+        if (L.tile) {
+            if (pt == 0) pt = M >= 128 * 256 ? 8 : 4;
+            const GemmTile t = pw_gemm_tile(pt, a.mult_neg != nullptr);
+            L.tfn = t.fn;
+            L.tlds = t.lds;
+            L.ta = a;
+            L.ta.n_chunks = (cout + t.tn - 1) / t.tn;
+            L.ta.wg_per_chunk = (int)((M + t.tm - 1) / t.tm);
+            const long long tot = (long long)L.ta.n_chunks * L.ta.wg_per_chunk;
+            if (tot > (1LL << 30)) return PROM_EUNSUPPORTED;
+            L.tgrid = (int)((tot + 7) / 8 * 8);
+            if (L.gemm) {
+                L.rows = false;
+                L.nt = 4;
+                L.pt = pt;
+                L.xmode = 16;
+                L.big_body = -1;
+                a.cw = 0;
+                a.wg_per_chunk = L.ta.wg_per_chunk;
+            }
+        }
     }
     return PROM_OK;
 }
 
 static int pw_launch(const PwLaunch &L, hipStream_t st)
 {
-    if (L.lds > 64 * 1024 && resident_workgroups(L.fn, L.lds, L.threads) < 1) return PROM_EHIP;
+    const KernelFn fn = L.tile ? L.tfn : L.fn;
+    const size_t lds = L.tile ? L.tlds : L.lds;
+    const int grid = L.tile ? L.tgrid : L.grid, threads = L.tile ? 256 : L.threads;
+    if (lds > 64 * 1024 && resident_workgroups(fn, lds, threads) < 1) return PROM_EHIP;
     clear_hip_error();
-    PwArgs args = L.a;
+    PwArgs args = L.tile ? L.ta : L.a;
     void *kargs[] = {&args};
-    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(L.fn), dim3(L.grid), dim3(L.threads), kargs,
-                                         L.lds, st);
+    const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(grid), dim3(threads), kargs, lds, st);
     if (e != hipSuccess) {
         last_hip_error() = e;
         (void)hipGetLastError();

@@ -1,251 +1,285 @@
 // Ternary pointwise convolution for wide layers (hundreds to thousands of input AND output
-// channels: the 1x1 layers of the deeper stages of ResNeXt / RegNet, paper Section 5): the k loop is
-// outermost over a workgroup tile of 128 output channels x 256 pixels.
+// channels: the 1x1 layers of ResNeXt and of the deeper stages of RegNet, paper Section 5): the k loop
+// is outermost over a workgroup tile of pixels x output channels.
 //
 // The streaming kernel (prom_pw_stream.h) keeps the decoded weights of a chunk of output channels
-// for ALL input channels in LDS and streams the pixels past them once per chunk; with 16 to 32 k
-// steps a chunk is two to four 16-channel tiles, so a layer with 2048 output channels reads its
-// activations 32 to 64 times and a wavefront issues two to four MFMAs per 16-byte activation load.
-// Such layers are bound by the matrix cores (arithmetic intensity above 625 op/B), and this kernel is
-// shaped for that:
-//   - a wavefront owns 8 channel tiles x 4 pixel tiles (32 accumulator tiles, 128 registers): 32
-//     MFMAs per k step against 8 LDS reads of 16 bytes (the decoded weights, shared by the four
-//     wavefronts) and 4 global loads of 16 bytes (its own pixels, straight into the B operand);
-//   - the 128 x 64 ternary codes of the next k step (2 KB packed) are fetched one step ahead, decoded
-//     by all 256 threads into the other of two 8 KB LDS slabs while the matrix cores work on this
-//     step; one barrier per k step;
-//   - the pixels of the next k step are fetched one step ahead into the other of two register sets;
-//   - workgroups that share a pixel tile (the layer's 128-channel column tiles) are neighbours in
-//     the XCD-aware order, so the activations are fetched from HBM once and from that XCD's L2 by the
-//     others;
-//   - epilogue as in the streaming kernel: 64-bit multiply-add requantisation per output, the
-//     wavefront's 64 pixels x 128 channels staged through LDS and written as whole 128-byte rows.
-#include "prom_pw_stream.h"
+// for ALL input channels in LDS and streams the pixels past them once per chunk: every MFMA reads a
+// weight fragment from LDS (256 B per cycle and CU at the matrix cores' rate, twice what LDS gives), the
+// activations pass the texture addresser once per chunk, and a workgroup decodes up to 64 KB of
+// fragments before its first MFMA.  Here
+//   - a wavefront owns PT x 4 accumulator tiles: 16*PT pixels x 64 output channels of the workgroup's
+//     16*PT x 256.  It decodes the packed codes of its own 64 channels in registers, 48 instructions per
+//     k step against 4*PT MFMAs of 16 cycles, so no decoded weight passes through LDS;
+//   - everything comes from global memory in lane order: four neighbouring lanes read one 64-byte run.  The
+//     texture addresser takes 24 to 30 cycles for such an instruction of 1 KB, and 65 for one in operand
+//     order (16 rows, neighbouring lanes in different lines), however few bytes its lanes load: a first
+//     version that fetched its codes as one dword per lane in operand order took 33 us (4 pixel tiles) and
+//     57 us (2) for 512 -> 1024 at 12544 and 25088 pixels, where this one takes 14.7 and 25.9;
+//   - the packed codes of four k steps (64 bytes per channel) go through 4 KB of LDS of the wavefront's own
+//     into operand order; no barrier, LDS operations of a wavefront keep their order;
+//   - the activations of a k step (64 bytes per pixel) are fetched by all 256 threads D k steps ahead in
+//     registers and put into one of two LDS slabs, from which every wavefront reads its B operands: 1 KB
+//     per 4 MFMAs, half of what LDS delivers.  The 16-byte pieces of a pixel are exchanged by the pixel's
+//     index, so that neither the writes nor the operand reads meet bank conflicts.  One barrier per k step,
+//     on LDS traffic only;
+//   - workgroups that share a pixel tile are neighbours in the XCD-aware order;
+//   - the epilogue requantises two pixels at a time (requant_pair4), assembles the tile in LDS and writes
+//     whole rows in 16-byte pieces; the skip connection is read and added in the same pieces.
+//
+// What bounds it: the chain of a k step in a wavefront (barrier, first operand reads, 128 to 512 cycles of
+// MFMAs with the decode between them, barrier: 0.27, 0.30 and 0.43 us with 2, 4 and 8 pixel tiles) and the 4 us
+// around the k loop, which 2 to 4 workgroups per CU overlap: 14x14 1024 -> 1024 at batch 128 runs at 1.5 Pop/s
+// (35 us; 58 with the streaming kernel, 53 with the kernel this one replaced, which fetched its pixels in
+// operand order and passed its decoded weights through LDS).  Without the decode (wrong results) the layers
+// take 4 to 7 % less, without the requantisation 10 %.
 #include "prom_pw_gemm.h"
 
 namespace prom {
 
-constexpr int kGemmTN = 128;  // output channels per workgroup
-constexpr int kGemmTM = 256;  // pixels per workgroup
-constexpr int kGemmStageStride = 144;  // bytes between pixels of the output staging tile (128 + 16)
-
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() carries a release fence over
 // every address space, which makes the compiler wait for ALL outstanding global loads -- here the
-// pixels and codes requested for three k steps ahead.  The wavefront's LDS writes are complete when
+// pixels and codes requested for the k steps ahead.  The wavefront's LDS writes are complete when
 // lgkmcnt reaches 0 (LDS operations of a wavefront finish in order).
 __device__ __forceinline__ void lds_barrier()
 {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-#ifdef PROM_TIMELINE
-__device__ unsigned long long g_gemm_stamps[1024 * 4];
-#define GEMM_STAMP(i) do { if (threadIdx.x == 0 && blockIdx.x < 1024) g_gemm_stamps[blockIdx.x * 4 + (i)] = wall_clock64(); } while (0)
-#else
-#define GEMM_STAMP(i) do { } while (0)
-#endif
+// A wavefront's packed codes of four k steps in LDS: [k step][64 channels][16 bytes], the k steps
+// 32 bytes further apart than they need (bank conflicts of the writes).
+constexpr int kGemmCodeStep = 64 * 16 + 32;
+constexpr int kGemmCodes = 4 * kGemmCodeStep;
 
-size_t pw_gemm_lds_bytes()
-{
-    // two slabs of decoded weights, parameters of 128 channels, staging of 4 x 64 pixels
-    return 2 * 8192 + 128 * 16 + 4 * 64 * kGemmStageStride;
-}
+template <int PT> struct GemmGeom {
+    static constexpr int TM = 16 * PT;            // pixels of a workgroup's tile
+    static constexpr int TN = 256;                // output channels of it, 64 per wavefront
+    static constexpr int NQ = TM >= 64 ? TM / 64 : 1;  // 16-byte pieces of activations per thread and k step
+    static constexpr int SLAB = NQ * 4096;        // bytes of one k step's activations (32-pixel tiles: half used)
+    static constexpr int PITCH = TN + 16;         // bytes between pixels of the assembled tile
+    static constexpr int BODY = 2 * SLAB > TM * PITCH ? 2 * SLAB : TM * PITCH;
+    static constexpr size_t LDS = (size_t)TN * 16 + 4 * kGemmCodes + BODY;
+    static constexpr int D = PT == 8 ? 2 : 4;     // k steps of activations requested ahead
+    static constexpr int NP = TM * TN / 16 / 256; // 16-byte pieces of the output tile per thread
+};
 
-// a.n_chunks = column tiles of 128 channels, a.wg_per_chunk = row tiles of 256 pixels; requires
-// K % 64 == 0, Nc % 16 == 0, 16-byte aligned x, y, residual and 8-byte aligned packed weights.
-template <bool PRELU>
-__global__ __launch_bounds__(256, 1) void pw_gemm_kernel(const PwArgs a)
+// a.n_chunks = column tiles of TN channels, a.wg_per_chunk = row tiles of TM pixels; requires
+// K % 64 == 0, Nc % 16 == 0 and 16-byte aligned x, y, residual.
+
+
+
+template <int PT, bool PRELU>
+__global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_kernel(const PwArgs a)
 {
+    using G = GemmGeom<PT>;
+    constexpr int D = G::D, NQ = G::NQ;
     extern __shared__ __align__(16) unsigned char lds[];
-    v4i *frag = reinterpret_cast<v4i *>(lds);                     // [2][8 tiles][64 lanes]
-    v4i *lpar = reinterpret_cast<v4i *>(lds + 2 * 8192);          // [128]
-    unsigned char *stage_all = lds + 2 * 8192 + 128 * 16;
+    v4i *lpar = reinterpret_cast<v4i *>(lds);  // [TN]
+    unsigned char *body = lds + G::TN * 16 + 4 * kGemmCodes;  // two slabs of activations, then the assembled tile
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, g = lane >> 4;
 
-    GEMM_STAMP(0);
     const int lid = logical_block_id();
     const int ntile = lid % a.n_chunks;
     const int mtile = lid / a.n_chunks;
     if (mtile >= a.wg_per_chunk) return;
-    const int n0 = ntile * kGemmTN;
-    const int m0 = mtile * kGemmTM + wave * 64;  // this wavefront's first pixel
+    const int n0 = ntile * G::TN;
+    const int m0 = mtile * G::TM;
     const int K = a.K, Nc = a.Nc, KW = a.KW, KS = a.KS;
 
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(a.x), 0, a.M * K, kBufFlags);
+    const __amdgpu_buffer_rsrc_t rw =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.wq), 0, Nc * KW * 4, kBufFlags);
     const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(a.y, 0, a.M * Nc, kBufFlags);
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int8_t *>(a.residual ? a.residual : a.y), 0, a.M * Nc, kBufFlags);
 
-    // activation offsets of the lane's pixel in each of the 4 pixel tiles (saturated beyond the tensor)
-    unsigned xoff[4];
+    // Activations: piece idx = tid + 256*q of a slab is 16-byte slot idx & 3 of pixel idx >> 2 and holds
+    // piece slot ^ ((pixel >> 1) & 3) of the pixel's 64 bytes.
+    unsigned xoff[NQ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const long long o = (long long)(m0 + 16 * i + j) * K + 16 * g;
-        xoff[i] = o < (long long)kOobOffset ? (unsigned)o : (unsigned)kOobOffset;
+    for (int q = 0; q < NQ; ++q) {
+        const int idx = tid + 256 * q;
+        const int px = idx >> 2, piece = (idx & 3) ^ ((px >> 1) & 3);
+        const long long o = (long long)(m0 + px) * K + 16 * piece;
+        xoff[q] = px < G::TM && o < (long long)kOobOffset ? (unsigned)o : (unsigned)kOobOffset;
     }
-    // weight staging: thread -> row tid >> 1 of the tile, words 4ks + 2*(tid & 1) + {0, 1}
-    const int wr = tid >> 1, wh = tid & 1;
-    const bool wrow_ok = n0 + wr < Nc;
-    const uint32_t *wsrc = a.wq + (long long)(wrow_ok ? n0 + wr : 0) * KW + 2 * wh;
-    v4i *wdst = frag + (wr >> 4) * 64 + (2 * wh) * 16 + (wr & 15);  // + slab * 512, and + 16 for the second word
+    // Codes of a group of four k steps: 64 bytes per channel.  Instruction r of a load: channel
+    // 16*r + (lane >> 2) of the wavefront's 64, 16-byte piece (= k step of the group) lane & 3; channels
+    // past the layer lie past the matrix and read zero, k steps past the row go out of range.
+    const int wpiece = lane & 3;
+    const unsigned woff = (unsigned)((n0 + 64 * wave + (lane >> 2)) * KW + 4 * wpiece) * 4u;
+    const unsigned wstep = 64u * (unsigned)KW;  // 16 rows
+    unsigned char *codes = lds + G::TN * 16 + wave * kGemmCodes;
+    unsigned char *wput = codes + wpiece * kGemmCodeStep + (lane >> 2) * 16;
+    const unsigned char *wget = codes + j * 16 + g * 4;
 
-    auto load_x = [&](int ks, v4i(&b)[4]) __attribute__((always_inline)) {
+    // (requests past the last k step go out of range and move nothing)
+    auto load_x = [&](int ks, v4i(&v)[NQ]) __attribute__((always_inline)) {
+        const unsigned ko = ks < KS ? 64u * (unsigned)ks : (unsigned)kOobOffset;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            b[i] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)min(xoff[i] + (unsigned)(64 * ks), (unsigned)kOobOffset), 0, 0);
+        for (int q = 0; q < NQ; ++q)
+            v[q] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)min(xoff[q] + ko, (unsigned)kOobOffset), 0, 0);
     };
-    auto load_w = [&](int ks) __attribute__((always_inline)) {
-        return *reinterpret_cast<const v2i *>(wsrc + 4 * ks);
+    auto load_w = [&](int ks, v4i(&v)[4]) __attribute__((always_inline)) {  // ks: first step of the group
+        const unsigned ko = ks + wpiece < KS ? 16u * (unsigned)ks : (unsigned)kOobOffset;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            v[r] = __builtin_amdgcn_raw_buffer_load_b128(rw, (int)min(woff + r * wstep + ko, (unsigned)kOobOffset), 0, 0);
     };
-    // (rows beyond the layer are zeroed here, at the use, not at the load: a select right behind the
-    // load would wait for it, and with it for every load issued before)
-    auto put_w = [&](int slab, v2i w, bool real) __attribute__((always_inline)) {
-        const bool ok = wrow_ok && real;
-        wdst[slab * 512] = decode_word(ok ? (uint32_t)w[0] : 0u);
-        wdst[slab * 512 + 16] = decode_word(ok ? (uint32_t)w[1] : 0u);
+    auto put_w = [&](const v4i(&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) *reinterpret_cast<v4i *>(wput + 256 * r) = v[r];
+    };
+    auto get_w = [&](int d, uint32_t(&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) v[t] = *reinterpret_cast<const uint32_t *>(wget + d * kGemmCodeStep + 256 * t);
+    };
+    auto put_x = [&](int slab, const v4i(&v)[NQ]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) *reinterpret_cast<v4i *>(body + slab * G::SLAB + (tid + 256 * q) * 16) = v[q];
     };
 
-    v4i acc[8][4];
+    // Ring: slot (s % D) holds step s's activations until they are put into LDS one step early.
+    v4i xr[D][NQ], wr[4];
+    load_w(0, wr);
 #pragma unroll
-    for (int t = 0; t < 8; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[t][i] = v4i{0, 0, 0, 0};
-
-    // Rings of three k steps: the pixels and the packed codes of step ks + 2 are requested when step
-    // ks starts (a k step is about 0.25 us; a request that misses the L2 takes longer, one that hits
-    // it less).
-    v4i bx[3][4];
-    v2i wq[3];
-#pragma unroll
-    for (int d = 0; d < 2; ++d) {
-        const int kd = min(d, KS - 1);
-        load_x(kd, bx[d]);
-        wq[d] = load_w(kd);
+    for (int d = 0; d < D; ++d) load_x(d, xr[d]);
+    int pb = 0, pm = 0, pn = 0, ps = 31;
+    if (tid < G::TN) {
+        const int c = min(n0 + tid, Nc - 1);
+        pb = a.bias[c];
+        pm = a.mult[c];
+        ps = a.shift[c];
+        if (PRELU) pn = a.mult_neg[c];
     }
-    if (tid < kGemmTN) {
-        const int c = n0 + tid;
-        v4i p = {0, 0, 0, 1};
-        if (c < Nc) p = requant_params(a.bias[c], a.mult[c], PRELU ? a.mult_neg[c] : 0, a.shift[c], PRELU);
-        lpar[tid] = p;
-    }
-    put_w(0, wq[0], true);
-    __syncthreads();
-    GEMM_STAMP(1);
 
-    // one k step: the matrix cores on slab ks & 1 and the pixels of ring slot ks % 3; the codes of
-    // the next step are decoded into the other slab behind the MFMAs; one barrier.  All eight weight
-    // fragments of the step are read from LDS before the first MFMA: with one wavefront per SIMD
-    // nothing else hides an LDS latency, and read pair by pair they cost four of them per step.  Six
-    // steps per iteration in straight-line code (a step beyond the last one runs on zero weights:
-    // branches inside the body make the compiler wait for the newest load instead of the one it needs).
-    for (int ks0 = 0; ks0 < KS; ks0 += 6) {
+    v4i acc[PT][4];
 #pragma unroll
-        for (int d = 0; d < 6; ++d) {
-            const int ks = ks0 + d;
-            const int kf = min(ks + 2, KS - 1);
-            load_x(kf, bx[(d + 2) % 3]);
-            wq[(d + 2) % 3] = load_w(kf);
-            const v4i *fr = frag + (d & 1) * 512 + lane;
-            v4i A[8];
-            __builtin_amdgcn_sched_barrier(0);  // (the scheduler would sink the reads to their uses)
+    for (int i = 0; i < PT; ++i)
 #pragma unroll
-            for (int t = 0; t < 8; ++t) A[t] = fr[t * 64];
-            __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < 4; ++t) acc[i][t] = v4i{0, 0, 0, 0};
+
+    uint32_t wc[4];
+    put_w(wr);
+    load_w(4, wr);
+    get_w(0, wc);
+    put_x(0, xr[0]);
+    load_x(D, xr[0]);
+    if (tid < G::TN) lpar[tid] = requant_params(pb, pm, pn, ps, PRELU);
+    lds_barrier();
+
+    // One k step; d = ks % 4.  The words of the next step are read one step early; the codes of the next
+    // group replace this group's once its last words have been requested (LDS operations of a wavefront
+    // keep their order, and no other wavefront reads them).
+    const unsigned char *bsrc = body + (j * 4 + (g ^ ((j >> 1) & 3))) * 16;
+    auto step = [&](auto dtag, int ks) __attribute__((always_inline)) {
+        constexpr int d = decltype(dtag)::value;
+        v4i B[PT];
 #pragma unroll
-            for (int t = 0; t < 8; ++t) {
+        for (int i = 0; i < PT; ++i) B[i] = *reinterpret_cast<const v4i *>(bsrc + (d & 1) * G::SLAB + i * 1024);
+        if constexpr (d == 3) {
+            put_w(wr);
+            load_w(ks + 5, wr);
+        }
+        uint32_t wnext[4];
+        get_w((d + 1) & 3, wnext);
+        put_x((d + 1) & 1, xr[(d + 1) % D]);
+        load_x(ks + 1 + D, xr[(d + 1) % D]);
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    acc[t][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[t], bx[d % 3][i], acc[t][i], 0, 0, 0);
-            }
-            put_w((d + 1) & 1, wq[(d + 1) % 3], ks + 1 < KS);
-            lds_barrier();
+        for (int t = 0; t < 4; ++t) {
+            const v4i A = decode_word(wc[t]);
+#pragma unroll
+            for (int i = 0; i < PT; ++i) acc[i][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A, B[i], acc[i][t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) wc[t] = wnext[t];
+        lds_barrier();
+    };
+    // straight-line code for four steps (a branch inside makes the compiler wait for the newest load
+    // instead of the one it needs); the last KS % 4 steps one by one
+    int ks0 = 0;
+    for (; ks0 + 4 <= KS; ks0 += 4) {
+        step(std::integral_constant<int, 0>{}, ks0);
+        step(std::integral_constant<int, 1>{}, ks0 + 1);
+        step(std::integral_constant<int, 2>{}, ks0 + 2);
+        step(std::integral_constant<int, 3>{}, ks0 + 3);
+    }
+    if (ks0 < KS) {
+        step(std::integral_constant<int, 0>{}, ks0);
+        if (ks0 + 1 < KS) {
+            step(std::integral_constant<int, 1>{}, ks0 + 1);
+            if (ks0 + 2 < KS) step(std::integral_constant<int, 2>{}, ks0 + 2);
         }
     }
 
-    GEMM_STAMP(2);
-    // ---- epilogue: requantise, skip, stage the wavefront's 64 x 128 tile, write whole rows ------------
+    // ---- epilogue ------------------------------------------------------------------------------------
     const int lo = in_vgpr(a.lo), hi = in_vgpr(a.hi);
-    const int m128 = in_vgpr(-128), p127 = in_vgpr(127);
-    const bool has_res = a.residual != nullptr;
-    unsigned char *stage = stage_all + wave * (64 * kGemmStageStride);
-    // residual dwords of the lane's (pixel, 4 channels) of tile t, one tile ahead
-    auto load_res = [&](int t, uint32_t(&r)[4]) __attribute__((always_inline)) {
+    // output piece q of this thread: 16 bytes of channels 16*(idx % (TN/16)) of pixel idx / (TN/16)
+    constexpr int PPR = G::TN / 16;
+    int yoff[G::NP];
+    v4i res[G::NP];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const long long o = (long long)(m0 + 16 * i + j) * Nc + n0 + 16 * t + 4 * g;
-            const bool ok = n0 + 16 * t + 4 * g < Nc && o < (long long)kOobOffset;
-            r[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rr, ok ? (int)o : kOobOffset, 0, 0);
-        }
-    };
-    uint32_t res[4] = {0, 0, 0, 0}, resn[4] = {0, 0, 0, 0};
-    if (has_res) load_res(0, res);
+    for (int q = 0; q < G::NP; ++q) {
+        const int idx = tid + 256 * q;
+        const int px = idx / PPR, c = n0 + 16 * (idx % PPR);
+        const long long o = (long long)(m0 + px) * Nc + c;
+        yoff[q] = c < Nc && o < (long long)kOobOffset ? (int)o : kOobOffset;
+    }
+    if (a.residual) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-        if (has_res && t + 1 < 8) load_res(t + 1, resn);
+        for (int q = 0; q < G::NP; ++q) res[q] = __builtin_amdgcn_raw_buffer_load_b128(rr, yoff[q], 0, 0);
+    }
+    unsigned char *sp = body + j * G::PITCH + 64 * wave + 4 * g;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
         v4i par[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) par[r] = lpar[16 * t + 4 * g + r];
-        auto tile = [&](auto mode) __attribute__((always_inline)) {
-            constexpr int MODE = decltype(mode)::value;
+        for (int r = 0; r < 4; ++r) par[r] = lpar[64 * wave + 16 * t + 4 * g + r];
+        auto tile = [&](auto form) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                int v[4];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = requant_mode<MODE>(acc[t][i][r], par[r], lo, hi);
-                if (has_res) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = med3_i32(v[r] + sbyte(res[i], r), m128, p127);
-                }
-                *reinterpret_cast<uint32_t *>(stage + (16 * i + j) * kGemmStageStride + 16 * t + 4 * g) =
-                    pack4_low_bytes(v[0], v[1], v[2], v[3]);
+            for (int i = 0; i < PT; i += 2) {
+                uint32_t o0, o1;
+                requant_pair4<decltype(form)::value>(acc[i][t], acc[i + 1][t], par, lo, hi, o0, o1);
+                *reinterpret_cast<uint32_t *>(sp + 16 * i * G::PITCH + 16 * t) = o0;
+                *reinterpret_cast<uint32_t *>(sp + 16 * (i + 1) * G::PITCH + 16 * t) = o1;
             }
         };
+        const int form = pair_form<PRELU>(par, a.lo, a.hi);
         if constexpr (PRELU) {
-            tile(std::integral_constant<int, 2>{});
+            if (form == kPairPreluFull) tile(std::integral_constant<int, kPairPreluFull>{});
+            else tile(std::integral_constant<int, kPairPreluAny>{});
         } else {
-            const bool shift0 = par[0][3] == 0 || par[1][3] == 0 || par[2][3] == 0 || par[3][3] == 0;
-            if (__builtin_amdgcn_ballot_w64(shift0) == 0) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) par[r][3] -= 1;
-                tile(std::integral_constant<int, 0>{});
-            } else {
-                tile(std::integral_constant<int, 1>{});
-            }
-        }
-        if (has_res) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) res[i] = resn[i];
+            if (form == kPairRelu) tile(std::integral_constant<int, kPairRelu>{});
+            else if (form == kPairFull) tile(std::integral_constant<int, kPairFull>{});
+            else tile(std::integral_constant<int, kPairAny>{});
         }
     }
-    // (a wavefront reads back only what it wrote itself: no barrier)
+    lds_barrier();
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int piece = lane + 64 * q;
-        const int px = piece >> 3, c16 = piece & 7;
-        const v4i v = *reinterpret_cast<const v4i *>(stage + px * kGemmStageStride + 16 * c16);
-        const long long o = (long long)(m0 + px) * Nc + n0 + 16 * c16;
-        const bool ok = n0 + 16 * c16 < Nc && o < (long long)kOobOffset;
-        store_b128_guarded(v, ry, ok ? (int)o : kOobOffset);
+    for (int q = 0; q < G::NP; ++q) {
+        const int idx = tid + 256 * q;
+        v4i v = *reinterpret_cast<const v4i *>(body + (idx / PPR) * G::PITCH + 16 * (idx % PPR));
+        if (a.residual) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = (int)add_sat_i8x4((uint32_t)v[r], (uint32_t)res[q][r]);
+        }
+        store_b128_guarded(v, ry, yoff[q]);
     }
-    GEMM_STAMP(3);
 }
 
-PwKernelFn pw_gemm_select(bool prelu)
+template <int PT> static GemmTile gemm_tile(bool prelu)
 {
-    return prelu ? &pw_gemm_kernel<true> : &pw_gemm_kernel<false>;
+    using G = GemmGeom<PT>;
+    return {G::TM, G::TN, PT == 8 ? 2 : PT == 4 ? 3 : 4, G::LDS, prelu ? &pw_gemm_kernel<PT, true> : &pw_gemm_kernel<PT, false>};
+}
+
+GemmTile pw_gemm_tile(int pt, bool prelu)
+{
+    return pt == 8 ? gemm_tile<8>(prelu) : pt == 4 ? gemm_tile<4>(prelu) : gemm_tile<2>(prelu);
 }
 
 }  // namespace prom
-
-#ifdef PROM_TIMELINE
-extern "C" int prom_debug_gemm_stamps(unsigned long long *host)
-{
-    if (hipDeviceSynchronize() != hipSuccess) return PROM_EHIP;
-    return hipMemcpyFromSymbol(host, HIP_SYMBOL(prom::g_gemm_stamps), sizeof(unsigned long long) * 1024 * 4) == hipSuccess ? PROM_OK : PROM_EHIP;
-}
-#endif

@@ -1,0 +1,48 @@
+"""The tile kernel of the pointwise layers at the sizes where it can go wrong: every number of pixel tiles
+per wavefront, 1 to 9 k steps (whole and broken groups of four), ragged pixel counts, column tiles that
+the channels do not fill, and every form of its epilogue, against the CPU oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+from workloads import make_pw_layer
+from workloads.generators import prelu_mult_neg
+from gpu_util import assert_same, dev
+
+pytestmark = pytest.mark.gpu
+
+# n, h, w, cin, cout
+SHAPES = [(1, 1, 1, 64, 256), (1, 9, 9, 128, 256), (3, 7, 5, 192, 208), (1, 13, 17, 320, 512), (1, 5, 7, 448, 1024),
+          (1, 3, 11, 576, 272), (16, 14, 14, 512, 1024), (7, 55, 57, 64, 256), (5, 53, 51, 128, 496)]
+# window, shift range, PReLU: [0, 127] with and without shifts below 2, [-128, 127] with and without shift 0,
+# another window, PReLU in the full window, with shift 0 and in another window
+FORMS = [((0, 127), (2, 9), False), ((0, 127), (1, 6), False), ((-128, 127), (1, 9), False), ((-128, 127), (0, 5), False),
+         ((-20, 90), (2, 9), False), ((-128, 127), (1, 9), True), ((-128, 127), (0, 4), True), ((-100, 127), (1, 9), True)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("res", [False, True])
+def test_tile_kernel(shape, res):
+    import torch
+    import paper_2505_03254_amd as P
+    n, h, w, cin, cout = shape
+    forms = FORMS if n * h * w < 2000 else FORMS[::3] + FORMS[5:6]
+    for f, (window, shifts, prelu) in enumerate(forms):
+        L = make_pw_layer(7000 + 31 * cin + cout + f, n, h, w, cin, cout, signed_x=True, act_window=window,
+                          with_residual=True, shift_range=shifts)
+        L.bias[::5] *= 100                       # some channels saturate on either side
+        L.residual.reshape(-1)[::11] = -128
+        L.residual.reshape(-1)[::13] = 127
+        neg = prelu_mult_neg(f, L.mult) if prelu else None
+        rq = P.Requant(dev(L.bias), dev(L.mult), dev(L.shift), window[0], window[1], dev(neg) if prelu else None)
+        r = L.residual if res else None
+        want = oracle.pw_conv(L.x, L.weight, L.bias, L.mult, L.shift, window[0], window[1], residual=r, mult_neg=neg)
+        x, wp = dev(L.x), dev(P.prom_pack_ternary(L.weight))
+        y = dev(L.residual).clone() if res else None   # in place
+        for plan in (P.PwPlan(k_outer=1), None):
+            got = P.prom_pw_conv_ex(x, wp, cout, rq, dev(r) if res else None, plan=plan)
+            assert_same(got.cpu().numpy(), want, f"{shape} {window} {shifts} prelu={prelu} plan={plan}")
+        if res:
+            P.prom_pw_conv(x, wp, cout, rq, y, y=y)
+            torch.cuda.synchronize()
+            assert_same(y.cpu().numpy(), want, f"{shape} in place")
