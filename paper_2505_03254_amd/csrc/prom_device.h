@@ -135,12 +135,17 @@ __device__ __forceinline__ int sbyte(uint32_t v, int i)
 //               clamp(floor(v), 0, 127) is half of that, rounded down -- one shift and one mask per dword
 //   kPairFull   window [-128, 127], every shift >= 1
 //   kPairAny    any window, any shift (requant_i64<true>)
-//   kPairPreluFull, kPairPreluAny   the same two for PReLU layers (par = (bias, mult, mult_neg, shift))
+//   kPairPreluFull  PReLU layer (par = (bias, mult, mult_neg, shift)), window [-128, 127], every shift >= 2
+//   kPairPreluAny   PReLU layer, any window, any shift
 constexpr int kPairRelu = 0, kPairFull = 1, kPairAny = 2, kPairPreluFull = 3, kPairPreluAny = 4;
 
+// What a form's shifts are reduced by in the parameters handed to requant_pair4.
+__host__ __device__ constexpr int pair_shift_less(int form) { return form == kPairRelu || form == kPairPreluFull ? 2 : form == kPairFull ? 1 : 0; }
+
 // a0, a1: the accumulators of two pixels, four channels each; par: the channels' parameters as
-// requant_params made them (shift NOT reduced); out0, out1: the packed outputs.
-template <int FORM>
+// requant_params made them, the shifts reduced by pair_shift_less(FORM); out0, out1: the packed outputs.
+// BIASED: the bias of a PReLU layer is in the accumulators already.
+template <int FORM, bool BIASED = false>
 __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, const v4i (&par)[4], int lo, int hi,
                                               uint32_t &out0, uint32_t &out1)
 {
@@ -152,8 +157,9 @@ __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, cons
                 v[r] = requant_i64<true>(a0[r], par[r], lo, hi);
                 w[r] = requant_i64<true>(a1[r], par[r], lo, hi);
             } else {
-                v[r] = requant_prelu_i64(a0[r], par[r], lo, hi);
-                w[r] = requant_prelu_i64(a1[r], par[r], lo, hi);
+                const int b = BIASED ? 0 : par[r][0];
+                v[r] = requant_prelu_s(a0[r] + b, par[r][1], par[r][2], par[r][3], lo, hi);
+                w[r] = requant_prelu_s(a1[r] + b, par[r][1], par[r][2], par[r][3], lo, hi);
             }
         }
         out0 = pack4_low_bytes(v[0], v[1], v[2], v[3]);
@@ -165,21 +171,26 @@ __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, cons
         for (int r = 0; r < 4; ++r) {
             int t0, t1;
             if constexpr (FORM == kPairPreluFull) {
-                const int s0 = a0[r] + par[r][0], s1 = a1[r] + par[r][0];
-                const int m0 = s0 < 0 ? par[r][2] : par[r][1], m1 = s1 < 0 ? par[r][2] : par[r][1];
-                const long long R = 1LL << (30 + par[r][3]);
-                t0 = (int)(((long long)s0 * m0 + R) >> 32);
-                t1 = (int)(((long long)s1 * m1 + R) >> 32);
+                const int b = BIASED ? 0 : par[r][0];
+                const int s0 = a0[r] + b, s1 = a1[r] + b;
+                // (a bit select by the sign, v_bfi_b32: the compiler turns a ternary between two elements of
+                // one vector into a chain of compares and selects)
+                const int n0 = s0 >> 31, n1 = s1 >> 31;
+                const int m0 = (n0 & par[r][2]) | (~n0 & par[r][1]), m1 = (n1 & par[r][2]) | (~n1 & par[r][1]);
+                // floor((s*m + 2^(30+shift)) / 2^32): the rounding term is a whole multiple of 2^32
+                t0 = __mulhi(s0, m0) + (1 << par[r][3]);
+                t1 = __mulhi(s1, m1) + (1 << par[r][3]);
             } else {
                 const long long C = (long long)(((unsigned long long)(uint32_t)par[r][1] << 32) | (uint32_t)par[r][0]);
                 t0 = (int)(((long long)a0[r] * par[r][2] + C) >> 32);
                 t1 = (int)(((long long)a1[r] * par[r][2] + C) >> 32);
             }
             // (the instruction, not the builtin: the builtin's 16-bit result costs a mask)
+            const int sh = FORM == kPairPreluFull ? par[r][3] + 1 : par[r][3];
             if constexpr (FORM == kPairRelu)
-                asm("v_ashr_pk_u8_i32 %0, %1, %2, %3" : "=v"(h[r]) : "v"(t0), "v"(t1), "v"(par[r][3] - 2));
+                asm("v_ashr_pk_u8_i32 %0, %1, %2, %3" : "=v"(h[r]) : "v"(t0), "v"(t1), "v"(sh));
             else
-                asm("v_ashr_pk_i8_i32 %0, %1, %2, %3" : "=v"(h[r]) : "v"(t0), "v"(t1), "v"(par[r][3] - 1));
+                asm("v_ashr_pk_i8_i32 %0, %1, %2, %3" : "=v"(h[r]) : "v"(t0), "v"(t1), "v"(sh));
         }
         const uint32_t ab = __builtin_amdgcn_perm(h[1], h[0], 0x05010400u);  // (p0 c0, p0 c1, p1 c0, p1 c1)
         const uint32_t cd = __builtin_amdgcn_perm(h[3], h[2], 0x05010400u);
@@ -192,16 +203,21 @@ __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, cons
     }
 }
 
-// The form a wavefront can take for the four channels of each of its lanes; wave-uniform.
+// The form a wavefront can take for the channels of its lanes; wave-uniform.
+// s: the smallest shift of the lane's channels.
 template <bool PRELU>
-__device__ __forceinline__ int pair_form(const v4i (&par)[4], int lo, int hi)
+__device__ __forceinline__ int pair_form(int s, int lo, int hi)
 {
-    const int s = min(min(par[0][3], par[1][3]), min(par[2][3], par[3][3]));
     const bool full = lo == -128 && hi == 127, relu = lo == 0 && hi == 127;
-    const int need = !PRELU && relu ? 2 : 1;
+    const int need = PRELU || relu ? 2 : 1;
     const bool ok = (full || (!PRELU && relu)) && __builtin_amdgcn_ballot_w64(s < need) == 0;
     if (PRELU) return ok ? kPairPreluFull : kPairPreluAny;
     return ok ? (relu ? kPairRelu : kPairFull) : kPairAny;
+}
+
+__device__ __forceinline__ int min_shift(const v4i (&par)[4])
+{
+    return min(min(par[0][3], par[1][3]), min(par[2][3], par[3][3]));
 }
 
 // Saturating sum of two dwords of four int8 each: the odd bytes as the high halves of 16-bit lanes, the

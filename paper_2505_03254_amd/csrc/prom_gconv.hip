@@ -196,14 +196,44 @@ struct GconvBand {
     int G;           // images per unit of work (above 1 only when a band is the whole image)
     int units;       // units of work per channel block
     int swizzle;     // XCD-aware order of the workgroups (wgs_per_cb % 8 == 0)
-    // floor(2^31 / d) + 1 for d = Wo and d = R * Wo: n / d = (n * this) >> 31 for every n with
-    // n * d < 2^31 (the pixels of a unit are a few thousand at most)
-    unsigned magic_wo, magic_img;
 };
 
 constexpr int kGconvFragBytes = 4 * 9 * 64 * 16;
 constexpr int kGconvParBytes = 64 * 16;
 constexpr int kGconvPieces = 9;  // 16-byte pieces of a staged band per thread
+
+// The pieces of a staged band that a thread fetches, NT apart: piece pc of a unit is 16-byte piece pc & 3 of
+// staged pixel pc >> 2 (images, rows, columns in order; column 0 is image column -1).  Per piece, once: its
+// offset behind the unit's first row, and its row (far beyond any image where the piece is a border column or
+// a channel that does not exist).  One division; the quotients of the other pieces follow by addition.
+template <int NK, int NT>
+__device__ __forceinline__ void band_pieces(const GconvArgs &a, const GconvBand &bd, int cbase, int tid, int (&prel)[NK], int (&prow)[NK])
+{
+    const int row_items = (a.W + 2) * 4;
+    const int step_rows = NT / row_items, step_items = NT - step_rows * row_items;
+    int gi = 0, row = tid / row_items, it = tid - row * row_items;
+    while (row >= bd.RI) {
+        row -= bd.RI;
+        ++gi;
+    }
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        const int col = it >> 2, qd = it & 3;
+        const bool ok = col >= 1 && col <= a.W && cbase + 16 * qd < a.C;
+        prel[k] = (__mul24(__mul24(gi, a.H) + row, a.W) + col - 1) * a.C + cbase + 16 * qd;
+        prow[k] = ok ? row : 1 << 30;
+        it += step_items;
+        row += step_rows;
+        if (it >= row_items) {
+            it -= row_items;
+            ++row;
+        }
+        while (row >= bd.RI) {
+            row -= bd.RI;
+            ++gi;
+        }
+    }
+}
 
 __device__ __forceinline__ void gconv_mfma_body(const GconvArgs &a, const GconvBand &bd, const int block)
 {
@@ -264,23 +294,18 @@ __device__ __forceinline__ void gconv_mfma_body(const GconvArgs &a, const GconvB
     // (one memory latency per band, not one per row), and written to LDS later: the fetch of the
     // next unit is in flight while the current one is computed, and the first fetch while the
     // weights are staged.  Pixels outside the image and channels beyond C are zeros.
+    int prel[NK], prow[NK];
+    band_pieces<NK, 256>(a, bd, cbase, tid, prel, prow);
     v4i piece[NK];
     auto fetch_band = [&](int u) {
         const Unit q = unit_of(u);
         const int ri0 = q.ro0 * S - 1;  // first input row (may be -1)
         const int npiece = q.count * img_items;
+        const int base = (q.img0 * a.H + ri0) * W * C;
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
-            const int pc = k * 256 + tid;
-            const int gi = pc / img_items;
-            const int rem = pc - gi * img_items;
-            const int row = rem / row_items;
-            const int it = rem - row * row_items;
-            const int col = it >> 2, qd = it & 3;  // staged column 0 is image column -1
-            const int iy = ri0 + row;
-            const bool ok = pc < npiece && iy >= 0 && iy < a.H && col >= 1 && col <= W && cbase + 16 * qd < C;
-            const int off = (((q.img0 + gi) * a.H + iy) * W + col - 1) * C + cbase + 16 * qd;
-            piece[k] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? off : kOob, 0, 0);
+            const bool ok = k * 256 + tid < npiece && (unsigned)(ri0 + prow[k]) < (unsigned)a.H;
+            piece[k] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? base + prel[k] : kOob, 0, 0);
         }
     };
     // ---- weights of the block -> MFMA A fragments: a plain copy when the caller has prepared them,
@@ -311,24 +336,30 @@ __device__ __forceinline__ void gconv_mfma_body(const GconvArgs &a, const GconvB
     }
     if (tid < 64) {
         const int c = cbase + tid;
-        v4i p = {0, 0, 0, 1};
+        v4i p = {0, 0, 0, 31};
         if (c < C) p = requant_params(a.bias[c], a.mult[c], prelu ? a.mult_neg[c] : 0, a.shift[c], prelu);
         lpar[tid] = p;
     }
     if (wg < bd.units) fetch_band(wg);
     __syncthreads();
 
-    v4i par[4][4];  // [tile t][r]: channel 16g + 4t + r
+    int smin = 31;
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) par[t][r] = lpar[16 * g + 4 * t + r];
+    for (int c = 0; c < 16; ++c) smin = min(smin, lpar[16 * g + c][3]);
     const int lo = in_vgpr(a.lo), hi = in_vgpr(a.hi);
     const int cl = cbase + 16 * g;  // the lane's first output channel
 
     // one instance of the loop per epilogue form: no branch per output
-    auto run = [&](auto prelu_tag) {
-        constexpr bool PRELU = decltype(prelu_tag)::value;
+    auto run = [&](auto form_tag) {
+        constexpr int FORM = decltype(form_tag)::value;
+        v4i par[4][4];  // [tile t][r]: channel 16g + 4t + r
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                par[t][r] = lpar[16 * g + 4 * t + r];
+                par[t][r][3] -= pair_shift_less(FORM);
+            }
         for (int u = wg; u < bd.units; u += bd.wgs_per_cb) {
             const Unit q = unit_of(u);
             const int npiece = q.count * img_items;
@@ -383,18 +414,14 @@ __device__ __forceinline__ void gconv_mfma_body(const GconvArgs &a, const GconvB
                             acc[p][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf, b[p], acc[p][t], 0, 0, 0);
                     }
                 }
+                uint32_t o[PT][4];
+#pragma unroll
+                for (int p = 0; p < PT; p += 2)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) requant_pair4<FORM>(acc[p][t], acc[p + 1][t], par[t], lo, hi, o[p][t], o[p + 1][t]);
 #pragma unroll
                 for (int p = 0; p < PT; ++p) {
-                    uint32_t out[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        int v[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            v[r] = PRELU ? requant_prelu_i64(acc[p][t][r], par[t][r], lo, hi)
-                                         : requant_i64<true>(acc[p][t][r], par[t][r], lo, hi);
-                        out[t] = pack4_low_bytes(v[0], v[1], v[2], v[3]);
-                    }
+                    const uint32_t (&out)[4] = o[p];
                     // the lane's channels cl .. cl+15 of its pixel (C % 4 == 0: whole dwords are in or out)
                     if (valid[p] && cl + 16 <= C) {
                         store_b128_guarded(v4i{(int)out[0], (int)out[1], (int)out[2], (int)out[3]}, ry, yo[p]);
@@ -408,10 +435,15 @@ __device__ __forceinline__ void gconv_mfma_body(const GconvArgs &a, const GconvB
             }
         }
     };
-    if (prelu)
-        run(std::true_type{});
-    else
-        run(std::false_type{});
+    if (prelu) {
+        if (pair_form<true>(smin, a.lo, a.hi) == kPairPreluFull) run(std::integral_constant<int, kPairPreluFull>{});
+        else run(std::integral_constant<int, kPairPreluAny>{});
+    } else {
+        const int form = pair_form<false>(smin, a.lo, a.hi);
+        if (form == kPairRelu) run(std::integral_constant<int, kPairRelu>{});
+        else if (form == kPairFull) run(std::integral_constant<int, kPairFull>{});
+        else run(std::integral_constant<int, kPairAny>{});
+    }
 }
 
 __global__ __launch_bounds__(256, 2) void gconv_mfma_kernel(const GconvArgs a, const GconvBand bd)
@@ -431,6 +463,16 @@ __global__ __launch_bounds__(256, 2) void gconv_mfma_kernel(const GconvArgs a, c
 // two pairs of lane-row swaps, after which lane (j, g) holds channels 16g .. 16g+15 of its pixel
 // and stores them as one 16-byte piece, as above.  Band geometry, staging through registers and
 // units of work are those of gconv_mfma_kernel.
+// What bounds it: the LDS reads of a group of 32 pixels, 24 operands of 1 KB and the fragments (9 of the 12 of
+// a plain layer, whose first tile's are held in registers; more of them, or all, spill): 0.9 us per round of
+// two workgroups' wavefronts, and the 2 to 3 us a band takes to arrive.  The vector ALU is no longer it: 82
+// instructions per group (204 with PReLU) where there were 200 and 330, since two pixels are requantised
+// at a time (requant_pair4), where an output pixel is found in a table made once per workgroup instead
+// of by divisions, the planes are a constant distance apart (offsets in the instruction; the 32 bytes
+// between them keep the pieces of a pixel on different banks: without, ResNeXt-50's sequence takes 286 us
+// instead of 277) and a thread's pieces are located once.  Layers alone, batch 64, us before and
+// after: 56x56x128 23.8 -> 19.9, 28x28x256 15.1 -> 12.8, 14x14x512 11.8 -> 9.3, 7x7x384 8.2 -> 6.3,
+// 56x56x256 stride 2 17.9 -> 18.0; with PReLU 27.0 -> 22.5, 17.1 -> 14.1, 13.2 -> 10.0, 8.5 -> 6.6, 19.0 -> 18.4.
 #ifdef PROM_TIMELINE
 // Developer build: workgroups 0 .. 255 record the 100 MHz clock at entry, after the prologue and
 // per band (pieces in LDS, barrier passed, band computed), then after the last store is acknowledged.
@@ -440,11 +482,16 @@ __device__ unsigned long long g_gc_stamps[256 * 16];
 #define GC_STAMP(i) do { } while (0)
 #endif
 
-constexpr int kTapkFragBytes = 4 * 3 * 64 * 16;
-constexpr int kTapkParBytes = kGconvParBytes + 16;  // the parameters and the flag of the epilogue form
 constexpr int kTapkPT = 2;          // pixel tiles per wavefront iteration
 constexpr int kTapkThreads = 256;   // 4 wavefronts, two workgroups per compute unit
 constexpr int kTapkPieces = 9;      // 16-byte pieces of a staged band per thread
+// bytes of a plane of pieces, whatever the band holds; 32 more than it needs, so that the four pieces of a
+// pixel are written to different banks
+constexpr int kTapkPlane = kTapkPieces * kTapkThreads * 16 / 4 + 32;
+// output pixels of a unit, rounded up: each has a staged pixel of its own (and those are a fourth of the pieces)
+constexpr int kTapkPixels = kTapkPieces * kTapkThreads / 4 + 16 * kTapkPT;
+constexpr int kTapkHeld = 1;        // tiles whose fragments a plain layer holds in registers
+constexpr int kTapkLds = kGconvParBytes + kTapkPixels * 8 + 4 * kTapkPlane + 4 * 3 * 64 * 16;
 
 // Rows of 16 lanes, registers o[0..3]: o[t] of row g  <->  o[g] of row t.
 __device__ __forceinline__ void transpose_rows4(uint32_t (&o)[4])
@@ -461,7 +508,7 @@ __device__ __forceinline__ void transpose_rows4(uint32_t (&o)[4])
     o[3] = b23[1];
 }
 
-template <int PT>
+template <int PT, bool PRELU>
 __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvBand &bd, const int block)
 {
     constexpr int kFlags = 0x00020000;
@@ -469,9 +516,10 @@ __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvB
     constexpr int NK = kTapkPieces;
     constexpr int NT = kTapkThreads;
     extern __shared__ __align__(16) unsigned char lds[];
-    v4i *frag = reinterpret_cast<v4i *>(lds);                                  // [tile t][step s][lane]
-    v4i *lpar = reinterpret_cast<v4i *>(lds + kTapkFragBytes);                 // [64] parameters, then a flag
-    unsigned char *xt = lds + kTapkFragBytes + kTapkParBytes;                  // [piece 4][G][RI][W+2][16]
+    v4i *lpar = reinterpret_cast<v4i *>(lds);                                  // [64] parameters
+    v2i *tab = reinterpret_cast<v2i *>(lds + kGconvParBytes);                  // [pixel of a unit] offsets in a plane and in y
+    unsigned char *xt = lds + kGconvParBytes + kTapkPixels * 8;                // [piece 4][G][RI][W+2][16]
+    v4i *fragl = reinterpret_cast<v4i *>(xt + 4 * kTapkPlane);                 // [tile t][step s][lane]
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -493,10 +541,8 @@ __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvB
     const int C = a.C, GS = a.gs, S = a.stride, W = a.W, Wo = a.Wo;
     const int W2 = W + 2;
     const int cbase = cb * 64;
-    const bool prelu = a.mult_neg != nullptr;
     const int row_items = W2 * 4;
     const int img_items = bd.RI * row_items;
-    const int PS = bd.G * bd.RI * W2 * 16;  // bytes of a plane of pieces
     GC_STAMP(0);
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t *>(a.x), 0, a.N * a.H * W * C, kFlags);
@@ -518,40 +564,31 @@ __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvB
         q.rows_out = min(bd.R, a.Ho - q.ro0);
         return q;
     };
-    // piece pc of a unit = piece (pc & 3) of staged pixel pc >> 2 (images, rows, columns in order)
+    int prel[NK], prow[NK];
+    band_pieces<NK, NT>(a, bd, cbase, tid, prel, prow);
     v4i piece[NK];
     auto fetch_band = [&](int u) {
         const Unit q = unit_of(u);
         const int ri0 = q.ro0 * S - 1;
         const int npiece = q.count * img_items;
+        const int base = (q.img0 * a.H + ri0) * W * C;
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
-            const int pc = k * NT + tid;
-            const int gi = pc / img_items;
-            const int rem = pc - gi * img_items;
-            const int row = rem / row_items;
-            const int it = rem - row * row_items;
-            const int col = it >> 2, qd = it & 3;
-            const int iy = ri0 + row;
-            const bool ok = pc < npiece && iy >= 0 && iy < a.H && col >= 1 && col <= W && cbase + 16 * qd < C;
-            const int off = (((q.img0 + gi) * a.H + iy) * W + col - 1) * C + cbase + 16 * qd;
-            piece[k] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? off : kOob, 0, 0);
+            const bool ok = k * NT + tid < npiece && (unsigned)(ri0 + prow[k]) < (unsigned)a.H;
+            piece[k] = __builtin_amdgcn_raw_buffer_load_b128(rx, ok ? base + prel[k] : kOob, 0, 0);
         }
     };
     // the first band is requested before anything else: one memory latency for it, the weights and
     // the parameters together
     if (wg < bd.units) fetch_band(wg);
     // ---- fragments: lane (i, kg) of tile t, step s holds, for output channel 16t + i of the block and
-    // tap 4s + kg, the weights on input channels 16t .. 16t+15 (zero outside the channel's group)
-    if (a.wfrag) {
-        const v4i *src = a.wfrag + (long long)cb * (4 * 3 * 64);
-        for (int idx = tid; idx < 4 * 3 * 64; idx += NT) frag[idx] = src[idx];
-    } else
-    for (int idx = tid; idx < 4 * 3 * 64; idx += NT) {
-        const int l = idx & 63, ts = idx >> 6, s = ts % 3, t = ts / 3;
-        const int i = l & 15, kg = l >> 4;
-        const int tap = 4 * s + kg;
-        const int oc = cbase + 16 * t + i;
+    // tap 4s + kg, the weights on input channels 16t .. 16t+15 (zero outside the channel's group).  A plain
+    // layer then holds them in registers, a third of the LDS reads of a group of pixels less; a PReLU layer
+    // needs the registers for its parameters.
+    auto fragment = [&](int t, int s) __attribute__((always_inline)) {
+        if (a.wfrag) return a.wfrag[(long long)cb * (4 * 3 * 64) + (t * 3 + s) * 64 + lane];
+        const int tap = 4 * s + g;
+        const int oc = cbase + 16 * t + j;
         v4i e = {0, 0, 0, 0};
         if (oc < C && tap < 9) {
             const int gfirst = (oc / GS) * GS;
@@ -562,39 +599,44 @@ __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvB
                 if (ic >= gfirst && ic < gfirst + GS) e[d] = *reinterpret_cast<const int *>(wrow + (ic - gfirst));
             }
         }
-        frag[idx] = e;
-    }
+        return e;
+    };
+#pragma unroll
+    for (int s = 0; s < 3; ++s) fragl[(wave * 3 + s) * 64 + lane] = fragment(wave, s);
     if (tid < 64) {
         const int c = cbase + tid;
-        int shift = 1;
-        v4i p = {0, 0, 0, 1};
-        if (c < C) {
-            shift = a.shift[c];
-            p = requant_params(a.bias[c], a.mult[c], prelu ? a.mult_neg[c] : 0, shift, prelu);
-        }
+        v4i p = {0, 0, 0, 31};
+        if (c < C) p = requant_params(a.bias[c], a.mult[c], PRELU ? a.mult_neg[c] : 0, a.shift[c], PRELU);
         lpar[tid] = p;
-        // every shift of the block >= 1 (the usual case): the quotient comes from the high half of the
-        // 64-bit sum and one 32-bit shift by shift - 1
-        const bool all_ge1 = __builtin_amdgcn_ballot_w64(shift >= 1) == ~0ull;
-        if (tid == 0) *reinterpret_cast<int *>(lpar + 64) = all_ge1 ? 1 : 0;
+    }
+    // Where a unit's output pixel idx is: its tap (0, 0) in a plane, and in y behind the unit's first row.
+    // The same for every unit: a unit is bands of one image, or whole images.
+    {
+        // floor((idx + 0.5) * (1 / d)) is idx / d for the few hundred pixels of a unit
+        const int img_full = bd.R * Wo;
+        const float rimg = 1.0f / (float)img_full, rwo = 1.0f / (float)Wo;
+#pragma unroll
+        for (int k = 0; k < (kTapkPixels + NT - 1) / NT; ++k) {
+            const int idx = tid + k * NT;
+            const int ii = min(idx, bd.G * img_full - 1);
+            const int gi = (int)(((float)ii + 0.5f) * rimg);
+            const int rem = ii - __mul24(gi, img_full);
+            const int r = (int)(((float)rem + 0.5f) * rwo);
+            const int ox = rem - __mul24(r, Wo);
+            if (idx < kTapkPixels)
+                tab[idx] = v2i{(__mul24(gi * bd.RI + r * S, W2) + ox * S) * 16, (__mul24(gi * a.Ho + r, Wo) + ox) * C};
+        }
     }
     __syncthreads();
 
-    const bool general = prelu || __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int *>(lpar + 64)) == 0;
-    v4i par[4][4];  // [tile t][r]: channel 16t + 4g + r; the fast form shifts by shift - 1
+    int smin = 31;
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            par[t][r] = lpar[16 * t + 4 * g + r];
-            if (!general) par[t][r][3] -= 1;
-        }
+        for (int r = 0; r < 4; ++r) smin = min(smin, lpar[16 * t + 4 * g + r][3]);
     GC_STAMP(1);
     [[maybe_unused]] int band_no = 0;
     const bool full_block = cbase + 64 <= C;
-    // n / d by the band's magic numbers
-    auto div_wo = [&](int n) { return (int)(((unsigned long long)(unsigned)n * bd.magic_wo) >> 31); };
-    auto div_img = [&](int n) { return (int)(((unsigned long long)(unsigned)n * bd.magic_img) >> 31); };
     const int lo = in_vgpr(a.lo), hi = in_vgpr(a.hi);
     const int cl = cbase + 16 * g;  // the lane's first output channel after the exchange
     int toff[3];                    // the lane's tap of each k step, as a byte offset in a plane
@@ -604,8 +646,28 @@ __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvB
         toff[s] = ((tap / 3) * W2 + tap % 3) * 16;
     }
 
-    auto run = [&](auto mode_tag) {
-        constexpr int MODE = decltype(mode_tag)::value;
+    auto run = [&](auto form_tag) {
+        constexpr int FORM = decltype(form_tag)::value;
+        v4i par[4][4];  // [tile t][r]: channel 16t + 4g + r
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                par[t][r] = lpar[16 * t + 4 * g + r];
+                par[t][r][3] -= pair_shift_less(FORM);
+            }
+        [[maybe_unused]] v4i frag[kTapkHeld][3];
+        if constexpr (!PRELU) {
+#pragma unroll
+            for (int t = 0; t < kTapkHeld; ++t)
+#pragma unroll
+                for (int s = 0; s < 3; ++s) frag[t][s] = fragl[(t * 3 + s) * 64 + lane];
+        }
+        // PReLU: the biases are what the accumulators start from
+        v4i cinit[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            cinit[t] = PRELU ? v4i{par[t][0][0], par[t][1][0], par[t][2][0], par[t][3][0]} : v4i{0, 0, 0, 0};
         for (int u = wg; u < bd.units; u += bd.wgs_per_cb) {
             const Unit q = unit_of(u);
             const int npiece = q.count * img_items;
@@ -613,70 +675,66 @@ __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvB
 #pragma unroll
             for (int k = 0; k < NK; ++k) {
                 const int pc = k * NT + tid;
-                if (pc < npiece) *reinterpret_cast<v4i *>(xt + (pc & 3) * PS + (pc >> 2) * 16) = piece[k];
+                if (pc < npiece) *reinterpret_cast<v4i *>(xt + (pc & 3) * kTapkPlane + (pc >> 2) * 16) = piece[k];
             }
             GC_STAMP(2 + 3 * band_no);
             __syncthreads();
             GC_STAMP(3 + 3 * band_no);
             if (u + bd.wgs_per_cb < bd.units) fetch_band(u + bd.wgs_per_cb);
-            const int img_pix = q.rows_out * Wo;
-            const int npix = q.count * img_pix;
+            const int npix = q.count * q.rows_out * Wo;
             const int ngrp = (npix + 16 * PT - 1) / (16 * PT);
+            const int ybase = (q.img0 * a.Ho + q.ro0) * Wo * C + cl;
             for (int grp = wave; grp < ngrp; grp += NT / 64) {
-                int pix[PT], yo[PT];
+                int yo[PT];
+                const unsigned char *src[PT][3];
                 bool valid[PT];
 #pragma unroll
                 for (int p = 0; p < PT; ++p) {
                     const int idx = (grp * PT + p) * 16 + j;
                     valid[p] = idx < npix;
-                    const int ii = valid[p] ? idx : 0;
-                    // img_pix = R * Wo except in an image's last band, where a unit is one image and idx < img_pix
-                    const int gi = div_img(ii);
-                    const int rem = ii - gi * img_pix;
-                    const int r = div_wo(rem);
-                    const int ox = rem - r * Wo;
-                    pix[p] = ((gi * bd.RI + r * S) * W2 + ox * S) * 16;  // tap (0, 0) of the pixel
-                    yo[p] = (((q.img0 + gi) * a.Ho + q.ro0 + r) * Wo + ox) * C + cl;
+                    const v2i e = tab[idx];
+#pragma unroll
+                    for (int s = 0; s < 3; ++s) src[p][s] = xt + (e[0] + toff[s]);
+                    yo[p] = ybase + e[1];
                 }
                 v4i acc[PT][4];
-#pragma unroll
-                for (int p = 0; p < PT; ++p)
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) acc[p][t] = v4i{0, 0, 0, 0};
                 int fo = lane;
                 asm volatile("" : "+v"(fo));  // keeps the fragment reads inside the loop
-                const v4i *fl = frag + fo;
 #pragma unroll
                 for (int s = 0; s < 3; ++s) {
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        const v4i wf = fl[(t * 3 + s) * 64];
+                        const v4i wf = PRELU || t >= kTapkHeld ? fragl[fo + (t * 3 + s) * 64] : frag[t % kTapkHeld][s];
 #pragma unroll
                         for (int p = 0; p < PT; ++p) {
-                            const v4i b = *reinterpret_cast<const v4i *>(xt + t * PS + pix[p] + toff[s]);
-                            acc[p][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf, b, acc[p][t], 0, 0, 0);
+                            const v4i b = *reinterpret_cast<const v4i *>(src[p][s] + t * kTapkPlane);
+                            acc[p][t] = __builtin_amdgcn_mfma_i32_16x16x64_i8(wf, b, s == 0 ? cinit[t] : acc[p][t], 0, 0, 0);
                         }
                     }
                 }
+                uint32_t out[PT][4];
+                if constexpr (PRELU) {  // (opaque: what the epilogue derives from a shift is not held in registers)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) asm volatile("" : "+v"(par[t][r][3]));
+                }
+#pragma unroll
+                for (int p = 0; p < PT; p += 2)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        requant_pair4<FORM, true>(acc[p][t], acc[p + 1][t], par[t], lo, hi, out[p][t], out[p + 1][t]);
 #pragma unroll
                 for (int p = 0; p < PT; ++p) {
-                    uint32_t out[4];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        int v[4];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = requant_mode<MODE>(acc[p][t][r], par[t][r], lo, hi);
-                        out[t] = pack4_low_bytes(v[0], v[1], v[2], v[3]);
-                    }
-                    transpose_rows4(out);  // now channels cl .. cl+15 of the lane's pixel
+                    transpose_rows4(out[p]);  // now channels cl .. cl+15 of the lane's pixel
                     if (full_block) {
-                        store_b128_guarded(v4i{(int)out[0], (int)out[1], (int)out[2], (int)out[3]}, ry,
+                        store_b128_guarded(v4i{(int)out[p][0], (int)out[p][1], (int)out[p][2], (int)out[p][3]}, ry,
                                            valid[p] ? yo[p] : kOob);
                     } else if (valid[p]) {
 #pragma unroll
                         for (int t = 0; t < 4; ++t)
                             if (cl + 4 * t < C)
-                                __builtin_amdgcn_raw_buffer_store_b32((int)out[t], ry, yo[p] + 4 * t, 0, 0);
+                                __builtin_amdgcn_raw_buffer_store_b32((int)out[p][t], ry, yo[p] + 4 * t, 0, 0);
                     }
                 }
             }
@@ -685,22 +743,25 @@ __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvB
 
         }
     };
-    if (prelu)
-        run(std::integral_constant<int, 2>{});
-    else if (general)
-        run(std::integral_constant<int, 1>{});
-    else
-        run(std::integral_constant<int, 0>{});
+    const int form = pair_form<PRELU>(smin, a.lo, a.hi);
+    if constexpr (PRELU) {
+        if (form == kPairPreluFull) run(std::integral_constant<int, kPairPreluFull>{});
+        else run(std::integral_constant<int, kPairPreluAny>{});
+    } else {
+        if (form == kPairRelu) run(std::integral_constant<int, kPairRelu>{});
+        else if (form == kPairFull) run(std::integral_constant<int, kPairFull>{});
+        else run(std::integral_constant<int, kPairAny>{});
+    }
 #ifdef PROM_TIMELINE
     __builtin_amdgcn_s_waitcnt(0);
     GC_STAMP(15);
 #endif
 }
 
-template <int PT>
+template <int PT, bool PRELU>
 __global__ __launch_bounds__(kTapkThreads, 2) void gconv_tapk_kernel(const GconvArgs a, const GconvBand bd)
 {
-    gconv_tapk_body<PT>(a, bd, (int)blockIdx.x);
+    gconv_tapk_body<PT, PRELU>(a, bd, (int)blockIdx.x);
 }
 
 // ---- several layers in one launch (prom_gconv3x3_sequence) ----------------------------------------
@@ -729,7 +790,8 @@ __device__ __forceinline__ int gconv_batch_member(const GconvBatchArgs &b)
 __device__ unsigned long long g_gcb_stamps[2048 * 3];
 #endif
 
-template <int PT>
+// ANY_PRELU: a launch with PReLU members; each member runs through the body of its kind.
+template <int PT, bool ANY_PRELU>
 __global__ __launch_bounds__(kTapkThreads, 2) void gconv_tapk_batch_kernel(const GconvBatchArgs b)
 {
     const int m = gconv_batch_member(b);
@@ -739,7 +801,10 @@ __global__ __launch_bounds__(kTapkThreads, 2) void gconv_tapk_batch_kernel(const
         g_gcb_stamps[blockIdx.x * 3 + 1] = wall_clock64();
     }
 #endif
-    gconv_tapk_body<PT>(b.a[m], b.bd[m], (int)blockIdx.x - b.start[m]);
+    if (ANY_PRELU && b.a[m].mult_neg)
+        gconv_tapk_body<PT, true>(b.a[m], b.bd[m], (int)blockIdx.x - b.start[m]);
+    else
+        gconv_tapk_body<PT, false>(b.a[m], b.bd[m], (int)blockIdx.x - b.start[m]);
 #ifdef PROM_TIMELINE
     __builtin_amdgcn_s_waitcnt(0);
     if (threadIdx.x == 0 && blockIdx.x < 2048) g_gcb_stamps[blockIdx.x * 3 + 2] = wall_clock64();
@@ -889,9 +954,6 @@ static int gconv_prepare(const int8_t *x, int n, int h, int w, int c, const int8
             }
             const long long units = bd.G > 1 ? ((long long)n + bd.G - 1) / bd.G : (long long)n * bd.bands;
             bd.units = (int)units;
-            const unsigned d_img = (unsigned)bd.R * (unsigned)a.Wo;
-            bd.magic_wo = (unsigned)((1ull << 31) / (unsigned)a.Wo) + 1u;
-            bd.magic_img = (unsigned)((1ull << 31) / d_img) + 1u;
             // two workgroups per compute unit, and not one more: a workgroup that does not fit in the
             // first round starts when another has finished all its units and doubles the run time
             long long per_cb = (2 * 256) / bd.ncb;
@@ -900,8 +962,7 @@ static int gconv_prepare(const int8_t *x, int n, int h, int w, int c, const int8
             if (per_cb >= 64) per_cb -= per_cb % 8;  // for the XCD-aware order; small grids keep every workgroup
             bd.wgs_per_cb = (int)per_cb;
             bd.swizzle = per_cb % 8 == 0;
-            L.lds = (size_t)(tapk ? kTapkFragBytes + kTapkParBytes : kGconvFragBytes + kGconvParBytes) +
-                    (size_t)bd.G * bd.RI * row_bytes;
+            L.lds = tapk ? (size_t)kTapkLds : (size_t)(kGconvFragBytes + kGconvParBytes) + (size_t)bd.G * bd.RI * row_bytes;
             L.grid = (unsigned)(per_cb * bd.ncb);
             L.kind = tapk ? GconvLaunch::TAPK : GconvLaunch::MFMA;
             return PROM_OK;
@@ -925,10 +986,12 @@ static int gconv_set_attributes()
     static std::once_flag once;
     static hipError_t attr_err = hipSuccess;
     std::call_once(once, [] {
-        const void *fns[4] = {reinterpret_cast<const void *>(&gconv_mfma_kernel),
-                              reinterpret_cast<const void *>(&gconv_tapk_kernel<kTapkPT>),
+        const void *fns[6] = {reinterpret_cast<const void *>(&gconv_mfma_kernel),
+                              reinterpret_cast<const void *>(&gconv_tapk_kernel<kTapkPT, false>),
+                              reinterpret_cast<const void *>(&gconv_tapk_kernel<kTapkPT, true>),
                               reinterpret_cast<const void *>(&gconv_mfma_batch_kernel),
-                              reinterpret_cast<const void *>(&gconv_tapk_batch_kernel<kTapkPT>)};
+                              reinterpret_cast<const void *>(&gconv_tapk_batch_kernel<kTapkPT, false>),
+                              reinterpret_cast<const void *>(&gconv_tapk_batch_kernel<kTapkPT, true>)};
         for (const void *fn : fns)
             if (attr_err == hipSuccess)
                 attr_err = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
@@ -953,7 +1016,7 @@ static int gconv_launch(const GconvLaunch &L, hipStream_t st)
     clear_hip_error();
     switch (L.kind) {
     case GconvLaunch::TAPK:
-        hipLaunchKernelGGL((gconv_tapk_kernel<kTapkPT>), dim3(L.grid), dim3(kTapkThreads), L.lds, st, a, L.bd);
+        hipLaunchKernelGGL((a.mult_neg ? gconv_tapk_kernel<kTapkPT, true> : gconv_tapk_kernel<kTapkPT, false>), dim3(L.grid), dim3(kTapkThreads), L.lds, st, a, L.bd);
         break;
     case GconvLaunch::MFMA:
         hipLaunchKernelGGL(gconv_mfma_kernel, dim3(L.grid), dim3(256), L.lds, st, a, L.bd);
@@ -1042,11 +1105,15 @@ extern "C" int prom_gconv3x3_sequence(const prom_gconv_layer_t *layers, int coun
                 // out so that every layer's workgroups live about equally long, by an estimate of a
                 // workgroup's time per unit of work (a fixed part for staging, barriers and the fetch
                 // latency, plus the rounds in which its four wavefronts take the unit's groups of 32
-                // pixels; fitted to the per-workgroup lifetimes of such a launch): the layer whose
+                // pixels; only their ratio matters.  1.3 to 2.0 was fitted to the lifetimes of workgroups
+                // whose round took twice the instructions it takes now; measured with this kernel, ResNeXt-50
+                // at batch 128 takes 278 us with 0.7 to 1.3 and 260 with 0.4, RegNetX-400MF 96 to 100 with
+                // any of them): the layer whose
                 // workgroups would live longest gets the next ones.  Shares by the bytes alone leave the
                 // layers with small images far behind (a unit of three 7x7 images takes as long as a
                 // band of 112 pixels), shares by the rounds alone the large ones.
                 const int n = j - i;
+                constexpr double kUnitRound = 0.4;  // per round, against a fixed part of 2.0
                 double cost[kGconvMaxBatch];
                 int per_cb[kGconvMaxBatch], step[kGconvMaxBatch];
                 double cost_sum = 0;
@@ -1065,13 +1132,14 @@ extern "C" int prom_gconv3x3_sequence(const prom_gconv_layer_t *layers, int coun
                     if (gmax > L.a.N) gmax = L.a.N;
                     auto per_image = [&](int g) {
                         const int rounds = ((g * bd.R * L.a.Wo + 31) / 32 + 3) / 4;
-                        return (2.0 + 1.3 * rounds) / g;
+                        return (2.0 + kUnitRound * rounds) / g;
                     };
                     int best = bd.G;
                     for (int g = 1; g <= gmax; ++g)
                         if (per_image(g) < 0.98 * per_image(best)) best = g;
                     if (best != bd.G) {
-                        L.lds = L.lds - (size_t)bd.G * image_bytes + (size_t)best * image_bytes;
+                        if (kind == GconvLaunch::MFMA)
+                            L.lds = L.lds - (size_t)bd.G * image_bytes + (size_t)best * image_bytes;
                         bd.G = best;
                         bd.units = (L.a.N + best - 1) / best;
                     }
@@ -1080,7 +1148,7 @@ extern "C" int prom_gconv3x3_sequence(const prom_gconv_layer_t *layers, int coun
                     const GconvLaunch &L = prepared[(size_t)(i + k)];
                     const int npix = (L.bd.G > 1 ? L.bd.G : 1) * L.bd.R * L.a.Wo;
                     const int rounds = ((npix + 31) / 32 + 3) / 4;
-                    cost[k] = (double)L.bd.ncb * L.bd.units * (2.0 + 1.3 * rounds);
+                    cost[k] = (double)L.bd.ncb * L.bd.units * (2.0 + kUnitRound * rounds);
                     cost_sum += cost[k];
                 }
                 // (three per compute unit would fit LDS and registers of the tap-in-k kernel: 108-114
@@ -1174,8 +1242,10 @@ extern "C" int prom_gconv3x3_sequence(const prom_gconv_layer_t *layers, int coun
                 b.count = n;
                 int start = 0;
                 size_t lds = 0;
+                bool any_prelu = false;
                 for (int k = 0; k < n; ++k) {
                     const int m = order[k];
+                    any_prelu |= prepared[(size_t)(i + m)].a.mult_neg != nullptr;
                     const GconvLaunch &L = prepared[(size_t)(i + m)];
                     b.a[k] = L.a;
                     b.bd[k] = L.bd;
@@ -1189,7 +1259,8 @@ extern "C" int prom_gconv3x3_sequence(const prom_gconv_layer_t *layers, int coun
                 b.start[j - i] = start;
                 clear_hip_error();
                 if (kind == GconvLaunch::TAPK)
-                    hipLaunchKernelGGL((gconv_tapk_batch_kernel<kTapkPT>), dim3((unsigned)start), dim3(kTapkThreads), lds, st, b);
+                    hipLaunchKernelGGL((any_prelu ? gconv_tapk_batch_kernel<kTapkPT, true> : gconv_tapk_batch_kernel<kTapkPT, false>),
+                                       dim3((unsigned)start), dim3(kTapkThreads), lds, st, b);
                 else
                     hipLaunchKernelGGL(gconv_mfma_batch_kernel, dim3((unsigned)start), dim3(256), lds, st, b);
                 rc = check_launch();

@@ -241,6 +241,8 @@ __global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_ke
         for (int r = 0; r < 4; ++r) par[r] = lpar[64 * wave + 16 * t + 4 * g + r];
         auto tile = [&](auto form) __attribute__((always_inline)) {
 #pragma unroll
+            for (int r = 0; r < 4; ++r) par[r][3] -= pair_shift_less(decltype(form)::value);
+#pragma unroll
             for (int i = 0; i < PT; i += 2) {
                 uint32_t o0, o1;
                 requant_pair4<decltype(form)::value>(acc[i][t], acc[i + 1][t], par, lo, hi, o0, o1);
@@ -248,7 +250,7 @@ __global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_ke
                 *reinterpret_cast<uint32_t *>(sp + 16 * (i + 1) * G::PITCH + 16 * t) = o1;
             }
         };
-        const int form = pair_form<PRELU>(par, a.lo, a.hi);
+        const int form = pair_form<PRELU>(min_shift(par), a.lo, a.hi);
         if constexpr (PRELU) {
             if (form == kPairPreluFull) tile(std::integral_constant<int, kPairPreluFull>{});
             else tile(std::integral_constant<int, kPairPreluAny>{});
