@@ -7,6 +7,7 @@ from dataclasses import dataclass
 from typing import Optional
 
 import numpy as np
+import torch as _torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libprom.so")
@@ -185,14 +186,18 @@ class Requant:
     mult_neg: "Optional[torch.Tensor]" = None
 
     def _c(self) -> _RequantC:
-        import torch
-        for t in (self.bias, self.mult, self.shift) + (() if self.mult_neg is None else (self.mult_neg,)):
-            assert t.dtype == torch.int32 and t.is_contiguous() and t.is_cuda
-        if self.mult_neg is not None:
-            assert self.mult_neg.numel() == self.mult.numel()
-        return _RequantC(self.bias.data_ptr(), self.mult.data_ptr(), self.shift.data_ptr(),
-                         int(self.act_min), int(self.act_max),
-                         None if self.mult_neg is None else self.mult_neg.data_ptr())
+        # (every layer call comes through here: 0.6 us, with a loop over the tensors and an import 1.0)
+        bias, mult, shift, neg = self.bias, self.mult, self.shift, self.mult_neg
+        i32 = _torch.int32
+        assert bias.dtype == i32 and bias.is_contiguous() and bias.is_cuda
+        assert mult.dtype == i32 and mult.is_contiguous() and mult.is_cuda
+        assert shift.dtype == i32 and shift.is_contiguous() and shift.is_cuda
+        if neg is None:
+            return _RequantC(bias.data_ptr(), mult.data_ptr(), shift.data_ptr(), int(self.act_min), int(self.act_max), None)
+        assert neg.dtype == i32 and neg.is_contiguous() and neg.is_cuda
+        assert neg.numel() == mult.numel()
+        return _RequantC(bias.data_ptr(), mult.data_ptr(), shift.data_ptr(), int(self.act_min), int(self.act_max),
+                         neg.data_ptr())
 
 
 @dataclass
@@ -208,15 +213,16 @@ class PwPlan:
 
 
 def _stream_ptr(stream) -> int:
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle of torch.cuda.current_stream() without the Stream object around it: 0.2 us against 2.9,
+        # a third of what a layer call costs the host
+        _torch.cuda._lazy_init()
+        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
     return int(stream.cuda_stream)
 
 
 def _dev_i8(t, name):
-    import torch
-    if not (t.is_cuda and t.dtype == torch.int8 and t.is_contiguous()):
+    if not (t.is_cuda and t.dtype == _torch.int8 and t.is_contiguous()):
         raise TypeError(f"{name} must be a contiguous int8 device tensor")
     return t
 
