@@ -47,8 +47,7 @@ __device__ unsigned long long g_pl_stamps[256 * 8];
 #define PL_STAMP(i) do { } while (0)
 #endif
 
-// Epilogue forms: 0 = every shift of the lane's channels >= 1 (pr.w holds shift - 1), 1 = any
-// shift, 2 = PReLU.
+// Epilogue forms (requant_pair4) and tile counts as types.
 template <int MODE> struct PlMode { static constexpr int value = MODE; };
 
 // Bias, multiplier(s) and shift of a lane's four channels (16*plane + 4*g + 0..3) as loaded.
@@ -244,9 +243,11 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
             }
             unsigned char *t1p = t1 + pl * slot1 + 4 * g;
             const int pt0 = grp * tpg, pt1 = min((grp + 1) * tpg, nt1);
+            // (PReLU: the biases are what the accumulators start from)
+            const v4i cinit = PRELU ? v4i{par[0][0], par[1][0], par[2][0], par[3][0]} : zero4;
             // NTL pixel tiles at once: independent chains for the matrix cores and the epilogue
             auto tiles = [&](auto mode, auto ntl, int pt) __attribute__((always_inline)) {
-                constexpr int MODE = decltype(mode)::value;
+                constexpr int FORM = decltype(mode)::value;
                 constexpr int NTL = decltype(ntl)::value;
                 v4i d[NTL];
                 int cell[NTL], p[NTL];
@@ -255,39 +256,44 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
                     p[i] = (pt + i) * 16 + j;
                     const int8_t *xp = xs + __umul24(p[i], cinp) + 16 * g;
                     cell[i] = o1[p[i]];
-                    d[i] = zero4;
+                    d[i] = cinit;
 #pragma unroll
                     for (int ks = 0; ks < KSE; ++ks)
                         d[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[ks], *reinterpret_cast<const v4i *>(xp + 64 * ks), d[i], 0, 0, 0);
                 }
 #pragma unroll
-                for (int i = 0; i < NTL; ++i) {
-                    int v[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = requant_mode<MODE>(d[i][r], par[r], lo_e, hi_e);
-                    *reinterpret_cast<uint32_t *>(t1p + cell[i] * 16) = pack4_low_bytes(v[0], v[1], v[2], v[3]);
+                for (int i = 0; i < NTL; i += 2) {  // two pixel tiles at a time; a tile alone is its own partner
+                    uint32_t q0, q1;
+                    requant_pair4<FORM, true>(d[i], d[i + (NTL > 1)], par, lo_e, hi_e, q0, q1);
+                    *reinterpret_cast<uint32_t *>(t1p + cell[i] * 16) = q0;
+                    if constexpr (NTL > 1) *reinterpret_cast<uint32_t *>(t1p + cell[i + 1] * 16) = q1;
                 }
             };
             auto run = [&](auto mode) __attribute__((always_inline)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) par[r][3] -= pair_shift_less(decltype(mode)::value);
                 int pt = pt0;
-                for (; pt + 4 <= pt1; pt += 4) tiles(mode, PlMode<4>{}, pt);
-                if (pt + 2 <= pt1) {
+                // (the rare form takes two tiles at a time: less code)
+                constexpr bool RARE = decltype(mode)::value == kPairAny;
+                if constexpr (!RARE)
+                    for (; pt + 4 <= pt1; pt += 4) tiles(mode, PlMode<4>{}, pt);
+                for (; pt + 2 <= pt1; pt += 2) {
                     tiles(mode, PlMode<2>{}, pt);
-                    pt += 2;
+                    if constexpr (!RARE) {
+                        pt += 2;
+                        break;
+                    }
                 }
                 if (pt < pt1) tiles(mode, PlMode<1>{}, pt);
             };
+            const int form = pair_form<PRELU>(min_shift(par), a.lo_e, a.hi_e);
             if constexpr (PRELU) {
-                run(PlMode<2>{});
+                if (form == kPairPreluFull) run(PlMode<kPairPreluFull>{});
+                else run(PlMode<kPairPreluAny>{});
             } else {
-                const bool shift0 = par[0][3] == 0 || par[1][3] == 0 || par[2][3] == 0 || par[3][3] == 0;
-                if (__builtin_amdgcn_ballot_w64(shift0) == 0) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) par[r][3] -= 1;
-                    run(PlMode<0>{});
-                } else {
-                    run(PlMode<1>{});
-                }
+                if (form == kPairRelu) run(PlMode<kPairRelu>{});
+                else if (form == kPairFull || form == kPairLow) run(PlMode<kPairLow>{});
+                else run(PlMode<kPairAny>{});
             }
         }
     }
@@ -296,7 +302,9 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
 
     // The projection's packed codes go to LDS while phase 2 runs: loads now, stores behind the loop.
     // Wide rows (whole 16-byte pieces): the matrix is one flat run of pieces.
-    constexpr int NW3 = 10;
+    // (NW3 pieces per thread cover 960 x 320 whatever the wavefronts; more pieces would only hold registers
+    // through phase 2, and with 16 wavefronts spill)
+    constexpr int NW3 = (80 + NW - 1) / NW;
     const bool w3wide = (KWp & 3) == 0 && (reinterpret_cast<uintptr_t>(a.wp) & 15) == 0;
     const int kq3 = KWp >> 2;
     const int n3 = w3wide ? cout * kq3 : cout * KWp;  // pieces: 16 bytes or one word
@@ -340,17 +348,18 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
                 const int un = min(u + kPlWaves, units2 - 1);
                 load_par(a.bd, a.md, a.nd, a.sd, G2 == 1 ? un : un / G2, rawd);
             }
+            const v4i cinit = PRELU ? v4i{par[0][0], par[1][0], par[2][0], par[3][0]} : zero4;
             const unsigned char *t1p = t1 + pl * slot1;
             unsigned char *t2p = t2 + pl * slot2 + 4 * g;
             const int pt0 = grp * tpg, pt1 = min((grp + 1) * tpg, nt2);
             auto tiles = [&](auto mode, auto ntl, int pt) __attribute__((always_inline)) {
-                constexpr int MODE = decltype(mode)::value;
+                constexpr int FORM = decltype(mode)::value;
                 constexpr int NTL = decltype(ntl)::value;
                 v4i d[NTL];
 #pragma unroll
                 for (int i = 0; i < NTL; ++i) {
                     const unsigned char *src = t1p + o2[(pt + i) * 16 + j] * 16;
-                    d[i] = zero4;
+                    d[i] = cinit;
 #pragma unroll
                     for (int q = 0; q < 3; ++q)
                         d[i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(adw[q], *reinterpret_cast<const v4i *>(src + toff[q]), d[i], 0, 0, 0);
@@ -358,33 +367,38 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
                 // (the reads of every tile are complete before the first write: with one owner per
                 // plane the output may land in a slot this wavefront has consumed, never in its own)
 #pragma unroll
-                for (int i = 0; i < NTL; ++i) {
-                    int v[4];
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] = requant_mode<MODE>(d[i][r], par[r], lo_d, hi_d);
-                    *reinterpret_cast<uint32_t *>(t2p + ((pt + i) * 16 + j) * 16) = pack4_low_bytes(v[0], v[1], v[2], v[3]);
+                for (int i = 0; i < NTL; i += 2) {  // two pixel tiles at a time; a tile alone is its own partner
+                    uint32_t q0, q1;
+                    requant_pair4<FORM, true>(d[i], d[i + (NTL > 1)], par, lo_d, hi_d, q0, q1);
+                    *reinterpret_cast<uint32_t *>(t2p + ((pt + i) * 16 + j) * 16) = q0;
+                    if constexpr (NTL > 1) *reinterpret_cast<uint32_t *>(t2p + ((pt + i + 1) * 16 + j) * 16) = q1;
                 }
             };
             auto run = [&](auto mode) __attribute__((always_inline)) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) par[r][3] -= pair_shift_less(decltype(mode)::value);
                 int pt = pt0;
-                for (; pt + 4 <= pt1; pt += 4) tiles(mode, PlMode<4>{}, pt);
-                if (pt + 2 <= pt1) {
+                // (the rare form takes two tiles at a time: less code)
+                constexpr bool RARE = decltype(mode)::value == kPairAny;
+                if constexpr (!RARE)
+                    for (; pt + 4 <= pt1; pt += 4) tiles(mode, PlMode<4>{}, pt);
+                for (; pt + 2 <= pt1; pt += 2) {
                     tiles(mode, PlMode<2>{}, pt);
-                    pt += 2;
+                    if constexpr (!RARE) {
+                        pt += 2;
+                        break;
+                    }
                 }
                 if (pt < pt1) tiles(mode, PlMode<1>{}, pt);
             };
+            const int form = pair_form<PRELU>(min_shift(par), a.lo_d, a.hi_d);
             if constexpr (PRELU) {
-                run(PlMode<2>{});
+                if (form == kPairPreluFull) run(PlMode<kPairPreluFull>{});
+                else run(PlMode<kPairPreluAny>{});
             } else {
-                const bool shift0 = par[0][3] == 0 || par[1][3] == 0 || par[2][3] == 0 || par[3][3] == 0;
-                if (__builtin_amdgcn_ballot_w64(shift0) == 0) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) par[r][3] -= 1;
-                    run(PlMode<0>{});
-                } else {
-                    run(PlMode<1>{});
-                }
+                if (form == kPairRelu) run(PlMode<kPairRelu>{});
+                else if (form == kPairFull || form == kPairLow) run(PlMode<kPairLow>{});
+                else run(PlMode<kPairAny>{});
             }
         }
     }
@@ -429,7 +443,6 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
     // 16-byte LDS read.
     {
         const int lo_p = in_vgpr(a.lo_p), hi_p = in_vgpr(a.hi_p);
-        const int m128 = in_vgpr(-128), p127 = in_vgpr(127);
         const __amdgpu_buffer_rsrc_t ry =
             __builtin_amdgcn_make_buffer_rsrc(a.y, 0, a.N * a.Ho * Wo * cout, kBufFlags);
         const int obase = (img * a.Ho + ro0) * Wo;  // first output pixel of the band
@@ -484,26 +497,33 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
             v4i pr[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) pr[r] = pp[c + r];
+            // two pixel tiles at a time (a tile alone is its own partner; tiles beyond the band are not stored)
+            auto finish = [&](auto form) __attribute__((always_inline)) {
 #pragma unroll
-            for (int i = 0; i < TPG; ++i) {
-                if (pt0 + i < nt2) {
-                    const int p = (pt0 + i) * 16 + j;
-                    const bool pvalid = cok && p < np2;
-                    int v[4];
+                for (int r = 0; r < 4; ++r) pr[r][3] -= pair_shift_less(decltype(form)::value);
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        v[r] = prelu_p ? requant_prelu_i64(acc[i][r], pr[r], lo_p, hi_p)
-                                       : requant_i64<true>(acc[i][r], pr[r], lo_p, hi_p);
-                    if (a.add_res) {
-                        // stride 1 and cin == cout: the block input at the same pixel, still in LDS
-                        const uint32_t res = *reinterpret_cast<const uint32_t *>(
-                            xs + ((1 - rv0) * W + min(p, np2 - 1)) * cinp + (cok ? c : 0));
+                for (int i = 0; i < TPG; i += 2) {
+                    uint32_t q[2];
+                    requant_pair4<decltype(form)::value>(acc[i], acc[i + (TPG > 1)], pr, lo_p, hi_p, q[0], q[1]);
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = med3_i32(v[r] + sbyte(res, r), m128, p127);
+                    for (int k = 0; k < (TPG > 1 ? 2 : 1); ++k) {
+                        const int p = (pt0 + i + k) * 16 + j;
+                        if (a.add_res) {
+                            // stride 1 and cin == cout: the block input at the same pixel, still in LDS
+                            const uint32_t res = *reinterpret_cast<const uint32_t *>(
+                                xs + ((1 - rv0) * W + min(p, np2 - 1)) * cinp + (cok ? c : 0));
+                            q[k] = add_sat_i8x4(q[k], res);
+                        }
+                        __builtin_amdgcn_raw_buffer_store_b32((int)q[k], ry, cok && p < np2 ? (obase + p) * cout + c : kOobOffset, 0, 0);
                     }
-                    __builtin_amdgcn_raw_buffer_store_b32((int)pack4_low_bytes(v[0], v[1], v[2], v[3]), ry,
-                                                          pvalid ? (obase + p) * cout + c : kOobOffset, 0, 0);
                 }
+            };
+            if (prelu_p) {
+                finish(PlMode<kPairPreluAny>{});
+            } else {
+                const int form = pair_form<false>(min_shift(pr), a.lo_p, a.hi_p);
+                if (form == kPairFull) finish(PlMode<kPairFull>{});
+                else finish(PlMode<kPairAny>{});
             }
         };
         for (int u = wave; u < units3; u += kPlWaves) {

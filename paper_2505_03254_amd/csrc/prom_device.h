@@ -134,13 +134,14 @@ __device__ __forceinline__ int sbyte(uint32_t v, int i)
 //   kPairRelu   window [0, 127], every shift >= 2: the pair instruction saturates floor(2v) to [0, 255];
 //               clamp(floor(v), 0, 127) is half of that, rounded down -- one shift and one mask per dword
 //   kPairFull   window [-128, 127], every shift >= 1
+//   kPairLow    either of the two windows, every shift >= 1 (one maximum per output more)
 //   kPairAny    any window, any shift (requant_i64<true>)
 //   kPairPreluFull  PReLU layer (par = (bias, mult, mult_neg, shift)), window [-128, 127], every shift >= 2
 //   kPairPreluAny   PReLU layer, any window, any shift
-constexpr int kPairRelu = 0, kPairFull = 1, kPairAny = 2, kPairPreluFull = 3, kPairPreluAny = 4;
+constexpr int kPairRelu = 0, kPairFull = 1, kPairAny = 2, kPairPreluFull = 3, kPairPreluAny = 4, kPairLow = 5;
 
 // What a form's shifts are reduced by in the parameters handed to requant_pair4.
-__host__ __device__ constexpr int pair_shift_less(int form) { return form == kPairRelu || form == kPairPreluFull ? 2 : form == kPairFull ? 1 : 0; }
+__host__ __device__ constexpr int pair_shift_less(int form) { return form == kPairRelu || form == kPairPreluFull ? 2 : form == kPairFull || form == kPairLow ? 1 : 0; }
 
 // a0, a1: the accumulators of two pixels, four channels each; par: the channels' parameters as
 // requant_params made them, the shifts reduced by pair_shift_less(FORM); out0, out1: the packed outputs.
@@ -173,9 +174,11 @@ __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, cons
             if constexpr (FORM == kPairPreluFull) {
                 const int b = BIASED ? 0 : par[r][0];
                 const int s0 = a0[r] + b, s1 = a1[r] + b;
-                // (a bit select by the sign, v_bfi_b32: the compiler turns a ternary between two elements of
-                // one vector into a chain of compares and selects)
-                const int n0 = s0 >> 31, n1 = s1 >> 31;
+                // (a bit select by the sign: the compiler turns a ternary between two elements of one vector
+                // into a chain of compares and selects, and this too if it sees where the mask comes from)
+                int n0 = s0 >> 31, n1 = s1 >> 31;
+                asm("" : "+v"(n0));
+                asm("" : "+v"(n1));
                 const int m0 = (n0 & par[r][2]) | (~n0 & par[r][1]), m1 = (n1 & par[r][2]) | (~n1 & par[r][1]);
                 // floor((s*m + 2^(30+shift)) / 2^32): the rounding term is a whole multiple of 2^32
                 t0 = __mulhi(s0, m0) + (1 << par[r][3]);
@@ -184,6 +187,11 @@ __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, cons
                 const long long C = (long long)(((unsigned long long)(uint32_t)par[r][1] << 32) | (uint32_t)par[r][0]);
                 t0 = (int)(((long long)a0[r] * par[r][2] + C) >> 32);
                 t1 = (int)(((long long)a1[r] * par[r][2] + C) >> 32);
+            }
+            if constexpr (FORM == kPairLow) {  // the high halves at least 0, or at least INT_MIN
+                const int low = (int)((unsigned)lo << 24);
+                t0 = max(t0, low);
+                t1 = max(t1, low);
             }
             // (the instruction, not the builtin: the builtin's 16-bit result costs a mask)
             const int sh = FORM == kPairPreluFull ? par[r][3] + 1 : par[r][3];
@@ -209,10 +217,10 @@ template <bool PRELU>
 __device__ __forceinline__ int pair_form(int s, int lo, int hi)
 {
     const bool full = lo == -128 && hi == 127, relu = lo == 0 && hi == 127;
-    const int need = PRELU || relu ? 2 : 1;
-    const bool ok = (full || (!PRELU && relu)) && __builtin_amdgcn_ballot_w64(s < need) == 0;
-    if (PRELU) return ok ? kPairPreluFull : kPairPreluAny;
-    return ok ? (relu ? kPairRelu : kPairFull) : kPairAny;
+    if constexpr (PRELU) return full && __builtin_amdgcn_ballot_w64(s < 2) == 0 ? kPairPreluFull : kPairPreluAny;
+    const bool ge1 = __builtin_amdgcn_ballot_w64(s < 1) == 0, ge2 = __builtin_amdgcn_ballot_w64(s < 2) == 0;
+    if (full) return ge1 ? kPairFull : kPairAny;
+    return relu && ge1 ? (ge2 ? kPairRelu : kPairLow) : kPairAny;
 }
 
 __device__ __forceinline__ int min_shift(const v4i (&par)[4])

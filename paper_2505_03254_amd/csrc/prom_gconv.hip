@@ -441,7 +441,7 @@ __device__ __forceinline__ void gconv_mfma_body(const GconvArgs &a, const GconvB
     } else {
         const int form = pair_form<false>(smin, a.lo, a.hi);
         if (form == kPairRelu) run(std::integral_constant<int, kPairRelu>{});
-        else if (form == kPairFull) run(std::integral_constant<int, kPairFull>{});
+        else if (form == kPairFull || form == kPairLow) run(std::integral_constant<int, kPairLow>{});
         else run(std::integral_constant<int, kPairAny>{});
     }
 }
@@ -749,7 +749,7 @@ __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvB
         else run(std::integral_constant<int, kPairPreluAny>{});
     } else {
         if (form == kPairRelu) run(std::integral_constant<int, kPairRelu>{});
-        else if (form == kPairFull) run(std::integral_constant<int, kPairFull>{});
+        else if (form == kPairFull || form == kPairLow) run(std::integral_constant<int, kPairLow>{});
         else run(std::integral_constant<int, kPairAny>{});
     }
 #ifdef PROM_TIMELINE

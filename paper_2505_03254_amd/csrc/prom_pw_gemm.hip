@@ -257,6 +257,7 @@ __global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_ke
         } else {
             if (form == kPairRelu) tile(std::integral_constant<int, kPairRelu>{});
             else if (form == kPairFull) tile(std::integral_constant<int, kPairFull>{});
+            else if (form == kPairLow) tile(std::integral_constant<int, kPairLow>{});
             else tile(std::integral_constant<int, kPairAny>{});
         }
     }
