@@ -98,10 +98,10 @@ int prom_requant_check(const prom_requant_t *rq, int channels, int cin, int *bad
  * channels together; it needs tiles_per_wave in 1..6, pixel_tiles 0 or 1 and
  * cout % (16*tiles_per_wave*row_waves) == 0 (and, like the fast path in general, cin % 8 == 0).
  * k_outer = 1 asks for the kernel of wide layers (the k loop outermost over a workgroup tile of 32 to
- * 128 pixels x 256 output channels, weights decoded per k step): it needs cin % 64 == 0,
+ * 128 pixels x 128 or 256 output channels, weights decoded per k step): it needs cin % 64 == 0,
  * cout % 16 == 0, 16-byte aligned x, y, residual, 8-byte aligned packed weights and every other
  * field zero; k_outer = -1 keeps it off; 0 leaves the choice to the library.  The library plans it
- * from 1024 input and 256 output channels on where it is the faster one; a smaller layer that is launched
+ * from 1024 input and 256 output channels on where it is the faster one; a smaller layer (cin % 16 == 0) launched
  * alone may run on it as well, its plan (prom_pw_plan_query) and its place in a shared launch stay those of
  * the streaming kernel. */
 typedef struct {

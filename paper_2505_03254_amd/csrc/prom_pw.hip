@@ -1,6 +1,7 @@
 // Host side of the ternary pointwise convolution (argument checks, launch planning, the
 // C entry points) and the generic any-shape kernel.  The streaming kernel lives in
 // prom_pw_stream.h and is instantiated per NT in prom_pw_inst.hip.
+#include <cmath>
 #include "prom_pw_batch.h"
 #include "prom_pw_gemm.h"
 #include "prom_launch.h"
@@ -274,53 +275,73 @@ struct PwLaunch {
     bool tile;
     PwArgs ta;
     KernelFn tfn;
-    int tgrid;
+    int tgrid, tthreads;
     size_t tlds;
 };
 
-// The tile kernel's pixel tiles per wavefront for a layer (2, 4 or 8), or 0 where the streaming kernel is
-// the faster one.  Times in us, batch 1 to 128 of 20 layer shapes of the three networks, tensors not in the
-// last-level cache.
+// The tile kernel's shape for a layer: 16-pixel tiles per wavefront (2, 4 or 8) and wavefronts (2 or 4, 64
+// output channels each); false where the streaming kernel is the faster one.  Times in us, streaming against
+// tile kernel, one launch per layer, batch 1 to 128 of 40 layer shapes of the three networks.
 //
-// Choice of the tile.  A tile takes base + step * KS however few there are; with r tiles per compute
-// unit the layer takes 2.5 + r * (c0 + c1 * KS).  The constants are fits: 14x14 1024 -> 512 takes
-// 19.9 / 22.4 / 25.7 at batch 128 with 8 / 4 / 2 pixel tiles (196 to 1568 workgroup tiles), 12.4 / 9.6 / 10.8
-// at batch 32, 11.2 / 8.3 / 7.5 at batch 4.
+// Choice of the shape.  A tile takes base + step * KS however few there are; with r tiles per compute
+// unit the layer takes 2.5 + r * (c0 + c1 * KS), and at least half the steps more than one tile once some units
+// have two (512 -> 512, 2 wavefronts: 5.4 at 196 tiles, 6.5 at 296, 7.3 at 784).  The constants are fits: 14x14 1024 -> 512 takes 20.9 /
+// 23.6 at batch 128 with 4 wavefronts and 8 / 4 pixel tiles, 20.4 / 23.3 with 2; 10.6 with (4, 4), 10.3 with (2, 2)
+// at batch 32.  Two wavefronts suit narrow layers and few pixels (56x56 256 -> 128, batch 32: 17.3 with 4
+// wavefronts, 11.9 with 2, streaming 12.9).
 //
 // Where the streaming kernel stays:
-//   - channels that do not fill the 256 of a tile (waste above 4/3): 28x28 576 -> 192 7.5 against 8.0,
-//     56x56 256 -> 128 23 against 28, 960 -> 320 7.9 against 9.2;
-//   - deep layers with few pixels, which it spreads over more workgroups: 1024 -> 512 at 784 pixels 5.8 against
-//     7.5, at 3136 pixels 8.6 against 8.1; 1024 -> 1024 6.0 / 7.6 and 12.9 / 9.6; 2048 -> 1024 at 784 pixels
-//     11.9 against 12.7, at 1568 19.1 against 12.9: level at M*N*K of about 1.1e9 (1024 channels), 1.5e9 to
-//     2e9 (2048); up to 512 input channels the tile kernel is ahead down to one image (512 -> 1024 at 14x14
-//     5.8 against 5.5, 64 -> 384 4.6 against 3.4);
-//   - shallow layers with many pixels, which are nothing but streams: 56x56 64 -> 256 14.1 against 13.0 at
-//     batch 32 (784 tiles of 128 pixels), 22.1 against 23.9 at batch 64; 28x28 128 -> 384, a quarter of its
-//     tiles' work wasted, 9.3 against 8.2 at batch 32 (392 tiles), 12.3 against 13.8 at batch 64.
-static int gemm_plan(long long M, int cin, int cout)
+//   - fewer than 96 output channels: 28x28 192 -> 64 3.6 / 3.8 to 8.4 / 11.0, 64 -> 64 3.4 / 3.6 to 7.6 / 8.8;
+//   - up to 5 k steps and many pixels, where a layer is nothing but a stream, unless the tiles waste nothing.
+//     The line is drawn in pixels times what the tiles waste of their k steps and channels: one k step 64 -> 256
+//     14.1 / 13.0 at 100 K pixels, 22.1 / 23.9 at 200 K; 32 -> 192 7.9 / 5.4 at 25 K (67 K with the waste), 13.1 / 13.1
+//     at 100 K (267 K); 64 -> 160 6.1 / 5.3 at 25 K (40 K), 10.7 / 12.9 at 100 K (160 K); more k steps 96 -> 576
+//     12.8 / 9.5 at 25 K (37 K), 160 -> 160 8.9 / 7.1 at 25 K (48 K); 128 -> 384 5.4 / 4.6 at 6 K, 9.0 / 9.1 at 19 K,
+//     12.9 / 13.4 at 50 K; 208 -> 304 9.8 / 9.3 at 19 K (29 K), 15.1 / 16.0 at 50 K (78 K); 256 -> 128 7.4 / 6.9 at
+//     25 K, 12.2 / 12.0 at 75 K, 20.7 / 25.3 at 200 K; without waste 128 -> 256 with a residual 64.3 / 57.3 at 400 K;
+//   - 6 to 8 k steps and fewer than 256 channels: 384 -> 96 5.0 / 4.8 to 7.2 / 7.1, 384 -> 64 6.8 / 7.5;
+//   - 6 to 8 k steps and a last round of tiles that leaves much of the chip idle, two to four tiles of 128 x 256 per
+//     compute unit: 14x14 512 -> 1024 with 2.3 / 2.7 / 3.06 / 3.8 / 4.6 tiles 18.5 / 19.6, 20.3 / 19.6, 22.4 / 22.6,
+//     24.9 / 23.2, 29.0 / 27.5; 384 -> 768 with 2.02 / 2.3 / 2.9 tiles 15.4 / 16.9, 15.7 / 17.1, 17.4 / 17.4;
+//     2 to 5 k steps the same with 2 to 2.5 tiles: 128 -> 256 12.7 / 13.7, 192 -> 768 13.6 / 14.6 (2.3 tiles each);
+//   - deeper layers with few pixels or channels, which it spreads over more workgroups: 1024 -> 512 at 784
+//     pixels 5.8 / 7.5, at 3136 8.6 / 8.1; 1024 -> 1024 6.0 / 7.6 and 12.9 / 9.6; 2048 -> 1024 at 784 pixels
+//     11.9 / 12.7, at 1568 19.1 / 12.9: level at M*N*K of about 1.1e9 (1024 channels), 1.5e9 to 2e9 (2048);
+//     960 -> 320 8.0 / 9.7, 576 -> 160 9.0 / 9.9.
+static bool gemm_plan(long long M, int cin, int cout, int *pt, int *nw)
 {
     const int KS = (cin + 63) / 64;
-    const long long ct = (cout + 255) / 256;
-    if (3 * 256 * ct > 4 * (long long)cout) return 0;
-    if (KS > 8 && (double)M * cout * cin < 1.1e9 * (KS / 16.0 > 1.0 ? 0.7 * KS / 16.0 + 0.3 : 1.0)) return 0;
-    const long long t8 = (M + 127) / 128 * ct;
-    if (KS == 1 && t8 > 800) return 0;
-    if (KS == 2 && 256 * ct != cout && t8 > 400) return 0;
-    static const struct { int pt; double base, step, c0, c1; } kFit[] = {
-        {8, 4.3, 0.43, 3.7, 0.46}, {4, 3.4, 0.295, 1.8, 0.28}, {2, 3.1, 0.27, 1.2, 0.16}};
-    int best = 0;
+    const double waste = 128.0 * ((cout + 127) / 128) / cout;
+    const double px = (double)M * waste * (64.0 * KS / cin);
+    const double r8 = (double)((M + 127) / 128 * ((cout + 255) / 256)) / kNumCU;
+    if (KS <= 5) {
+        if (KS > 1 && r8 > 2 && r8 < 2.5) return false;
+        const bool exact = cout % 256 == 0 && cin % 64 == 0;
+        if (cout < (KS <= 3 ? 96 : 128) || (KS == 1 ? px > 130e3 : !exact && px > 50e3)) return false;
+    } else {
+        if (cout < 256 || waste > 1.34) return false;
+        if (KS <= 8) {
+            if (r8 > 2 && r8 <= 4 && r8 < 0.88 * std::ceil(r8)) return false;
+        } else {
+            if (3 * 256 * ((cout + 255) / 256) > 4 * cout) return false;
+            if ((double)M * cout * cin < 1.1e9 * (KS > 16 ? 0.7 * KS / 16.0 + 0.3 : 1.0)) return false;
+        }
+    }
+    static const struct { int pt, nw; double base, step, c0, c1; } kFit[] = {
+        {8, 4, 4.3, 0.43, 3.7, 0.46}, {4, 4, 3.4, 0.295, 1.8, 0.28}, {2, 4, 3.1, 0.27, 1.2, 0.16},
+        {8, 2, 4.5, 0.45, 1.95, 0.24}, {4, 2, 3.6, 0.31, 0.94, 0.145}, {2, 2, 3.2, 0.24, 0.56, 0.075}};
     double best_us = 0;
     for (const auto &f : kFit) {
-        const double r = (double)((M + 16 * f.pt - 1) / (16 * f.pt) * ct) / kNumCU;
-        const double alone = f.base + f.step * KS, many = 2.5 + r * (f.c0 + f.c1 * KS);
+        const double r = (double)((M + 16 * f.pt - 1) / (16 * f.pt) * ((cout + 64 * f.nw - 1) / (64 * f.nw))) / kNumCU;
+        const double alone = f.base + (r > 1 ? 1.5 : 1) * f.step * KS, many = 2.5 + r * (f.c0 + f.c1 * KS);
         const double us = alone > many ? alone : many;
-        if (best == 0 || us < best_us) {
-            best = f.pt;
+        if (best_us == 0 || us < best_us) {
+            *pt = f.pt;
+            *nw = f.nw;
             best_us = us;
         }
     }
-    return best;
+    return true;
 }
 
 // Validate the arguments and fill the launch description.  mode: 0 = requantised int8
@@ -499,21 +520,22 @@ static int pw_prepare(const int8_t *x, int n, int h, int w, int cin, const void 
     if (k_outer != 0 && k_outer != 1 && k_outer != -1) return PROM_EINVAL;
     const bool aligned16 = shape_only || ((((uintptr_t)x | (uintptr_t)y | (uintptr_t)residual) & 15) == 0 &&
                                           ((uintptr_t)w_packed & 7) == 0);
-    const bool gemm_ok = fast && cin % 64 == 0 && cout % 16 == 0 && aligned16;
+    const bool gemm_ok = fast && cin % 16 == 0 && cout % 16 == 0 && aligned16;
     if (k_outer == 1) {
-        if (!gemm_ok || plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves || plan->workgroups)
+        if (!gemm_ok || cin % 64 != 0 || plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves || plan->workgroups)
             return PROM_EINVAL;
     }
     const bool explicit_stream = plan && (plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves || plan->workgroups);
     if (gemm_ok && k_outer != -1 && !explicit_stream) {
-        int pt = gemm_plan(M, cin, cout);
+        int pt = M >= 128 * 256 ? 8 : 4, nw = 4;
+        const bool pays = gemm_plan(M, cin, cout, &pt, &nw);
         const long long pieces = ((M + 255) / 256) * ((cout + 127) / 128);
-        L.gemm = k_outer == 1 || (cin >= 1024 && cout >= 256 && pieces * (cin / 64) >= 2800);
-        L.tile = L.gemm || pt != 0;
+        L.gemm = k_outer == 1 || (cin % 64 == 0 && cin >= 1024 && cout >= 256 && pieces * (cin / 64) >= 2800);
+        L.tile = L.gemm || pays;
         if (L.tile) {
-            if (pt == 0) pt = M >= 128 * 256 ? 8 : 4;
-            const GemmTile t = pw_gemm_tile(pt, a.mult_neg != nullptr);
+            const GemmTile t = pw_gemm_tile(pt, nw, a.mult_neg != nullptr);
             L.tfn = t.fn;
+            L.tthreads = t.threads;
             L.tlds = t.lds;
             L.ta = a;
             L.ta.n_chunks = (cout + t.tn - 1) / t.tn;
@@ -539,7 +561,7 @@ static int pw_launch(const PwLaunch &L, hipStream_t st)
 {
     const KernelFn fn = L.tile ? L.tfn : L.fn;
     const size_t lds = L.tile ? L.tlds : L.lds;
-    const int grid = L.tile ? L.tgrid : L.grid, threads = L.tile ? 256 : L.threads;
+    const int grid = L.tile ? L.tgrid : L.grid, threads = L.tile ? L.tthreads : L.threads;
     if (lds > 64 * 1024 && resident_workgroups(fn, lds, threads) < 1) return PROM_EHIP;
     clear_hip_error();
     PwArgs args = L.tile ? L.ta : L.a;

@@ -5,14 +5,14 @@
 
 namespace prom {
 
-// A workgroup's tile: tm pixels x tn output channels; wgs: workgroups resident per compute unit.
+// A workgroup's tile: tm pixels x tn output channels.
 struct GemmTile {
-    int tm, tn, wgs;
+    int tm, tn, threads;
     size_t lds;
     PwKernelFn fn;
 };
 
-// pt: 16-pixel tiles per wavefront (2, 4 or 8).
-GemmTile pw_gemm_tile(int pt, bool prelu);
+// pt: 16-pixel tiles per wavefront (2, 4 or 8); nw: wavefronts, 64 output channels each (2 or 4).
+GemmTile pw_gemm_tile(int pt, int nw, bool prelu);
 
 }  // namespace prom

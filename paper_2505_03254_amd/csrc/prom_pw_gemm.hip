@@ -1,6 +1,6 @@
-// Ternary pointwise convolution for wide layers (hundreds to thousands of input AND output
-// channels: the 1x1 layers of ResNeXt and of the deeper stages of RegNet, paper Section 5): the k loop
-// is outermost over a workgroup tile of pixels x output channels.
+// Ternary pointwise convolution with the k loop outermost over a workgroup tile of pixels x output channels:
+// wide layers (hundreds to thousands of input AND output channels: the 1x1 layers of ResNeXt and RegNet,
+// paper Section 5) and, launched alone, the expansion layers of MobileNetV2.
 //
 // The streaming kernel (prom_pw_stream.h) keeps the decoded weights of a chunk of output channels
 // for ALL input channels in LDS and streams the pixels past them once per chunk: every MFMA reads a
@@ -8,7 +8,7 @@
 // activations pass the texture addresser once per chunk, and a workgroup decodes up to 64 KB of
 // fragments before its first MFMA.  Here
 //   - a wavefront owns PT x 4 accumulator tiles: 16*PT pixels x 64 output channels of the workgroup's
-//     16*PT x 256.  It decodes the packed codes of its own 64 channels in registers, 48 instructions per
+//     16*PT x 128 or 256.  It decodes the packed codes of its own 64 channels in registers, 48 instructions per
 //     k step against 4*PT MFMAs of 16 cycles, so no decoded weight passes through LDS;
 //   - everything comes from global memory in lane order: four neighbouring lanes read one 64-byte run.  The
 //     texture addresser takes 24 to 30 cycles for such an instruction of 1 KB, and 65 for one in operand
@@ -17,7 +17,7 @@
 //     57 us (2) for 512 -> 1024 at 12544 and 25088 pixels, where this one takes 14.7 and 25.9;
 //   - the packed codes of four k steps (64 bytes per channel) go through 4 KB of LDS of the wavefront's own
 //     into operand order; no barrier, LDS operations of a wavefront keep their order;
-//   - the activations of a k step (64 bytes per pixel) are fetched by all 256 threads D k steps ahead in
+//   - the activations of a k step (64 bytes per pixel) are fetched by all threads D k steps ahead in
 //     registers and put into one of two LDS slabs, from which every wavefront reads its B operands: 1 KB
 //     per 4 MFMAs, half of what LDS delivers.  The 16-byte pieces of a pixel are exchanged by the pixel's
 //     index, so that neither the writes nor the operand reads meet bank conflicts.  One barrier per k step,
@@ -50,31 +50,30 @@ __device__ __forceinline__ void lds_barrier()
 constexpr int kGemmCodeStep = 64 * 16 + 32;
 constexpr int kGemmCodes = 4 * kGemmCodeStep;
 
-template <int PT> struct GemmGeom {
+template <int PT, int NW> struct GemmGeom {
+    static constexpr int NT = 64 * NW;            // threads
     static constexpr int TM = 16 * PT;            // pixels of a workgroup's tile
-    static constexpr int TN = 256;                // output channels of it, 64 per wavefront
-    static constexpr int NQ = TM >= 64 ? TM / 64 : 1;  // 16-byte pieces of activations per thread and k step
-    static constexpr int SLAB = NQ * 4096;        // bytes of one k step's activations (32-pixel tiles: half used)
+    static constexpr int TN = 64 * NW;            // output channels of it, 64 per wavefront
+    static constexpr int NQ = (TM * 4 + NT - 1) / NT;  // 16-byte pieces of activations per thread and k step
+    static constexpr int SLAB = NQ * NT * 16;     // bytes of one k step's activations, rounded up to whole pieces per thread
     static constexpr int PITCH = TN + 16;         // bytes between pixels of the assembled tile
     static constexpr int BODY = 2 * SLAB > TM * PITCH ? 2 * SLAB : TM * PITCH;
-    static constexpr size_t LDS = (size_t)TN * 16 + 4 * kGemmCodes + BODY;
-    static constexpr int D = PT == 8 ? 2 : 4;     // k steps of activations requested ahead
-    static constexpr int NP = TM * TN / 16 / 256; // 16-byte pieces of the output tile per thread
+    static constexpr size_t LDS = (size_t)TN * 16 + NW * kGemmCodes + BODY;
+    // k steps of activations requested ahead, as many as the registers hold
+    static constexpr int D = PT == 8 ? (NW == 2 ? 1 : 2) : PT == 4 && NW < 4 ? 2 : 4;
+    static constexpr int NP = (TM * TN / 16 + NT - 1) / NT;  // 16-byte pieces of the output tile per thread
 };
 
 // a.n_chunks = column tiles of TN channels, a.wg_per_chunk = row tiles of TM pixels; requires
-// K % 64 == 0, Nc % 16 == 0 and 16-byte aligned x, y, residual.
-
-
-
-template <int PT, bool PRELU>
-__global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_kernel(const PwArgs a)
+// K % 16 == 0, Nc % 16 == 0 and 16-byte aligned x, y, residual.
+template <int PT, int NW, bool PRELU>
+__global__ __launch_bounds__(64 * NW, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_kernel(const PwArgs a)
 {
-    using G = GemmGeom<PT>;
+    using G = GemmGeom<PT, NW>;
     constexpr int D = G::D, NQ = G::NQ;
     extern __shared__ __align__(16) unsigned char lds[];
     v4i *lpar = reinterpret_cast<v4i *>(lds);  // [TN]
-    unsigned char *body = lds + G::TN * 16 + 4 * kGemmCodes;  // two slabs of activations, then the assembled tile
+    unsigned char *body = lds + G::TN * 16 + NW * kGemmCodes;  // two slabs of activations, then the assembled tile
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -97,14 +96,17 @@ __global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_ke
     const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int8_t *>(a.residual ? a.residual : a.y), 0, a.M * Nc, kBufFlags);
 
-    // Activations: piece idx = tid + 256*q of a slab is 16-byte slot idx & 3 of pixel idx >> 2 and holds
+    // Activations: piece idx = tid + NT*q of a slab is 16-byte slot idx & 3 of pixel idx >> 2 and holds
     // piece slot ^ ((pixel >> 1) & 3) of the pixel's 64 bytes.
+    // (the piece is the same in all of a thread's pixels; xlast: the k steps in which it exists)
+    const int xpiece = (tid & 3) ^ ((tid >> 3) & 3);
+    const int xlast = (K - 16 * xpiece + 63) >> 6;
     unsigned xoff[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-        const int idx = tid + 256 * q;
-        const int px = idx >> 2, piece = (idx & 3) ^ ((px >> 1) & 3);
-        const long long o = (long long)(m0 + px) * K + 16 * piece;
+        const int idx = tid + G::NT * q;
+        const int px = idx >> 2;
+        const long long o = (long long)(m0 + px) * K + 16 * xpiece;
         xoff[q] = px < G::TM && o < (long long)kOobOffset ? (unsigned)o : (unsigned)kOobOffset;
     }
     // Codes of a group of four k steps: 64 bytes per channel.  Instruction r of a load: channel
@@ -117,12 +119,13 @@ __global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_ke
     unsigned char *wput = codes + wpiece * kGemmCodeStep + (lane >> 2) * 16;
     const unsigned char *wget = codes + j * 16 + g * 4;
 
-    // (requests past the last k step go out of range and move nothing)
+    // (requests past the last k step go out of range and move nothing; pieces past the end of a row are zeros,
+    // so that the codes beside them, the next row's, count for nothing)
     auto load_x = [&](int ks, v4i(&v)[NQ]) __attribute__((always_inline)) {
-        const unsigned ko = ks < KS ? 64u * (unsigned)ks : (unsigned)kOobOffset;
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
-            v[q] = __builtin_amdgcn_raw_buffer_load_b128(rx, (int)min(xoff[q] + ko, (unsigned)kOobOffset), 0, 0);
+            v[q] = __builtin_amdgcn_raw_buffer_load_b128(
+                rx, ks < xlast ? (int)min(xoff[q] + 64u * (unsigned)ks, (unsigned)kOobOffset) : kOobOffset, 0, 0);
     };
     auto load_w = [&](int ks, v4i(&v)[4]) __attribute__((always_inline)) {  // ks: first step of the group
         const unsigned ko = ks + wpiece < KS ? 16u * (unsigned)ks : (unsigned)kOobOffset;
@@ -140,7 +143,7 @@ __global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_ke
     };
     auto put_x = [&](int slab, const v4i(&v)[NQ]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) *reinterpret_cast<v4i *>(body + slab * G::SLAB + (tid + 256 * q) * 16) = v[q];
+        for (int q = 0; q < NQ; ++q) *reinterpret_cast<v4i *>(body + slab * G::SLAB + (tid + G::NT * q) * 16) = v[q];
     };
 
     // Ring: slot (s % D) holds step s's activations until they are put into LDS one step early.
@@ -224,7 +227,7 @@ __global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_ke
     v4i res[G::NP];
 #pragma unroll
     for (int q = 0; q < G::NP; ++q) {
-        const int idx = tid + 256 * q;
+        const int idx = tid + G::NT * q;
         const int px = idx / PPR, c = n0 + 16 * (idx % PPR);
         const long long o = (long long)(m0 + px) * Nc + c;
         yoff[q] = c < Nc && o < (long long)kOobOffset ? (int)o : kOobOffset;
@@ -264,7 +267,7 @@ __global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_ke
     lds_barrier();
 #pragma unroll
     for (int q = 0; q < G::NP; ++q) {
-        const int idx = tid + 256 * q;
+        const int idx = tid + G::NT * q;
         v4i v = *reinterpret_cast<const v4i *>(body + (idx / PPR) * G::PITCH + 16 * (idx % PPR));
         if (a.residual) {
 #pragma unroll
@@ -274,15 +277,15 @@ __global__ __launch_bounds__(256, PT == 8 ? 2 : PT == 4 ? 3 : 4) void pw_gemm_ke
     }
 }
 
-template <int PT> static GemmTile gemm_tile(bool prelu)
+template <int PT, int NW> static GemmTile gemm_tile(bool prelu)
 {
-    using G = GemmGeom<PT>;
-    return {G::TM, G::TN, PT == 8 ? 2 : PT == 4 ? 3 : 4, G::LDS, prelu ? &pw_gemm_kernel<PT, true> : &pw_gemm_kernel<PT, false>};
+    using G = GemmGeom<PT, NW>;
+    return {G::TM, G::TN, G::NT, G::LDS, prelu ? &pw_gemm_kernel<PT, NW, true> : &pw_gemm_kernel<PT, NW, false>};
 }
-
-GemmTile pw_gemm_tile(int pt, bool prelu)
+GemmTile pw_gemm_tile(int pt, int nw, bool prelu)
 {
-    return pt == 8 ? gemm_tile<8>(prelu) : pt == 4 ? gemm_tile<4>(prelu) : gemm_tile<2>(prelu);
+    if (nw == 4) return pt == 8 ? gemm_tile<8, 4>(prelu) : pt == 4 ? gemm_tile<4, 4>(prelu) : gemm_tile<2, 4>(prelu);
+    return pt == 8 ? gemm_tile<8, 2>(prelu) : pt == 4 ? gemm_tile<4, 2>(prelu) : gemm_tile<2, 2>(prelu);
 }
 
 }  // namespace prom

@@ -46,3 +46,27 @@ def test_tile_kernel(shape, res):
             P.prom_pw_conv(x, wp, cout, rq, y, y=y)
             torch.cuda.synchronize()
             assert_same(y.cpu().numpy(), want, f"{shape} in place")
+
+
+# Launched alone: two wavefronts per tile, input channels that fill no whole k step, output channels that fill no
+# whole tile; the plan with the k loop innermost is the streaming kernel.
+NARROW = [(1, 1, 1, 16, 96), (1, 14, 14, 80, 112), (2, 9, 7, 96, 576), (3, 13, 11, 144, 208), (1, 7, 7, 160, 960),
+          (1, 5, 9, 240, 144), (2, 3, 5, 304, 272), (1, 7, 9, 464, 496), (9, 31, 29, 48, 320), (3, 55, 57, 256, 128)]
+
+
+@pytest.mark.parametrize("shape", NARROW, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("prelu", [False, True])
+def test_narrow_layers(shape, prelu):
+    import paper_2505_03254_amd as P
+    n, h, w, cin, cout = shape
+    L = make_pw_layer(9000 + 31 * cin + cout, n, h, w, cin, cout, signed_x=True, act_window=(-128, 127),
+                      with_residual=True, shift_range=(0, 9))
+    L.bias[::5] *= 100
+    neg = prelu_mult_neg(3, L.mult) if prelu else None
+    rq = P.Requant(dev(L.bias), dev(L.mult), dev(L.shift), -128, 127, dev(neg) if prelu else None)
+    for r in (None, L.residual):
+        want = oracle.pw_conv(L.x, L.weight, L.bias, L.mult, L.shift, -128, 127, residual=r, mult_neg=neg)
+        x, wp, rd = dev(L.x), dev(P.prom_pack_ternary(L.weight)), None if r is None else dev(r)
+        for plan in (None, P.PwPlan(k_outer=-1)):
+            got = P.prom_pw_conv_ex(x, wp, cout, rq, rd, plan=plan)
+            assert_same(got.cpu().numpy(), want, f"{shape} prelu={prelu} residual={r is not None} plan={plan}")
