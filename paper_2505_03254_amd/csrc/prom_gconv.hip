@@ -1106,14 +1106,15 @@ extern "C" int prom_gconv3x3_sequence(const prom_gconv_layer_t *layers, int coun
                 // workgroup's time per unit of work (a fixed part for staging, barriers and the fetch
                 // latency, plus the rounds in which its four wavefronts take the unit's groups of 32
                 // pixels; only their ratio matters.  1.3 to 2.0 was fitted to the lifetimes of workgroups
-                // whose round took twice the instructions it takes now; measured with this kernel, ResNeXt-50
-                // at batch 128 takes 278 us with 0.7 to 1.3 and 260 with 0.4, RegNetX-400MF 96 to 100 with
-                // any of them): the layer whose
+                // whose round took twice the instructions it takes now.  Shares move in steps, so times do too;
+                // RegNetX-400MF / the same as a PReLU network / ResNeXt-50 at batch 128, us: with 0.4
+                // 93.4 / 103.3 / 256, 0.5 93.2 / 104.0 / 255, 0.6 90.3 / 99.4 / 265, 0.8 90.1 / 99.4 / 276, 1.3
+                // 92.9 / 101.2 / 275; at batch 32 to 100 the same order): the layer whose
                 // workgroups would live longest gets the next ones.  Shares by the bytes alone leave the
                 // layers with small images far behind (a unit of three 7x7 images takes as long as a
                 // band of 112 pixels), shares by the rounds alone the large ones.
                 const int n = j - i;
-                constexpr double kUnitRound = 0.4;  // per round, against a fixed part of 2.0
+                constexpr double kUnitRound = 0.6;  // per round, against a fixed part of 2.0
                 double cost[kGconvMaxBatch];
                 int per_cb[kGconvMaxBatch], step[kGconvMaxBatch];
                 double cost_sum = 0;
