@@ -135,13 +135,14 @@ __device__ __forceinline__ int sbyte(uint32_t v, int i)
 //               clamp(floor(v), 0, 127) is half of that, rounded down -- one shift and one mask per dword
 //   kPairFull   window [-128, 127], every shift >= 1
 //   kPairLow    either of the two windows, every shift >= 1 (one maximum per output more)
+//   kPairClamp  any window, every shift >= 1: one shift and one clamp per output (requant_i64<false>)
 //   kPairAny    any window, any shift (requant_i64<true>)
 //   kPairPreluFull  PReLU layer (par = (bias, mult, mult_neg, shift)), window [-128, 127], every shift >= 2
 //   kPairPreluAny   PReLU layer, any window, any shift
-constexpr int kPairRelu = 0, kPairFull = 1, kPairAny = 2, kPairPreluFull = 3, kPairPreluAny = 4, kPairLow = 5;
+constexpr int kPairRelu = 0, kPairFull = 1, kPairAny = 2, kPairPreluFull = 3, kPairPreluAny = 4, kPairLow = 5, kPairClamp = 6;
 
 // What a form's shifts are reduced by in the parameters handed to requant_pair4.
-__host__ __device__ constexpr int pair_shift_less(int form) { return form == kPairRelu || form == kPairPreluFull ? 2 : form == kPairFull || form == kPairLow ? 1 : 0; }
+__host__ __device__ constexpr int pair_shift_less(int form) { return form == kPairRelu || form == kPairPreluFull ? 2 : form == kPairFull || form == kPairLow || form == kPairClamp ? 1 : 0; }
 
 // a0, a1: the accumulators of two pixels, four channels each; par: the channels' parameters as
 // requant_params made them, the shifts reduced by pair_shift_less(FORM); out0, out1: the packed outputs.
@@ -150,13 +151,13 @@ template <int FORM, bool BIASED = false>
 __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, const v4i (&par)[4], int lo, int hi,
                                               uint32_t &out0, uint32_t &out1)
 {
-    if constexpr (FORM == kPairAny || FORM == kPairPreluAny) {
+    if constexpr (FORM == kPairAny || FORM == kPairClamp || FORM == kPairPreluAny) {
         int v[4], w[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            if constexpr (FORM == kPairAny) {
-                v[r] = requant_i64<true>(a0[r], par[r], lo, hi);
-                w[r] = requant_i64<true>(a1[r], par[r], lo, hi);
+            if constexpr (FORM != kPairPreluAny) {
+                v[r] = requant_i64<FORM == kPairAny>(a0[r], par[r], lo, hi);
+                w[r] = requant_i64<FORM == kPairAny>(a1[r], par[r], lo, hi);
             } else {
                 const int b = BIASED ? 0 : par[r][0];
                 v[r] = requant_prelu_s(a0[r] + b, par[r][1], par[r][2], par[r][3], lo, hi);
@@ -211,16 +212,23 @@ __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, cons
     }
 }
 
+// The form for a window and channels whose shifts are all >= 1 (ge1), all >= 2 (ge2).  Every window has a form
+// without the 64-bit shift of kPairAny as long as no shift is 0: windows other than the first two through
+// kPairAny cost the depthwise kernel 4 to 11 % and the blocks with planes in LDS 2 to 5 %.
+__host__ __device__ constexpr int pair_form_of(bool prelu, bool ge1, bool ge2, int lo, int hi)
+{
+    const bool full = lo == -128 && hi == 127, relu = lo == 0 && hi == 127;
+    if (prelu) return full && ge2 ? kPairPreluFull : kPairPreluAny;
+    if (!ge1) return kPairAny;
+    return full ? kPairFull : relu ? (ge2 ? kPairRelu : kPairLow) : kPairClamp;
+}
+
 // The form a wavefront can take for the channels of its lanes; wave-uniform.
 // s: the smallest shift of the lane's channels.
 template <bool PRELU>
 __device__ __forceinline__ int pair_form(int s, int lo, int hi)
 {
-    const bool full = lo == -128 && hi == 127, relu = lo == 0 && hi == 127;
-    if constexpr (PRELU) return full && __builtin_amdgcn_ballot_w64(s < 2) == 0 ? kPairPreluFull : kPairPreluAny;
-    const bool ge1 = __builtin_amdgcn_ballot_w64(s < 1) == 0, ge2 = __builtin_amdgcn_ballot_w64(s < 2) == 0;
-    if (full) return ge1 ? kPairFull : kPairAny;
-    return relu && ge1 ? (ge2 ? kPairRelu : kPairLow) : kPairAny;
+    return pair_form_of(PRELU, PRELU || __builtin_amdgcn_ballot_w64(s < 1) == 0, __builtin_amdgcn_ballot_w64(s < 2) == 0, lo, hi);
 }
 
 __device__ __forceinline__ int min_shift(const v4i (&par)[4])

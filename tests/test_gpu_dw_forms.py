@@ -72,3 +72,38 @@ def test_block_forms(shape):
                              dev(d.weight), _requant(P, d, window, dn), dev(P.prom_pack_ternary(p.weight)),
                              _requant(P, p, pwin, None), B.add_residual, ws, path=path)
             assert_same(y.cpu().numpy(), want, f"{shape} {window} {shifts} prelu={prelu} path={path}")
+
+
+# Windows other than [0, 127] and [-128, 127] with no shift of 0: one-sided, of one value, at either end; shifts of
+# exactly 1 and up to 31
+OTHER = [((0, 100), (1, 9)), ((-100, 99), (1, 1)), ((1, 127), (2, 31)), ((-128, 126), (1, 31)), ((5, 5), (1, 9)),
+         ((-128, -128), (1, 9)), ((127, 127), (1, 9))]
+
+
+@pytest.mark.parametrize("window,shifts", OTHER, ids=lambda v: "_".join(map(str, v)))
+def test_other_windows(window, shifts):
+    import torch
+    import paper_2505_03254_amd as P
+    layers, wants = [], []
+    for n, h, w, c, stride in ((2, 9, 7, 20, 1), (1, 5, 6, 8, 1), (2, 11, 9, 36, 2)):
+        L = make_dw_layer(1200 + c, n, h, w, c, stride, signed_x=True, act_window=window, shift_range=shifts)
+        wants.append(oracle.dw_conv(L.x, L.weight, stride, L.bias, L.mult, L.shift, window[0], window[1]))
+        x, wd, rq = dev(L.x), dev(L.weight), _requant(P, L, window, None)
+        assert_same(P.prom_dw_conv(x, wd, stride, rq).cpu().numpy(), wants[-1], f"{c} {window} {shifts}")
+        layers.append((x, wd, stride, rq, torch.empty(wants[-1].shape, dtype=torch.int8, device="cuda")))
+    P.prom_dw_conv_sequence(layers)
+    torch.cuda.synchronize()
+    for l, want in zip(layers, wants):
+        assert_same(l[4].cpu().numpy(), want, f"{window} {shifts} in the shared launch")
+    n, h, w, cin, t, cout = 2, 9, 7, 16, 6, 16
+    B = make_block(1300, n, h, w, cin, t, cout, 1, signed_x=True, expand_shift=shifts, dw_shift=shifts, project_shift=(1, 9))
+    e, d, p = B.expand, B.dw, B.project
+    t1 = oracle.pw_conv(B.x, e.weight, e.bias, e.mult, e.shift, window[0], window[1])
+    t2 = oracle.dw_conv(t1, d.weight, 1, d.bias, d.mult, d.shift, window[0], window[1])
+    want = oracle.pw_conv(t2, p.weight, p.bias, p.mult, p.shift, -128, 127, residual=B.x if B.add_residual else None)
+    ws = torch.empty(P.prom_block_workspace_size(n, h, w, cin, cin * t, cout, 1), dtype=torch.int8, device="cuda")
+    for path in (P.BLOCK_PLANES, P.BLOCK_UNFUSED):
+        y = P.prom_block(dev(B.x), cin * t, cout, 1, dev(P.prom_pack_ternary(e.weight)), _requant(P, e, window, None),
+                         dev(d.weight), _requant(P, d, window, None), dev(P.prom_pack_ternary(p.weight)),
+                         _requant(P, p, (-128, 127), None), B.add_residual, ws, path=path)
+        assert_same(y.cpu().numpy(), want, f"block {window} {shifts} path={path}")

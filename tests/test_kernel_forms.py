@@ -1,0 +1,55 @@
+"""What the built kernels are: which form of requantisation a window takes, and that the depthwise kernels keep the
+registers that 7 wavefronts per SIMD allow."""
+import os
+import shutil
+import struct
+import subprocess
+
+import msgpack
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_forms_of_requantisation():
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    cmd = [hipcc, "--cuda-host-only", "-fsyntax-only", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
+           "-I" + os.path.join(ROOT, "paper_2505_03254_amd", "csrc"), "-x", "hip", os.path.join(ROOT, "tests", "pair_forms.hip")]
+    p = subprocess.run(cmd, capture_output=True, text=True)
+    assert p.returncode == 0, p.stderr
+
+
+def _kernels(path):
+    """name -> metadata of every kernel in the device code objects (ELF images) of a library built here."""
+    data = open(path, "rb").read()
+    out, at = {}, data.find(b"\x7fELF", 4)
+    while at >= 0:
+        if struct.unpack_from("<H", data, at + 18)[0] == 224:  # EM_AMDGPU
+            shoff, = struct.unpack_from("<Q", data, at + 40)
+            size, count = struct.unpack_from("<HH", data, at + 58)
+            for i in range(count):
+                kind, off, length = (struct.unpack_from("<I", data, at + shoff + i * size + 4)[0],
+                                     *struct.unpack_from("<QQ", data, at + shoff + i * size + 24))
+                pos = at + off
+                while kind == 7 and pos < at + off + length:  # SHT_NOTE
+                    n, d, t = struct.unpack_from("<III", data, pos)
+                    desc = pos + 12 + (n + 3) // 4 * 4
+                    if t == 32:  # NT_AMDGPU_METADATA
+                        for k in msgpack.unpackb(data[desc:desc + d])["amdhsa.kernels"]:
+                            out[k[".name"]] = k
+                    pos = desc + (d + 3) // 4 * 4
+        at = data.find(b"\x7fELF", at + 4)
+    return out
+
+
+def test_depthwise_registers():
+    import paper_2505_03254_amd as P
+    if not os.path.exists(P.library_path()):
+        from paper_2505_03254_amd.build import build
+        build()
+    found = {k: v for k, v in _kernels(P.library_path()).items() if "dw_kernel_v4" in k or "dw_batch_kernel" in k}
+    if not found:
+        pytest.skip("no readable kernel metadata")
+    assert len(found) == 4, sorted(found)
+    for name, k in found.items():
+        assert k[".vgpr_count"] <= 72 and k[".private_segment_fixed_size"] == 0, (name, k[".vgpr_count"])
