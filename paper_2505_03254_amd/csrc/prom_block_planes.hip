@@ -273,16 +273,10 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
 #pragma unroll
                 for (int r = 0; r < 4; ++r) par[r][3] -= pair_shift_less(decltype(mode)::value);
                 int pt = pt0;
-                // (the rare form takes two tiles at a time: less code)
-                constexpr bool RARE = decltype(mode)::value == kPairAny;
-                if constexpr (!RARE)
-                    for (; pt + 4 <= pt1; pt += 4) tiles(mode, PlMode<4>{}, pt);
-                for (; pt + 2 <= pt1; pt += 2) {
+                for (; pt + 4 <= pt1; pt += 4) tiles(mode, PlMode<4>{}, pt);
+                if (pt + 2 <= pt1) {
                     tiles(mode, PlMode<2>{}, pt);
-                    if constexpr (!RARE) {
-                        pt += 2;
-                        break;
-                    }
+                    pt += 2;
                 }
                 if (pt < pt1) tiles(mode, PlMode<1>{}, pt);
             };
@@ -293,6 +287,7 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
             } else {
                 if (form == kPairRelu) run(PlMode<kPairRelu>{});
                 else if (form == kPairFull || form == kPairLow) run(PlMode<kPairLow>{});
+                else if (form == kPairClamp) run(PlMode<kPairClamp>{});
                 else run(PlMode<kPairAny>{});
             }
         }
@@ -378,16 +373,10 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
 #pragma unroll
                 for (int r = 0; r < 4; ++r) par[r][3] -= pair_shift_less(decltype(mode)::value);
                 int pt = pt0;
-                // (the rare form takes two tiles at a time: less code)
-                constexpr bool RARE = decltype(mode)::value == kPairAny;
-                if constexpr (!RARE)
-                    for (; pt + 4 <= pt1; pt += 4) tiles(mode, PlMode<4>{}, pt);
-                for (; pt + 2 <= pt1; pt += 2) {
+                for (; pt + 4 <= pt1; pt += 4) tiles(mode, PlMode<4>{}, pt);
+                if (pt + 2 <= pt1) {
                     tiles(mode, PlMode<2>{}, pt);
-                    if constexpr (!RARE) {
-                        pt += 2;
-                        break;
-                    }
+                    pt += 2;
                 }
                 if (pt < pt1) tiles(mode, PlMode<1>{}, pt);
             };
@@ -398,6 +387,7 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
             } else {
                 if (form == kPairRelu) run(PlMode<kPairRelu>{});
                 else if (form == kPairFull || form == kPairLow) run(PlMode<kPairLow>{});
+                else if (form == kPairClamp) run(PlMode<kPairClamp>{});
                 else run(PlMode<kPairAny>{});
             }
         }
