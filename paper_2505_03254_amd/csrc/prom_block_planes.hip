@@ -510,6 +510,8 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
             };
             if (prelu_p) {
                 finish(PlMode<kPairPreluAny>{});
+            } else if constexpr (TPG == 1) {
+                finish(PlMode<kPairAny>{});  // (one tile does not pay for the test)
             } else {
                 const int form = pair_form<false>(min_shift(pr), a.lo_p, a.hi_p);
                 if (form == kPairFull) finish(PlMode<kPairFull>{});
