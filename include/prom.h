@@ -227,6 +227,15 @@ int prom_pw_conv_ex(const int8_t *x, int n, int h, int w, int cin,
 int prom_pw_plan_query(int n, int h, int w, int cin, int cout, prom_pw_plan_t *plan_out,
                        int *load_bytes_out);
 
+/* Which kernel prom_pw_conv_ex launches for a layer of this shape (with a residual, with mult_neg: 0 or 1;
+ * x, y, residual 16-byte aligned) under `plan` (NULL: the library's choice, prom_pw_conv): 1 and the workgroup
+ * tile of the kernel with the k loop outermost (k_outer above) in *tile_pixels x *tile_channels, or 0 and 0 x 0
+ * for the streaming and the generic kernel.  PROM_EINVAL if the plan is not realisable.  It differs from
+ * prom_pw_plan_query, whose plan is what the layer is in a shared launch: that plan given back to
+ * prom_pw_conv_ex asks for the streaming kernel by name.  Host only, launches nothing. */
+int prom_pw_kernel_query(int n, int h, int w, int cin, int cout, int has_residual, int prelu,
+                         const prom_pw_plan_t *plan, int *tile_pixels, int *tile_channels);
+
 /* One layer of a sequence for prom_pw_conv_sequence: the arguments of prom_pw_conv. */
 typedef struct {
     const int8_t *x;

@@ -125,6 +125,8 @@ def load_library():
     lib.prom_block_workspace_size.argtypes = [ci] * 7
     lib.prom_pw_plan_query.restype = ci
     lib.prom_pw_plan_query.argtypes = [ci, ci, ci, ci, ci, ctypes.POINTER(_PlanC), ctypes.POINTER(ci)]
+    lib.prom_pw_kernel_query.restype = ci
+    lib.prom_pw_kernel_query.argtypes = [ci, ci, ci, ci, ci, ci, ci, ctypes.POINTER(_PlanC), ctypes.POINTER(ci), ctypes.POINTER(ci)]
     lib.prom_pw_conv_sequence.restype = ci
     lib.prom_pw_conv_sequence.argtypes = [ctypes.POINTER(_PwLayerC), ci, ctypes.POINTER(ci), vp]
     lib.prom_dw_conv_sequence.restype = ci
@@ -573,6 +575,19 @@ def prom_pw_plan_query(n: int, h: int, w: int, cin: int, cout: int) -> dict:
            "prom_pw_plan_query")
     return {"tiles_per_wave": p.tiles_per_wave, "pixel_tiles": p.pixel_tiles,
             "workgroups": p.workgroups, "row_waves": p.row_waves, "k_outer": p.k_outer, "load_bytes": lb.value}
+
+
+def prom_pw_kernel_query(n: int, h: int, w: int, cin: int, cout: int, residual: bool = False, prelu: bool = False,
+                         plan: Optional[PwPlan] = None):
+    """(pixels, output channels) of the workgroup tile if prom_pw_conv_ex runs the layer on the kernel with the k
+    loop outermost (16-byte aligned tensors), None if it runs the streaming or the generic kernel."""
+    tm, tn = ctypes.c_int(0), ctypes.c_int(0)
+    rc = load_library().prom_pw_kernel_query(n, h, w, cin, cout, int(residual), int(prelu),
+                                             ctypes.byref(plan._c()) if plan is not None else None,
+                                             ctypes.byref(tm), ctypes.byref(tn))
+    if rc < 0:
+        raise PromError(rc, "prom_pw_kernel_query")
+    return (tm.value, tn.value) if rc else None
 
 
 def prom_pw_batch_class(n: int, h: int, w: int, cin: int, cout: int) -> int:

@@ -277,6 +277,7 @@ struct PwLaunch {
     KernelFn tfn;
     int tgrid, tthreads;
     size_t tlds;
+    int tm, tn;  // its pixels and output channels
 };
 
 // The tile kernel's shape for a layer: 16-pixel tiles per wavefront (2, 4 or 8) and wavefronts (2 or 4, 64
@@ -537,6 +538,8 @@ static int pw_prepare(const int8_t *x, int n, int h, int w, int cin, const void 
             L.tfn = t.fn;
             L.tthreads = t.threads;
             L.tlds = t.lds;
+            L.tm = t.tm;
+            L.tn = t.tn;
             L.ta = a;
             L.ta.n_chunks = (cout + t.tn - 1) / t.tn;
             L.ta.wg_per_chunk = (int)((M + t.tm - 1) / t.tm);
@@ -624,6 +627,22 @@ extern "C" int prom_pw_plan_query(int n, int h, int w, int cin, int cout, prom_p
     plan_out->k_outer = L.gemm ? 1 : 0;
     if (load_bytes_out) *load_bytes_out = L.xmode;
     return PROM_OK;
+}
+
+extern "C" int prom_pw_kernel_query(int n, int h, int w, int cin, int cout, int has_residual, int prelu,
+                                    const prom_pw_plan_t *plan, int *tile_pixels, int *tile_channels)
+{
+    if (!tile_pixels || !tile_channels) return PROM_EINVAL;
+    // (addresses that are only looked at for being there)
+    prom_requant_t rq = {};
+    rq.mult_neg = prelu ? reinterpret_cast<const int32_t *>(uintptr_t{4096}) : nullptr;
+    const int8_t *residual = has_residual ? reinterpret_cast<const int8_t *>(uintptr_t{8192}) : nullptr;
+    prom::PwLaunch L;
+    const int rc = prom::pw_prepare(nullptr, n, h, w, cin, nullptr, cout, &rq, residual, nullptr, nullptr, plan, 0, true, L);
+    if (rc != PROM_OK) return rc;
+    *tile_pixels = L.tile ? L.tm : 0;
+    *tile_channels = L.tile ? L.tn : 0;
+    return L.tile ? 1 : 0;
 }
 
 namespace prom {
