@@ -526,13 +526,14 @@ static int pw_prepare(const int8_t *x, int n, int h, int w, int cin, const void 
         if (!gemm_ok || cin % 64 != 0 || plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves || plan->workgroups)
             return PROM_EINVAL;
     }
-    const bool explicit_stream = plan && (plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves || plan->workgroups);
+    const bool explicit_stream = plan && (plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves);
     if (gemm_ok && k_outer != -1 && !explicit_stream) {
         int pt = M >= 128 * 256 ? 8 : 4, nw = 4;
         const bool pays = gemm_plan(M, cin, cout, &pt, &nw);
         const long long pieces = ((M + 255) / 256) * ((cout + 127) / 128);
         L.gemm = k_outer == 1 || (cin % 64 == 0 && cin >= 1024 && cout >= 256 && pieces * (cin / 64) >= 2800);
-        L.tile = L.gemm || pays;
+        // (a number of workgroups alone is one for the streaming kernel, unless the layer's plan is the tile kernel)
+        L.tile = L.gemm || (pays && !(plan && plan->workgroups));
         if (L.tile) {
             const GemmTile t = pw_gemm_tile(pt, nw, a.mult_neg != nullptr);
             L.tfn = t.fn;

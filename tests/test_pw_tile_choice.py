@@ -32,3 +32,9 @@ def test_query_names_the_kernel(P):
         P.prom_pw_kernel_query(1, 4, 4, 72, 32, plan=P.PwPlan(k_outer=1))
     with pytest.raises(P.PromError):
         P.prom_pw_kernel_query(0, 4, 4, 64, 32)
+
+
+def test_workgroups_alone_leave_the_planned_kernel(P):
+    # a layer planned for the tile kernel stays on it; one that is not gets the streaming kernel's workgroups
+    assert P.prom_pw_kernel_query(128, 14, 14, 1024, 512, plan=P.PwPlan(workgroups=64)) is not None
+    assert P.prom_pw_kernel_query(1, 14, 14, 64, 384, plan=P.PwPlan(workgroups=4)) is None
