@@ -280,18 +280,41 @@ struct PwLaunch {
     int tm, tn;  // its pixels and output channels
 };
 
-// The tile kernel's shape for a layer: 16-pixel tiles per wavefront (2, 4 or 8) and wavefronts (2 or 4, 64
-// output channels each); false where the streaming kernel is the faster one.  Times in us, streaming against
-// tile kernel, one launch per layer, batch 1 to 128 of 40 layer shapes of the three networks.
-//
-// Choice of the shape.  A tile takes base + step * KS however few there are; with r tiles per compute
-// unit the layer takes 2.5 + r * (c0 + c1 * KS), and at least half the steps more than one tile once some units
-// have two (512 -> 512, 2 wavefronts: 5.4 at 196 tiles, 6.5 at 296, 7.3 at 784).  The constants are fits: 14x14 1024 -> 512 takes 20.9 /
-// 23.6 at batch 128 with 4 wavefronts and 8 / 4 pixel tiles, 20.4 / 23.3 with 2; 10.6 with (4, 4), 10.3 with (2, 2)
-// at batch 32.  Two wavefronts suit narrow layers and few pixels (56x56 256 -> 128, batch 32: 17.3 with 4
-// wavefronts, 11.9 with 2, streaming 12.9).
-//
-// Where the streaming kernel stays:
+// The tile kernel's shape for a layer: 16-pixel tiles per wavefront (2, 4 or 8) and wavefronts (2 or 4, 64 output
+// channels each).  An estimate of each shape's time in us, the smallest is taken: with `resident` tiles on a
+// compute unit at a time, the busiest unit's tiles come in batches; k of them at once take
+//     wait + wait_ks * KS + k * (work + work_ks * KS) + crowd * k * (k - 1) * KS,
+// the first batch `first` more, the later ones `again` times the wait.
+// Fitted to the choice of the fastest of the six on 11000 layers (the three networks' shapes at batch 1 to 256 and
+// random ones up to 2048 channels, with and without residual and PReLU): 0.2 % behind the fastest on average, 1.6 % or
+// less for 95 of 100 (the times of a shape where it is never the fastest are not fitted).  A first fit, with times in
+// proportion to the tiles, was 4 % behind: it took (8, 2) for 1.4 to 2.3 tiles per unit, where that is 7 to 28 %
+// behind (4, 2): 14x14 512 -> 320 at batch 107 11.9 instead of 9.8, 160 -> 384 at batch 96 8.2 instead of 6.7;
+// 1024 -> 320 at batch 128 runs 18.4 / 18.8 / 21.9 / 17.7 us as (8, 2), (8, 4), (4, 4), (4, 2).
+static void gemm_shape(long long M, int cin, int cout, int *pt, int *nw)
+{
+    static const struct { int pt, nw, resident; double first, wait, wait_ks, work, work_ks, again, crowd; } kFit[] = {
+        {8, 4, 2, 3.71, 0.15, 0.303, 1.608, 0.258, 1.22, 0.0090}, {4, 4, 3, 3.25, 0.12, 0.243, 0.950, 0.172, 1.13, 0.0027},
+        {2, 4, 4, 2.79, 0.34, 0.131, 0.330, 0.051, 1.77, 0.5723}, {8, 2, 4, 3.41, 0.12, 0.320, 0.912, 0.173, 1.60, 0.0055},
+        {4, 2, 6, 2.96, 0.41, 0.255, 0.428, 0.093, 1.33, 0.0042}, {2, 2, 8, 2.13, 0.56, 0.103, 0.368, 0.061, 2.50, 0.0086}};
+    const int KS = (cin + 63) / 64;
+    double best_us = 0;
+    for (const auto &f : kFit) {
+        const long long tiles = (M + 16 * f.pt - 1) / (16 * f.pt) * ((cout + 64 * f.nw - 1) / (64 * f.nw));
+        const long long most = (tiles + kNumCU - 1) / kNumCU, full = (most - 1) / f.resident;
+        const double wait = f.wait + f.wait_ks * KS;
+        auto batch = [&](double k) { return wait + k * (f.work + f.work_ks * KS) + f.crowd * k * (k - 1) * KS; };
+        const double us = f.first + full * ((f.again - 1) * wait + batch(f.resident)) + batch((double)(most - full * f.resident));
+        if (best_us == 0 || us < best_us) {
+            *pt = f.pt;
+            *nw = f.nw;
+            best_us = us;
+        }
+    }
+}
+
+// Whether the tile kernel is the faster one for a layer launched alone.  Times in us, streaming against tile kernel,
+// one launch per layer, batch 1 to 128 of 40 layer shapes of the three networks.  The streaming kernel stays for
 //   - fewer than 96 output channels: 28x28 192 -> 64 3.6 / 3.8 to 8.4 / 11.0, 64 -> 64 3.4 / 3.6 to 7.6 / 8.8;
 //   - up to 5 k steps and many pixels, where a layer is nothing but a stream, unless the tiles waste nothing.
 //     The line is drawn in pixels times what the tiles waste of their k steps and channels: one k step 64 -> 256
@@ -309,7 +332,7 @@ struct PwLaunch {
 //     pixels 5.8 / 7.5, at 3136 8.6 / 8.1; 1024 -> 1024 6.0 / 7.6 and 12.9 / 9.6; 2048 -> 1024 at 784 pixels
 //     11.9 / 12.7, at 1568 19.1 / 12.9: level at M*N*K of about 1.1e9 (1024 channels), 1.5e9 to 2e9 (2048);
 //     960 -> 320 8.0 / 9.7, 576 -> 160 9.0 / 9.9.
-static bool gemm_plan(long long M, int cin, int cout, int *pt, int *nw)
+static bool gemm_pays(long long M, int cin, int cout)
 {
     const int KS = (cin + 63) / 64;
     const double waste = 128.0 * ((cout + 127) / 128) / cout;
@@ -326,20 +349,6 @@ static bool gemm_plan(long long M, int cin, int cout, int *pt, int *nw)
         } else {
             if (3 * 256 * ((cout + 255) / 256) > 4 * cout) return false;
             if ((double)M * cout * cin < 1.1e9 * (KS > 16 ? 0.7 * KS / 16.0 + 0.3 : 1.0)) return false;
-        }
-    }
-    static const struct { int pt, nw; double base, step, c0, c1; } kFit[] = {
-        {8, 4, 4.3, 0.43, 3.7, 0.46}, {4, 4, 3.4, 0.295, 1.8, 0.28}, {2, 4, 3.1, 0.27, 1.2, 0.16},
-        {8, 2, 4.5, 0.45, 1.95, 0.24}, {4, 2, 3.6, 0.31, 0.94, 0.145}, {2, 2, 3.2, 0.24, 0.56, 0.075}};
-    double best_us = 0;
-    for (const auto &f : kFit) {
-        const double r = (double)((M + 16 * f.pt - 1) / (16 * f.pt) * ((cout + 64 * f.nw - 1) / (64 * f.nw))) / kNumCU;
-        const double alone = f.base + (r > 1 ? 1.5 : 1) * f.step * KS, many = 2.5 + r * (f.c0 + f.c1 * KS);
-        const double us = alone > many ? alone : many;
-        if (best_us == 0 || us < best_us) {
-            *pt = f.pt;
-            *nw = f.nw;
-            best_us = us;
         }
     }
     return true;
@@ -528,13 +537,14 @@ static int pw_prepare(const int8_t *x, int n, int h, int w, int cin, const void 
     }
     const bool explicit_stream = plan && (plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves);
     if (gemm_ok && k_outer != -1 && !explicit_stream) {
-        int pt = M >= 128 * 256 ? 8 : 4, nw = 4;
-        const bool pays = gemm_plan(M, cin, cout, &pt, &nw);
+        const bool pays = gemm_pays(M, cin, cout);
         const long long pieces = ((M + 255) / 256) * ((cout + 127) / 128);
         L.gemm = k_outer == 1 || (cin % 64 == 0 && cin >= 1024 && cout >= 256 && pieces * (cin / 64) >= 2800);
         // (a number of workgroups alone is one for the streaming kernel, unless the layer's plan is the tile kernel)
         L.tile = L.gemm || (pays && !(plan && plan->workgroups));
         if (L.tile) {
+            int pt, nw;
+            gemm_shape(M, cin, cout, &pt, &nw);
             const GemmTile t = pw_gemm_tile(pt, nw, a.mult_neg != nullptr);
             L.tfn = t.fn;
             L.tthreads = t.threads;

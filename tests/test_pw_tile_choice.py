@@ -38,3 +38,16 @@ def test_workgroups_alone_leave_the_planned_kernel(P):
     # a layer planned for the tile kernel stays on it; one that is not gets the streaming kernel's workgroups
     assert P.prom_pw_kernel_query(128, 14, 14, 1024, 512, plan=P.PwPlan(workgroups=64)) is not None
     assert P.prom_pw_kernel_query(1, 14, 14, 64, 384, plan=P.PwPlan(workgroups=4)) is None
+
+
+def test_tile_shapes(P):
+    # (8, 2) has too few wavefronts in flight for one or two tiles per compute unit
+    for shape in ((107, 14, 14, 512, 320), (96, 14, 14, 160, 384), (128, 14, 14, 1024, 320)):
+        assert P.prom_pw_kernel_query(*shape) == (64, 128), shape
+    assert P.prom_pw_kernel_query(64, 14, 14, 2048, 320)[1] == 128  # 320 channels are two and a half tiles of 128
+    assert P.prom_pw_kernel_query(128, 14, 14, 1024, 512) == (128, 256)
+    # a layer that is planned for the tile kernel, or asked for by the caller, gets the shape that the estimate names
+    # also where the rule for narrower layers would keep the streaming kernel
+    assert P.prom_pw_plan_query(128, 14, 14, 1024, 272)["k_outer"] == 1
+    assert P.prom_pw_kernel_query(128, 14, 14, 1024, 272)[1] == 128
+    assert P.prom_pw_kernel_query(1, 7, 7, 1024, 64, plan=P.PwPlan(k_outer=1)) == (32, 128)
