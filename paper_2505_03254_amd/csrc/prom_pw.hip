@@ -328,11 +328,19 @@ static void gemm_shape(long long M, int cin, int cout, int *pt, int *nw)
 //     compute unit: 14x14 512 -> 1024 with 2.3 / 2.7 / 3.06 / 3.8 / 4.6 tiles 18.5 / 19.6, 20.3 / 19.6, 22.4 / 22.6,
 //     24.9 / 23.2, 29.0 / 27.5; 384 -> 768 with 2.02 / 2.3 / 2.9 tiles 15.4 / 16.9, 15.7 / 17.1, 17.4 / 17.4;
 //     2 to 5 k steps the same with 2 to 2.5 tiles: 128 -> 256 12.7 / 13.7, 192 -> 768 13.6 / 14.6 (2.3 tiles each);
-//   - deeper layers with few pixels or channels, which it spreads over more workgroups: 1024 -> 512 at 784
-//     pixels 5.8 / 7.5, at 3136 8.6 / 8.1; 1024 -> 1024 6.0 / 7.6 and 12.9 / 9.6; 2048 -> 1024 at 784 pixels
-//     11.9 / 12.7, at 1568 19.1 / 12.9: level at M*N*K of about 1.1e9 (1024 channels), 1.5e9 to 2e9 (2048);
-//     960 -> 320 8.0 / 9.7, 576 -> 160 9.0 / 9.9.
-static bool gemm_pays(long long M, int cin, int cout)
+//   - more than 8 k steps and no more workgroups than the chip holds of the streaming kernel at a time (64 pixels
+//     times a chunk of channels each; 160 KB of LDS hold two or three): it then takes one round, one chain of
+//     k steps, and so does the tile kernel, with a longer step.  Tile against streaming time, median and 10th to 90th
+//     percentile of 1300 layers from 13 k steps on, by workgroups over places: 1.20 (1.09 to 1.50) up to
+//     1; 0.8 (0.71 to 1.01) from 1 to 1.25; 0.85 to 2; 0.72 above.  Where rows are whole 128-byte lines,
+//     the third workgroup per unit gains the streaming kernel nothing (0.9 from two thirds of three places
+//     on).  Where they are no whole 64 bytes, its decode of the weights is slower (0.95 from half the places
+//     on, 0.85 above one).  9 to 12 k steps: 1.0 to 1.05 up to 1, 0.85 above.  (The line was drawn by M*N*K before,
+//     at half as many workgroups: 1344 -> 768 at 1925 pixels ran in 11.0 us instead of 8.6);
+//   - the same and 256-channel tiles less than three quarters full: 960 -> 320 8.0 / 9.7; fewer than 256
+//     channels: 576 -> 160 9.0 / 9.9.
+// stream_lds: LDS of a workgroup of the streaming kernel, stream_nt: its channel tiles.
+static bool gemm_pays(long long M, int cin, int cout, int stream_nt, size_t stream_lds)
 {
     const int KS = (cin + 63) / 64;
     const double waste = 128.0 * ((cout + 127) / 128) / cout;
@@ -348,7 +356,10 @@ static bool gemm_pays(long long M, int cin, int cout)
             if (r8 > 2 && r8 <= 4 && r8 < 0.88 * std::ceil(r8)) return false;
         } else {
             if (3 * 256 * ((cout + 255) / 256) > 4 * cout) return false;
-            if ((double)M * cout * cin < 1.1e9 * (KS > 16 ? 0.7 * KS / 16.0 + 0.3 : 1.0)) return false;
+            const long long wgs = (M + 63) / 64 * ((cout + 16 * stream_nt - 1) / (16 * stream_nt));
+            const int most = stream_nt <= 2 ? 4 : stream_nt <= 4 ? 3 : 2;  // what its registers allow
+            const int places = std::min(cin % 128 == 0 ? 2 : most, std::max(1, (int)(160 * 1024 / stream_lds)));
+            if (2 * wgs <= (cin % 64 ? 1 : 2) * (long long)kNumCU * places) return false;
         }
     }
     return true;
@@ -537,7 +548,7 @@ static int pw_prepare(const int8_t *x, int n, int h, int w, int cin, const void 
     }
     const bool explicit_stream = plan && (plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves);
     if (gemm_ok && k_outer != -1 && !explicit_stream) {
-        const bool pays = gemm_pays(M, cin, cout);
+        const bool pays = gemm_pays(M, cin, cout, nt, L.lds);
         const long long pieces = ((M + 255) / 256) * ((cout + 127) / 128);
         L.gemm = k_outer == 1 || (cin % 64 == 0 && cin >= 1024 && cout >= 256 && pieces * (cin / 64) >= 2800);
         // (a number of workgroups alone is one for the streaming kernel, unless the layer's plan is the tile kernel)

@@ -51,3 +51,14 @@ def test_tile_shapes(P):
     assert P.prom_pw_plan_query(128, 14, 14, 1024, 272)["k_outer"] == 1
     assert P.prom_pw_kernel_query(128, 14, 14, 1024, 272)[1] == 128
     assert P.prom_pw_kernel_query(1, 7, 7, 1024, 64, plan=P.PwPlan(k_outer=1)) == (32, 128)
+
+
+def test_deep_layers_with_few_pixels_stay(P):
+    # as long as the streaming kernel's workgroups all run at a time
+    for shape in ((8, 14, 14, 960, 896), (25, 7, 11, 1344, 768), (4, 14, 14, 1024, 512), (1, 32, 64, 1024, 1024)):
+        assert P.prom_pw_kernel_query(*shape) is None, shape
+    for shape in ((1, 3, 683, 1024, 1024), (32, 14, 14, 1024, 512), (16, 14, 14, 1536, 1024)):
+        assert P.prom_pw_kernel_query(*shape) is not None, shape
+    # rows that are no whole 64 bytes: from half as many on
+    assert P.prom_pw_kernel_query(6, 14, 14, 992, 1024) is not None
+    assert P.prom_pw_kernel_query(2, 14, 14, 992, 1024) is None
