@@ -62,3 +62,14 @@ def test_deep_layers_with_few_pixels_stay(P):
     # rows that are no whole 64 bytes: from half as many on
     assert P.prom_pw_kernel_query(6, 14, 14, 992, 1024) is not None
     assert P.prom_pw_kernel_query(2, 14, 14, 992, 1024) is None
+
+
+def test_streams_without_residual_stay(P):
+    for shape in ((64, 56, 56, 128, 256), (128, 56, 56, 128, 256), (64, 56, 56, 256, 256), (128, 28, 28, 256, 512),
+                  (192, 14, 14, 192, 768)):
+        assert P.prom_pw_kernel_query(*shape) is None, shape
+        assert P.prom_pw_kernel_query(*shape, prelu=True) is not None, shape
+    for shape in ((128, 56, 56, 128, 256), (128, 28, 28, 256, 512), (192, 14, 14, 192, 768)):
+        assert P.prom_pw_kernel_query(*shape, residual=True) is not None, shape
+    for shape in ((16, 56, 56, 128, 256), (32, 28, 28, 256, 512), (80, 28, 28, 256, 512)):  # few tiles, a full last round
+        assert P.prom_pw_kernel_query(*shape) is not None, shape
