@@ -322,7 +322,7 @@ static void gemm_shape(long long M, int cin, int cout, int *pt, int *nw)
 //     at 100 K (267 K); 64 -> 160 6.1 / 5.3 at 25 K (40 K), 10.7 / 12.9 at 100 K (160 K); more k steps 96 -> 576
 //     12.8 / 9.5 at 25 K (37 K), 160 -> 160 8.9 / 7.1 at 25 K (48 K); 128 -> 384 5.4 / 4.6 at 6 K, 9.0 / 9.1 at 19 K,
 //     12.9 / 13.4 at 50 K; 208 -> 304 9.8 / 9.3 at 19 K (29 K), 15.1 / 16.0 at 50 K (78 K); 256 -> 128 7.4 / 6.9 at
-//     25 K, 12.2 / 12.0 at 75 K, 20.7 / 25.3 at 200 K;
+//     25 K, level from 75 K to 100 K, 16.6 / 20.3 at 150 K;
 //   - 2 to 5 k steps without that waste, from two tiles of 128 x 256 per compute unit on, without residual and PReLU
 //     (the streaming kernel adds a residual dword by dword and requantises PReLU outputs one by one):
 //     128 -> 256 23.4 / 26.7 at 200 K pixels, 39.5 / 43.2 at 400 K, with a residual 30.6 / 31.2 and 54.1 / 53.0, with
@@ -334,7 +334,10 @@ static void gemm_shape(long long M, int cin, int cout, int *pt, int *nw)
 //   - 6 to 8 k steps and a last round of tiles that leaves much of the chip idle, two to four tiles of 128 x 256 per
 //     compute unit: 14x14 512 -> 1024 with 2.3 / 2.7 / 3.06 / 3.8 / 4.6 tiles 18.5 / 19.6, 20.3 / 19.6, 22.4 / 22.6,
 //     24.9 / 23.2, 29.0 / 27.5; 384 -> 768 with 2.02 / 2.3 / 2.9 tiles 15.4 / 16.9, 15.7 / 17.1, 17.4 / 17.4;
-//     2 to 5 k steps the same with 2 to 2.5 tiles: 128 -> 256 12.7 / 13.7, 192 -> 768 13.6 / 14.6 (2.3 tiles each);
+//     2 to 5 k steps with a residual, without waste and without PReLU the same with 2 to 2.5 tiles: 192 -> 768 14.5 / 15.4
+//     (2.05 tiles), 128 -> 256 16.2 / 15.5, 256 -> 512 18.0 / 17.9 (2.3 tiles each); layers that waste are ahead there
+//     too, in smaller tiles: 96 -> 576 with 2.05 / 2.3 / 2.43 tiles 11.6 / 9.4, 12.5 / 9.9, 12.7 / 12.3, 160 -> 304 with
+//     2.3 tiles 12.4 / 10.7;
 //   - more than 8 k steps and no more workgroups than the chip holds of the streaming kernel at a time (64 pixels
 //     times a chunk of channels each; 160 KB of LDS hold two or three): it then takes one round, one chain of
 //     k steps, and so does the tile kernel, with a longer step.  Tile against streaming time, median and 10th to 90th
@@ -346,8 +349,8 @@ static void gemm_shape(long long M, int cin, int cout, int *pt, int *nw)
 //     at half as many workgroups: 1344 -> 768 at 1925 pixels ran in 11.0 us instead of 8.6);
 //   - the same and 256-channel tiles less than three quarters full: 960 -> 320 8.0 / 9.7; fewer than 256
 //     channels: 576 -> 160 9.0 / 9.9.
-// plain: neither residual nor PReLU; stream_nt, stream_lds: channel tiles and LDS of a streaming workgroup.
-static bool gemm_pays(long long M, int cin, int cout, bool plain, int stream_nt, size_t stream_lds)
+// stream_nt, stream_lds: channel tiles and LDS of a streaming workgroup.
+static bool gemm_pays(long long M, int cin, int cout, bool residual, bool prelu, int stream_nt, size_t stream_lds)
 {
     const int KS = (cin + 63) / 64;
     const double waste = 128.0 * ((cout + 127) / 128) / cout;
@@ -355,9 +358,8 @@ static bool gemm_pays(long long M, int cin, int cout, bool plain, int stream_nt,
     const double r8 = (double)((M + 127) / 128 * ((cout + 255) / 256)) / kNumCU;
     const bool idle_end = r8 > 2 && r8 <= 4 && r8 < 0.88 * std::ceil(r8);  // the last round leaves much of the chip idle
     if (KS <= 5) {
-        if (KS > 1 && r8 > 2 && r8 < 2.5) return false;
         const bool exact = cout % 256 == 0 && cin % 64 == 0;
-        if (KS > 1 && exact && plain && r8 > 2 && (KS <= 3 || r8 > 4 || idle_end)) return false;
+        if (KS > 1 && exact && !prelu && r8 > 2 && (residual ? r8 < 2.5 : KS <= 3 || r8 > 4 || idle_end)) return false;
         if (cout < (KS <= 3 ? 96 : 128) || (KS == 1 ? px > 130e3 : !exact && px > 50e3)) return false;
     } else {
         if (cout < 256 || waste > 1.34) return false;
@@ -557,7 +559,7 @@ static int pw_prepare(const int8_t *x, int n, int h, int w, int cin, const void 
     }
     const bool explicit_stream = plan && (plan->tiles_per_wave || plan->pixel_tiles || plan->row_waves);
     if (gemm_ok && k_outer != -1 && !explicit_stream) {
-        const bool pays = gemm_pays(M, cin, cout, !a.residual && !a.mult_neg, nt, L.lds);
+        const bool pays = gemm_pays(M, cin, cout, a.residual != nullptr, a.mult_neg != nullptr, nt, L.lds);
         const long long pieces = ((M + 255) / 256) * ((cout + 127) / 128);
         L.gemm = k_outer == 1 || (cin % 64 == 0 && cin >= 1024 && cout >= 256 && pieces * (cin / 64) >= 2800);
         // (a number of workgroups alone is one for the streaming kernel, unless the layer's plan is the tile kernel)

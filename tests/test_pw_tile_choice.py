@@ -73,3 +73,11 @@ def test_streams_without_residual_stay(P):
         assert P.prom_pw_kernel_query(*shape, residual=True) is not None, shape
     for shape in ((16, 56, 56, 128, 256), (32, 28, 28, 256, 512), (80, 28, 28, 256, 512)):  # few tiles, a full last round
         assert P.prom_pw_kernel_query(*shape) is not None, shape
+
+
+def test_ragged_channels_with_two_tiles_per_unit(P):
+    # 96 -> 576 runs in its own tiles of 128 x 128; how many of 128 x 256 there would be does not matter
+    for n in (96, 111, 114, 128, 135, 139, 142):
+        assert P.prom_pw_kernel_query(n, 14, 14, 96, 576) is not None, n
+    assert P.prom_pw_kernel_query(128, 14, 14, 96, 576) == (128, 128)
+    assert P.prom_pw_kernel_query(114, 14, 14, 192, 768, residual=True) is None     # fills its tiles
