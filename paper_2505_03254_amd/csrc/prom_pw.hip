@@ -319,10 +319,14 @@ static void gemm_shape(long long M, int cin, int cout, int *pt, int *nw)
 //   - up to 5 k steps and many pixels, where a layer is nothing but a stream, unless the tiles waste nothing.
 //     The line is drawn in pixels times what the tiles waste of their k steps and channels: one k step 64 -> 256
 //     14.1 / 13.0 at 100 K pixels, 22.1 / 23.9 at 200 K; 32 -> 192 7.9 / 5.4 at 25 K (67 K with the waste), 13.1 / 13.1
-//     at 100 K (267 K); 64 -> 160 6.1 / 5.3 at 25 K (40 K), 10.7 / 12.9 at 100 K (160 K); more k steps 96 -> 576
+//     at 100 K (267 K); more k steps 96 -> 576
 //     12.8 / 9.5 at 25 K (37 K), 160 -> 160 8.9 / 7.1 at 25 K (48 K); 128 -> 384 5.4 / 4.6 at 6 K, 9.0 / 9.1 at 19 K,
 //     12.9 / 13.4 at 50 K; 208 -> 304 9.8 / 9.3 at 19 K (29 K), 15.1 / 16.0 at 50 K (78 K); 256 -> 128 7.4 / 6.9 at
 //     25 K, level from 75 K to 100 K, 16.6 / 20.3 at 150 K;
+//   - 64 channels, whose weights the streaming kernel decodes fastest, into columns that fill no whole tiles, without
+//     a residual, from 12.5 M outputs on: 64 -> 160 8.0 / 7.7 at 50 K pixels (8 M), 10.8 / 13.3 at 100 K, 64 -> 208
+//     9.0 / 8.4 at 57 K (12 M), 64 -> 144 10.8 / 11.5 at 91 K (13.1 M), 64 -> 224 11.0 / 12.4 at 96 K, 64 -> 288
+//     12.1 / 13.7 at 67 K; with a residual 64 -> 208 11.4 / 9.7 at 61 K, 64 -> 160 11.5 / 11.7 at 75 K;
 //   - 2 to 5 k steps without that waste, from two tiles of 128 x 256 per compute unit on, without residual and PReLU
 //     (the streaming kernel adds a residual dword by dword and requantises PReLU outputs one by one):
 //     128 -> 256 23.4 / 26.7 at 200 K pixels, 39.5 / 43.2 at 400 K, with a residual 30.6 / 31.2 and 54.1 / 53.0, with
@@ -361,6 +365,7 @@ static bool gemm_pays(long long M, int cin, int cout, bool residual, bool prelu,
         const bool exact = cout % 256 == 0 && cin % 64 == 0;
         if (KS > 1 && exact && !prelu && r8 > 2 && (residual ? r8 < 2.5 : KS <= 3 || r8 > 4 || idle_end)) return false;
         if (cout < (KS <= 3 ? 96 : 128) || (KS == 1 ? px > 130e3 : !exact && px > 50e3)) return false;
+        if (cin == 64 && cout % 128 != 0 && !residual && (double)M * cout > 12.5e6) return false;
     } else {
         if (cout < 256 || waste > 1.34) return false;
         if (KS <= 8) {

@@ -81,3 +81,11 @@ def test_ragged_channels_with_two_tiles_per_unit(P):
         assert P.prom_pw_kernel_query(n, 14, 14, 96, 576) is not None, n
     assert P.prom_pw_kernel_query(128, 14, 14, 96, 576) == (128, 128)
     assert P.prom_pw_kernel_query(114, 14, 14, 192, 768, residual=True) is None     # fills its tiles
+
+
+def test_64_channels_into_ragged_columns_stay_from_12_million_outputs(P):
+    for shape in ((128, 28, 28, 64, 160), (122, 28, 28, 64, 224), (86, 28, 28, 64, 288), (90, 28, 28, 64, 336)):
+        assert P.prom_pw_kernel_query(*shape) is None, shape
+    assert P.prom_pw_kernel_query(77, 28, 28, 64, 208, residual=True) is not None
+    for shape in ((32, 28, 28, 64, 160), (64, 28, 28, 64, 160), (73, 28, 28, 64, 208), (96, 28, 28, 64, 256), (96, 28, 28, 48, 112)):
+        assert P.prom_pw_kernel_query(*shape) is not None, shape
