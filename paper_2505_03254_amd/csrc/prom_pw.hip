@@ -342,6 +342,10 @@ static void gemm_shape(long long M, int cin, int cout, int *pt, int *nw)
 //     (2.05 tiles), 128 -> 256 16.2 / 15.5, 256 -> 512 18.0 / 17.9 (2.3 tiles each); layers that waste are ahead there
 //     too, in smaller tiles: 96 -> 576 with 2.05 / 2.3 / 2.43 tiles 11.6 / 9.4, 12.5 / 9.9, 12.7 / 12.3, 160 -> 304 with
 //     2.3 tiles 12.4 / 10.7;
+//   - 6 to 8 k steps into 256 or 384 channels, one or two of the streaming kernel's chunks, without residual and PReLU,
+//     from two tiles per compute unit on: 512 -> 256 30.0 / 30.7 at 125 K pixels, 35.9 / 36.2 at 150 K, 44.4 / 47.2 at
+//     200 K, 352 -> 384 29.1 / 32.0 at 94 K; 512 -> 512 62.6 / 60.8 at 150 K, with a residual 512 -> 256 53.0 / 49.2 at
+//     200 K;
 //   - more than 8 k steps and no more workgroups than the chip holds of the streaming kernel at a time (64 pixels
 //     times a chunk of channels each; 160 KB of LDS hold two or three): it then takes one round, one chain of
 //     k steps, and so does the tile kernel, with a longer step.  Tile against streaming time, median and 10th to 90th
@@ -369,7 +373,7 @@ static bool gemm_pays(long long M, int cin, int cout, bool residual, bool prelu,
     } else {
         if (cout < 256 || waste > 1.34) return false;
         if (KS <= 8) {
-            if (idle_end) return false;
+            if (idle_end || (!residual && !prelu && r8 > 2 && (cout == 256 || cout == 384))) return false;
         } else {
             if (3 * 256 * ((cout + 255) / 256) > 4 * cout) return false;
             const long long wgs = (M + 63) / 64 * ((cout + 16 * stream_nt - 1) / (16 * stream_nt));

@@ -89,3 +89,11 @@ def test_64_channels_into_ragged_columns_stay_from_12_million_outputs(P):
     assert P.prom_pw_kernel_query(77, 28, 28, 64, 208, residual=True) is not None
     for shape in ((32, 28, 28, 64, 160), (64, 28, 28, 64, 160), (73, 28, 28, 64, 208), (96, 28, 28, 64, 256), (96, 28, 28, 48, 112)):
         assert P.prom_pw_kernel_query(*shape) is not None, shape
+
+
+def test_narrow_outputs_of_6_to_8_k_steps_stay(P):
+    for shape in ((64, 56, 56, 512, 256), (30, 56, 56, 352, 384)):
+        assert P.prom_pw_kernel_query(*shape) is None, shape
+        assert P.prom_pw_kernel_query(*shape, residual=True) is not None, shape
+    assert P.prom_pw_kernel_query(64, 28, 28, 512, 256) is not None
+    assert P.prom_pw_kernel_query(48, 56, 56, 512, 512) is not None
