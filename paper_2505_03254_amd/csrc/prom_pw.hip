@@ -353,8 +353,9 @@ static void gemm_shape(long long M, int cin, int cout, int *pt, int *nw)
 //     1; 0.8 (0.71 to 1.01) from 1 to 1.25; 0.85 to 2; 0.72 above.  Where rows are whole 128-byte lines,
 //     the third workgroup per unit gains the streaming kernel nothing (0.9 from two thirds of three places
 //     on).  Where they are no whole 64 bytes, its decode of the weights is slower (0.95 from half the places
-//     on, 0.85 above one).  9 to 12 k steps: 1.0 to 1.05 up to 1, 0.85 above.  (The line was drawn by M*N*K before,
-//     at half as many workgroups: 1344 -> 768 at 1925 pixels ran in 11.0 us instead of 8.6);
+//     on, 0.85 above one).  Odd multiples of 64 with a residual are level (0.99 to 1.03) up to two rounds.  9 to 12
+//     k steps: 1.0 to 1.05 up to 1, 0.85 above.  (The line was drawn by M*N*K before, at half as many
+//     workgroups: 1344 -> 768 at 1925 pixels ran in 11.0 us instead of 8.6);
 //   - the same and 256-channel tiles less than three quarters full: 960 -> 320 8.0 / 9.7; fewer than 256
 //     channels: 576 -> 160 9.0 / 9.9.
 // stream_nt, stream_lds: channel tiles and LDS of a streaming workgroup.
@@ -379,7 +380,8 @@ static bool gemm_pays(long long M, int cin, int cout, bool residual, bool prelu,
             const long long wgs = (M + 63) / 64 * ((cout + 16 * stream_nt - 1) / (16 * stream_nt));
             const int most = stream_nt <= 2 ? 4 : stream_nt <= 4 ? 3 : 2;  // what its registers allow
             const int places = std::min(cin % 128 == 0 ? 2 : most, std::max(1, (int)(160 * 1024 / stream_lds)));
-            if (2 * wgs <= (cin % 64 ? 1 : 2) * (long long)kNumCU * places) return false;
+            const int halves = cin % 64 ? 1 : cin % 128 && residual && KS > 12 ? 4 : 2;  // of the places
+            if (2 * wgs <= halves * (long long)kNumCU * places) return false;
         }
     }
     return true;

@@ -97,3 +97,9 @@ def test_narrow_outputs_of_6_to_8_k_steps_stay(P):
         assert P.prom_pw_kernel_query(*shape, residual=True) is not None, shape
     assert P.prom_pw_kernel_query(64, 28, 28, 512, 256) is not None
     assert P.prom_pw_kernel_query(48, 56, 56, 512, 512) is not None
+
+
+def test_odd_multiples_of_64_with_a_residual_stay_up_to_two_rounds(P):
+    assert P.prom_pw_kernel_query(44, 14, 14, 960, 448, residual=True) is None
+    assert P.prom_pw_kernel_query(44, 14, 14, 960, 448) is not None
+    assert P.prom_pw_kernel_query(128, 14, 14, 960, 448, residual=True) is not None
