@@ -326,7 +326,8 @@ static void gemm_shape(long long M, int cin, int cout, int *pt, int *nw)
 //   - 64 channels, whose weights the streaming kernel decodes fastest, into columns that fill no whole tiles, without
 //     a residual, from 12.5 M outputs on: 64 -> 160 8.0 / 7.7 at 50 K pixels (8 M), 10.8 / 13.3 at 100 K, 64 -> 208
 //     9.0 / 8.4 at 57 K (12 M), 64 -> 144 10.8 / 11.5 at 91 K (13.1 M), 64 -> 224 11.0 / 12.4 at 96 K, 64 -> 288
-//     12.1 / 13.7 at 67 K; with a residual 64 -> 208 11.4 / 9.7 at 61 K, 64 -> 160 11.5 / 11.7 at 75 K;
+//     12.1 / 13.7 at 67 K; with a residual 64 -> 208 11.4 / 9.7 at 61 K; 64 -> 160 11.5 / 11.7 at 75 K (120 K with the
+//     waste), 11.3 / 12.5 with PReLU as well;
 //   - 2 to 5 k steps without that waste, from two tiles of 128 x 256 per compute unit on, without residual and PReLU
 //     (the streaming kernel adds a residual dword by dword and requantises PReLU outputs one by one):
 //     128 -> 256 23.4 / 26.7 at 200 K pixels, 39.5 / 43.2 at 400 K, with a residual 30.6 / 31.2 and 54.1 / 53.0, with
@@ -369,7 +370,8 @@ static bool gemm_pays(long long M, int cin, int cout, bool residual, bool prelu,
     if (KS <= 5) {
         const bool exact = cout % 256 == 0 && cin % 64 == 0;
         if (KS > 1 && exact && !prelu && r8 > 2 && (residual ? r8 < 2.5 : KS <= 3 || r8 > 4 || idle_end)) return false;
-        if (cout < (KS <= 3 ? 96 : 128) || (KS == 1 ? px > 130e3 : !exact && px > 50e3)) return false;
+        if (cout < (KS <= 3 ? 96 : 128) || (KS == 1 ? px > (cin == 64 && cout % 128 ? 115e3 : 130e3) : !exact && px > 50e3))
+            return false;
         if (cin == 64 && cout % 128 != 0 && !residual && (double)M * cout > 12.5e6) return false;
     } else {
         if (cout < 256 || waste > 1.34) return false;

@@ -87,6 +87,7 @@ def test_64_channels_into_ragged_columns_stay_from_12_million_outputs(P):
     for shape in ((128, 28, 28, 64, 160), (122, 28, 28, 64, 224), (86, 28, 28, 64, 288), (90, 28, 28, 64, 336)):
         assert P.prom_pw_kernel_query(*shape) is None, shape
     assert P.prom_pw_kernel_query(77, 28, 28, 64, 208, residual=True) is not None
+    assert P.prom_pw_kernel_query(96, 28, 28, 64, 160, residual=True, prelu=True) is None
     for shape in ((32, 28, 28, 64, 160), (64, 28, 28, 64, 160), (73, 28, 28, 64, 208), (96, 28, 28, 64, 256), (96, 28, 28, 48, 112)):
         assert P.prom_pw_kernel_query(*shape) is not None, shape
 
