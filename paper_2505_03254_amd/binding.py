@@ -7,13 +7,20 @@ from dataclasses import dataclass
 from typing import Optional
 
 import numpy as np
-import torch as _torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libprom.so")
 _lib = None
+_torch = None  # torch, from the first call that needs it on (importing this package does not)
 
 PROM_OK = 0
+
+
+def _import_torch():
+    global _torch
+    import torch
+    _torch = torch
+    return torch
 
 
 class PromError(RuntimeError):
@@ -190,7 +197,7 @@ class Requant:
     def _c(self) -> _RequantC:
         # (every layer call comes through here: 0.6 us, with a loop over the tensors and an import 1.0)
         bias, mult, shift, neg = self.bias, self.mult, self.shift, self.mult_neg
-        i32 = _torch.int32
+        i32 = (_torch or _import_torch()).int32
         assert bias.dtype == i32 and bias.is_contiguous() and bias.is_cuda
         assert mult.dtype == i32 and mult.is_contiguous() and mult.is_cuda
         assert shift.dtype == i32 and shift.is_contiguous() and shift.is_cuda
@@ -218,13 +225,14 @@ def _stream_ptr(stream) -> int:
     if stream is None:
         # the handle of torch.cuda.current_stream() without the Stream object around it: 0.2 us against 2.9,
         # a third of what a layer call costs the host
-        _torch.cuda._lazy_init()
-        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+        torch = _torch or _import_torch()
+        torch.cuda._lazy_init()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return int(stream.cuda_stream)
 
 
 def _dev_i8(t, name):
-    if not (t.is_cuda and t.dtype == _torch.int8 and t.is_contiguous()):
+    if not (t.is_cuda and t.dtype == (_torch or _import_torch()).int8 and t.is_contiguous()):
         raise TypeError(f"{name} must be a contiguous int8 device tensor")
     return t
 
