@@ -1,5 +1,5 @@
-"""The tile kernel of the pointwise layers at the sizes where it can go wrong: every number of pixel tiles
-per wavefront, 1 to 9 k steps (whole and broken groups of four), ragged pixel counts, column tiles that
+"""The tile kernel of the pointwise layers at the sizes where it can go wrong: each of its six tiles (named by the
+library, test_every_tile), 1 to 10 k steps (whole and broken groups of four), ragged pixel counts, column tiles that
 the channels do not fill, and every form of its epilogue, against the CPU oracle, bit for bit."""
 import numpy as np
 import pytest
@@ -70,3 +70,37 @@ def test_narrow_layers(shape, prelu):
         for plan in (None, P.PwPlan(k_outer=-1)):
             got = P.prom_pw_conv_ex(x, wp, cout, rq, rd, plan=plan)
             assert_same(got.cpu().numpy(), want, f"{shape} prelu={prelu} residual={r is not None} plan={plan}")
+
+
+# The six tiles of the kernel (pixels x channels) at k steps that are no multiple of four, pixels and channels that fill
+# no whole tile, input channels that fill the last k step and that do not.
+TILES = {(32, 128): [(1, 5, 7, 384, 304), (1, 5, 7, 304, 144)], (32, 256): [(29, 13, 11, 320, 144), (47, 5, 7, 432, 528)],
+         (64, 128): [(23, 31, 29, 320, 144), (47, 13, 11, 336, 528)], (64, 256): [(2, 55, 57, 448, 400), (5, 53, 51, 304, 144)],
+         (128, 128): [(9, 55, 57, 320, 272), (9, 55, 57, 336, 304)], (128, 256): [(11, 31, 29, 448, 528), (5, 53, 51, 592, 400)]}
+
+
+@pytest.mark.parametrize("tile,shape", [(t, s) for t in TILES for s in TILES[t]], ids=lambda v: "x".join(map(str, v)))
+def test_every_tile(tile, shape):
+    import paper_2505_03254_amd as P
+    n, h, w, cin, cout = shape
+    # [0, 127]; any shift; another window; PReLU in the full window and with shift 0: with the residual every second time
+    for f, (window, shifts, prelu) in enumerate([FORMS[0], FORMS[3], FORMS[4], FORMS[5], FORMS[6]]):
+        res = f % 2 == 1
+        assert P.prom_pw_kernel_query(*shape, residual=res, prelu=prelu) == tile
+        L = make_pw_layer(8100 + 31 * cin + cout + f, n, h, w, cin, cout, signed_x=True, act_window=window,
+                          with_residual=True, shift_range=shifts)
+        L.bias[::5] *= 100
+        neg = prelu_mult_neg(f, L.mult) if prelu else None
+        rq = P.Requant(dev(L.bias), dev(L.mult), dev(L.shift), window[0], window[1], dev(neg) if prelu else None)
+        r = L.residual if res else None
+        want = oracle.pw_conv(L.x, L.weight, L.bias, L.mult, L.shift, window[0], window[1], residual=r, mult_neg=neg)
+        got = P.prom_pw_conv(dev(L.x), dev(P.prom_pack_ternary(L.weight)), cout, rq, dev(r) if res else None)
+        assert_same(got.cpu().numpy(), want, f"{tile} {shape} {window} {shifts} prelu={prelu} residual={res}")
+
+
+def test_narrow_layers_run_on_the_tile_kernel():
+    import paper_2505_03254_amd as P
+    for shape in NARROW:
+        for res in (False, True):
+            for prelu in (False, True):
+                assert P.prom_pw_kernel_query(*shape, residual=res, prelu=prelu) is not None, shape

@@ -1,5 +1,5 @@
-"""The pointwise kernel for wide layers (k loop outermost over a 128-channel x 256-pixel workgroup
-tile, plan field k_outer) against the CPU oracle, bit for bit: forced on shapes with ragged pixel
+"""The pointwise kernel for wide layers (k loop outermost over a workgroup tile of 32 to 128 pixels x 128 or
+256 channels, plan field k_outer) against the CPU oracle, bit for bit: forced on shapes with ragged pixel
 counts and channel counts off the tile sizes, with and without the skip connection (also in place),
 shifts down to 0, the PReLU epilogue, and the shapes the library takes it for by itself."""
 import numpy as np
@@ -21,7 +21,7 @@ def P():
 
 WIDE_SHAPES = [
     # n, h, w, cin, cout: one and many k steps (odd and even counts), one ragged and several column
-    # tiles of 128 channels, pixel counts below one row tile, ragged, and several row tiles
+    # tiles, pixel counts below one row tile, ragged, and several row tiles
     (1, 1, 1, 64, 16), (3, 7, 7, 64, 400), (2, 14, 14, 192, 128), (1, 5, 13, 320, 144),
     (2, 9, 9, 512, 1024), (1, 14, 14, 1024, 512), (4, 7, 7, 2048, 272), (1, 31, 33, 128, 640),
     (1, 20, 13, 4096, 32),
