@@ -228,7 +228,11 @@ __host__ __device__ constexpr int pair_form_of(bool prelu, bool ge1, bool ge2, i
 template <bool PRELU>
 __device__ __forceinline__ int pair_form(int s, int lo, int hi)
 {
-    return pair_form_of(PRELU, PRELU || __builtin_amdgcn_ballot_w64(s < 1) == 0, __builtin_amdgcn_ballot_w64(s < 2) == 0, lo, hi);
+    // (shifts are looked at only where they decide: ahead of the window, the test takes the PReLU kernel of the
+    // grouped convolutions from 242 registers to 256 and 180 bytes of scratch, RegNetX-400MF from 99 to 113 us)
+    if constexpr (PRELU) return lo == -128 && hi == 127 && __builtin_amdgcn_ballot_w64(s < 2) == 0 ? kPairPreluFull : kPairPreluAny;
+    const bool ge2 = __builtin_amdgcn_ballot_w64(s < 2) == 0;
+    return pair_form_of(false, __builtin_amdgcn_ballot_w64(s < 1) == 0, ge2, lo, hi);
 }
 
 __device__ __forceinline__ int min_shift(const v4i (&par)[4])

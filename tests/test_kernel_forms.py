@@ -1,5 +1,5 @@
-"""What the built kernels are: which form of requantisation a window takes, and that the depthwise kernels keep the
-registers that 7 wavefronts per SIMD allow."""
+"""What the built kernels are: which form of requantisation a window takes, that the depthwise kernels keep the
+registers that 7 wavefronts per SIMD allow, and that the grouped kernels keep their loops out of scratch memory."""
 import os
 import shutil
 import struct
@@ -42,14 +42,26 @@ def _kernels(path):
     return out
 
 
-def test_depthwise_registers():
+def _found(*names):
     import paper_2505_03254_amd as P
     if not os.path.exists(P.library_path()):
         from paper_2505_03254_amd.build import build
         build()
-    found = {k: v for k, v in _kernels(P.library_path()).items() if "dw_kernel_v4" in k or "dw_batch_kernel" in k}
+    found = {k: v for k, v in _kernels(P.library_path()).items() if any(n in k for n in names)}
     if not found:
         pytest.skip("no readable kernel metadata")
+    return found
+
+
+def test_depthwise_registers():
+    found = _found("dw_kernel_v4", "dw_batch_kernel")
     assert len(found) == 4, sorted(found)
     for name, k in found.items():
         assert k[".vgpr_count"] <= 72 and k[".private_segment_fixed_size"] == 0, (name, k[".vgpr_count"])
+
+
+def test_grouped_kernels_use_no_scratch():
+    found = _found("gconv_tapk_kernel", "gconv_tapk_batch_kernel")
+    assert len(found) == 4, sorted(found)
+    for name, k in found.items():
+        assert k[".private_segment_fixed_size"] == 0, (name, k[".private_segment_fixed_size"])
