@@ -20,6 +20,7 @@
 // (36 instructions per output byte at gs = 16), i.e. the kernel is ALU bound there.
 #include "prom.h"
 #include "prom_device.h"
+#include "prom_gconv_shares.h"
 #include "prom_launch.h"
 
 #include <algorithm>
@@ -1102,22 +1103,22 @@ extern "C" int prom_gconv3x3_sequence(const prom_gconv_layer_t *layers, int coun
                 // The launch has as many workgroups as are resident at once (two per compute unit):
                 // alone, a small layer spreads over the chip for the sake of latency; here that would
                 // queue thousands of workgroups that each live one latency chain long.  They are shared
-                // out so that every layer's workgroups live about equally long, by an estimate of a
-                // workgroup's time per unit of work (a fixed part for staging, barriers and the fetch
-                // latency, plus the rounds in which its four wavefronts take the unit's groups of 32
-                // pixels; only their ratio matters.  1.3 to 2.0 was fitted to the lifetimes of workgroups
-                // whose round took twice the instructions it takes now.  Shares move in steps, so times do too;
-                // RegNetX-400MF / the same as a PReLU network / ResNeXt-50 at batch 128, us: with 0.4
-                // 93.4 / 103.3 / 256, 0.5 93.2 / 104.0 / 255, 0.6 90.3 / 99.4 / 265, 0.8 90.1 / 99.4 / 276, 1.3
-                // 92.9 / 101.2 / 275; at batch 32 to 100 the same order): the layer whose
-                // workgroups would live longest gets the next ones.  Shares by the bytes alone leave the
-                // layers with small images far behind (a unit of three 7x7 images takes as long as a
-                // band of 112 pixels), shares by the rounds alone the large ones.
+                // out so that the last one ends as early as it can, by an estimate of a workgroup's time
+                // per unit of work: a fixed part for staging, barriers and the fetch latency, plus the
+                // rounds in which its four wavefronts take the unit's groups of 32 pixels; only their
+                // ratio matters.  Shares by the bytes alone leave the layers with small images far
+                // behind (a unit of three 7x7 images takes as long as a band of 112 pixels), shares by
+                // the rounds alone the large ones.  Measured with 0.6 and shares in proportion to the
+                // cost, then with 0.5 and gconv_shares, us at batch 32 / 64 / 128 / 256: ResNeXt-50 80.6 / 146.4
+                // / 266.3 / 510 -> 79.0 / 144.4 / 259.5 / 495, as a PReLU network 86.5 / 153.9 / 280.6 / 536 -> 86.4
+                // / 153.9 / 277.9 / 530; RegNetX-400MF 32.7 / 52.5 / 92.1 / 177 -> 32.7 / 52.6 / 92.5 / 173, PReLU
+                // 35.0 / 56.7 / 101.0 / 198 -> 35.3 / 56.8 / 101.1 / 189.  At 0.8 ResNeXt-50 takes 276.
                 const int n = j - i;
-                constexpr double kUnitRound = 0.6;  // per round, against a fixed part of 2.0
-                double cost[kGconvMaxBatch];
+                // per round, against a fixed part of 2.0; the other kernel's shares hardly move with it, but
+                // with 0.5 its units at batch 6 are chosen worse (ResNeXt-50 33.4 against 31.8 us)
+                const double unit_round = kind == GconvLaunch::TAPK ? 0.5 : 0.6;
+                GconvShareLayer share[kGconvMaxBatch];
                 int per_cb[kGconvMaxBatch], step[kGconvMaxBatch];
-                double cost_sum = 0;
                 // Small images: a layer alone takes no more images per unit of work than leaves a
                 // workgroup for every compute unit; here a layer has a dozen workgroups whatever it
                 // does, and takes as many images per unit as cost least per image by the same
@@ -1133,7 +1134,7 @@ extern "C" int prom_gconv3x3_sequence(const prom_gconv_layer_t *layers, int coun
                     if (gmax > L.a.N) gmax = L.a.N;
                     auto per_image = [&](int g) {
                         const int rounds = ((g * bd.R * L.a.Wo + 31) / 32 + 3) / 4;
-                        return (2.0 + kUnitRound * rounds) / g;
+                        return (2.0 + unit_round * rounds) / g;
                     };
                     int best = bd.G;
                     for (int g = 1; g <= gmax; ++g)
@@ -1149,85 +1150,11 @@ extern "C" int prom_gconv3x3_sequence(const prom_gconv_layer_t *layers, int coun
                     const GconvLaunch &L = prepared[(size_t)(i + k)];
                     const int npix = (L.bd.G > 1 ? L.bd.G : 1) * L.bd.R * L.a.Wo;
                     const int rounds = ((npix + 31) / 32 + 3) / 4;
-                    cost[k] = (double)L.bd.ncb * L.bd.units * (2.0 + kUnitRound * rounds);
-                    cost_sum += cost[k];
+                    share[k] = {L.bd.ncb, L.bd.units, 2.0 + unit_round * rounds};
                 }
                 // (three per compute unit would fit LDS and registers of the tap-in-k kernel: 108-114
                 // against 91 us for RegNetX-400MF's 22 layers, 301-313 against 264 for ResNeXt-50's)
-                constexpr int slots = kGconvBatchSlots;
-                int used = 0;
-                for (int k = 0; k < n; ++k) {
-                    const GconvBand &bd = prepared[(size_t)(i + k)].bd;
-                    const double ideal = slots * cost[k] / cost_sum / bd.ncb;
-                    // several channel blocks and enough workgroups: multiples of 8, for the XCD-aware order
-                    step[k] = (bd.ncb > 1 && ideal >= 8 && bd.units >= 8) ? 8 : 1;
-                    int w = (int)(ideal / step[k]) * step[k];
-                    if (w < step[k]) w = step[k];
-                    if (w > bd.units) w = bd.units / step[k] * step[k];
-                    per_cb[k] = w;
-                    used += w * bd.ncb;
-                }
-                for (;;) {  // the remaining workgroups, one step at a time, to the layer that would end last
-                    int best = -1;
-                    double best_life = 0;
-                    for (int k = 0; k < n; ++k) {
-                        const GconvBand &bd = prepared[(size_t)(i + k)].bd;
-                        if (per_cb[k] + step[k] > bd.units || used + step[k] * bd.ncb > slots) continue;
-                        const double life = cost[k] / ((double)per_cb[k] * bd.ncb);
-                        if (best < 0 || life > best_life) {
-                            best = k;
-                            best_life = life;
-                        }
-                    }
-                    if (best < 0) break;
-                    per_cb[best] += step[best];
-                    used += step[best] * prepared[(size_t)(i + best)].bd.ncb;
-                }
-                // A layer that takes its workgroups 8 per channel block at a time can be left with
-                // half of what it needs when the others' minimum shares have used up the launch: while
-                // the layer that would end last can still grow, it takes workgroups from layers
-                // that would end a quarter sooner even without them (RegNetX-400MF at batch 256: 174
-                // against 223 us; with any gain taken, batch 32 and 128 lose 3-6 %: the estimate is
-                // no finer than that).
-                for (int pass = 0; pass < 4 * slots; ++pass) {
-                    int last = -1;
-                    double last_life = 0;
-                    for (int k = 0; k < n; ++k) {
-                        const double life = cost[k] / ((double)per_cb[k] * prepared[(size_t)(i + k)].bd.ncb);
-                        if (life > last_life) {
-                            last_life = life;
-                            last = k;
-                        }
-                    }
-                    const GconvBand &lb = prepared[(size_t)(i + last)].bd;
-                    if (per_cb[last] + step[last] > lb.units) break;
-                    int trial[kGconvMaxBatch];
-                    for (int k = 0; k < n; ++k) trial[k] = per_cb[k];
-                    int need = step[last] * lb.ncb - (slots - used);
-                    while (need > 0) {
-                        int donor = -1;
-                        double donor_life = 0;
-                        for (int k = 0; k < n; ++k) {
-                            if (k == last || trial[k] < 2 * step[k]) continue;
-                            const double life =
-                                cost[k] / ((double)(trial[k] - step[k]) * prepared[(size_t)(i + k)].bd.ncb);
-                            if (donor < 0 || life < donor_life) {
-                                donor = k;
-                                donor_life = life;
-                            }
-                        }
-                        if (donor < 0 || donor_life * 1.25 >= last_life) break;
-                        trial[donor] -= step[donor];
-                        need -= step[donor] * prepared[(size_t)(i + donor)].bd.ncb;
-                    }
-                    if (need > 0) break;
-                    trial[last] += step[last];
-                    used = 0;
-                    for (int k = 0; k < n; ++k) {
-                        per_cb[k] = trial[k];
-                        used += per_cb[k] * prepared[(size_t)(i + k)].bd.ncb;
-                    }
-                }
+                gconv_shares(share, n, kGconvBatchSlots, per_cb, step);
                 // Order: the layers without the XCD-aware order first, packed without gaps (padding
                 // blocks would leave some XCDs with more workgroups than they can hold at once), then,
                 // from a multiple of 8 on, the others; within each kind the least bytes first (a small
