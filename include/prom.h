@@ -103,7 +103,7 @@ int prom_requant_check(const prom_requant_t *rq, int channels, int cin, int *bad
  * field zero; k_outer = -1 keeps it off; 0 leaves the choice to the library.  The library plans it
  * from 1024 input and 256 output channels on where it is the faster one; a smaller layer (cin % 16 == 0) launched
  * alone may run on it as well, its plan (prom_pw_plan_query) and its place in a shared launch stay those of
- * the streaming kernel. */
+ * the streaming kernel, and prom_pw_kernel_query tells which of the two it runs on and in which tiles. */
 typedef struct {
     int32_t tiles_per_wave;  /* NT: 16-channel output tiles each wavefront owns (1..10)       */
     int32_t pixel_tiles;     /* PT: 16-pixel tiles a wavefront processes per iteration (1,2,4)*/

@@ -429,12 +429,14 @@ static bool plan_fused(BlockArgs &a, BlockFn &fn, size_t &lds, int &grid, bool f
 // than the serial chunk loop.  The form stays available through PROM_BLOCK_DWPROJ and
 // prom_dw_pw_conv: it moves one intermediate tensor less through HBM.
 // Whether PROM_BLOCK_AUTO takes the plane-resident kernel where it applies.  Measured (GPU time per
-// call, MobileNetV2 blocks): with at least 12 planes of hidden channels on maps up to 28x28 the one
-// kernel beats the three launches and the chunk-interleaved fused kernel (batch 128: 28x28x192
-// 26 against 27 us fused, stride 2 18 against 28; 14x14x384 15 against 29; 14x14x576 21 against 34;
-// 7x7x960 20 to 25 against 29).  On larger maps the band's halo rows and the vector ALU's
-// requantisation of the expanded tensor cost more than the three streaming kernels (56x56x144: 89
-// against 66 us; 112x112x96: 109 against 88).
+// call, MobileNetV2 blocks, one kernel against three launches replayed from a HIP graph): with at least 12
+// planes of hidden channels on maps up to 28x28 the one kernel is ahead (batch 128: 28x28x192 21.6 against
+// 32.5 us, stride 2 15.6 against 23.8; 14x14x384 13.2 against 21.6; 14x14x576 17.7 against 26.5; 7x7x960 17.7
+// against 20.4), but for 7x7x960 into 320 channels (21.7 against 20.3) and 7x7x960 from batch 32 down (15.9
+// against 14.2), where a program without graphs pays for two more launches.  On larger maps the band's halo
+// rows and the vector ALU's requantisation of the expanded tensor cost as much as the three streaming
+// kernels: 56x56x144 69.8 against 69.6 at batch 128 and 39.8 against 40.7 at 64, stride 2 41.0 against 40.8 and 25.0
+// against 29.8; 112x112x96 102 against 93 at batch 128, 58 against 51 at 64, 30.2 against 32.7 at 32.
 static bool planes_is_faster(int n, int h, int w, int cin, int chid, int cout, int stride)
 {
     (void)cin; (void)cout; (void)stride;

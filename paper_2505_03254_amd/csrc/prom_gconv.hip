@@ -583,9 +583,9 @@ __device__ __forceinline__ void gconv_tapk_body(const GconvArgs &a, const GconvB
     // the parameters together
     if (wg < bd.units) fetch_band(wg);
     // ---- fragments: lane (i, kg) of tile t, step s holds, for output channel 16t + i of the block and
-    // tap 4s + kg, the weights on input channels 16t .. 16t+15 (zero outside the channel's group).  A plain
-    // layer then holds them in registers, a third of the LDS reads of a group of pixels less; a PReLU layer
-    // needs the registers for its parameters.
+    // tap 4s + kg, the weights on input channels 16t .. 16t+15 (zero outside the channel's group).  They
+    // are read from LDS for each group of 32 pixels, except that a plain layer holds those of one tile in
+    // registers (3 of its 12, 3 of the 36 reads of a group); a PReLU layer needs the registers for its parameters.
     auto fragment = [&](int t, int s) __attribute__((always_inline)) {
         if (a.wfrag) return a.wfrag[(long long)cb * (4 * 3 * 64) + (t * 3 + s) * 64 + lane];
         const int tap = 4 * s + g;
