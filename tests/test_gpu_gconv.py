@@ -247,6 +247,14 @@ def test_gconv_sequence_at_benchmark_size_equals_layer_by_layer(P, family, batch
         assert_same(entries[i][4][:2].cpu().numpy(), want, f"{family} layer {i} against the oracle")
 
 
+@pytest.mark.parametrize("batch", [1, 2, 10, 23])
+@pytest.mark.parametrize("family", ["regnetx_400mf", "resnext50_32x4d"])
+def test_gconv_sequence_at_small_batches_equals_layer_by_layer(P, family, batch):
+    """Layers with fewer units of work than workgroups, with no room for the next multiple of eight workgroups
+    (batch 2 of ResNeXt-50), and with a last unit of fewer images than the others."""
+    test_gconv_sequence_at_benchmark_size_equals_layer_by_layer(P, family, batch)
+
+
 def test_gconv_matrix_core_kernels_on_random_shapes(P):
     """Seeded random shapes for the two matrix-core kernels: odd sizes down to one pixel, channel counts
     that leave a partial block of 64, several images per unit of work, both strides, all three epilogue
