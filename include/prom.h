@@ -402,10 +402,17 @@ int prom_block_ex(const int8_t *x, int n, int h, int w, int cin, int chid, int c
                   int add_residual, void *workspace, size_t workspace_bytes,
                   int8_t *y, int path, void *stream);
 
-/* 1 if prom_block (PROM_BLOCK_AUTO) runs this shape as one kernel of either kind (pointers
- * assumed aligned), 0 if as three launches through the workspace, PROM_EINVAL for bad dimensions.
- * Host only, launches nothing. */
+/* 1 if prom_block (PROM_BLOCK_AUTO) runs this shape as one of the two kernels that keep a band of the
+ * expanded tensor in LDS (pointers assumed aligned), 0 if as three launches through the workspace,
+ * PROM_EINVAL for bad dimensions -- unless the kernel of pixel tiles takes the shape over
+ * (prom_block_tile_applies).  Host only, launches nothing. */
 int prom_block_is_fused(int n, int h, int w, int cin, int chid, int cout, int stride);
+
+/* Positive (which of its variants) if PROM_BLOCK_AUTO takes the kernel whose wavefronts own pixel tiles instead of what
+ * prom_block_is_fused names (prelu != 0: the expansion or the depthwise layer has negative-side multipliers; pointers
+ * assumed 8-byte aligned): cin and cout <= 64 and multiples of 4, chid % 16 == 0, tensors below 2 GiB, and estimated to
+ * be faster.  0 if not, PROM_EINVAL for bad dimensions.  Host only. */
+int prom_block_tile_applies(int n, int h, int w, int cin, int chid, int cout, int stride, int prelu);
 
 /* 1 if the chunk-interleaved fused kernel (PROM_BLOCK_FUSED) applies to the shape at all (cin % 8 == 0, chid % 4 == 0, cout % 4 == 0,
  * cout <= 160, chid <= 192, a band of rows fits in LDS), 0 if not. */

@@ -126,6 +126,8 @@ def load_library():
     lib.prom_dw_pw_can_fuse.argtypes = [ci] * 6
     lib.prom_block_can_fuse.restype = ci
     lib.prom_block_can_fuse.argtypes = [ci] * 7
+    lib.prom_block_tile_applies.restype = ci
+    lib.prom_block_tile_applies.argtypes = [ci] * 8
     lib.prom_block_planes_applies.restype = ci
     lib.prom_block_planes_applies.argtypes = [ci] * 7
     lib.prom_block_workspace_size.restype = sz
@@ -469,6 +471,13 @@ def prom_block_planes_applies(n: int, h: int, w: int, cin: int, chid: int, cout:
     if rc < 0:
         raise PromError(rc, "prom_block_planes_applies")
     return bool(rc)
+
+
+def prom_block_tile_applies(n: int, h: int, w: int, cin: int, chid: int, cout: int, stride: int, prelu: bool = False) -> int:
+    rc = load_library().prom_block_tile_applies(n, h, w, cin, chid, cout, stride, int(prelu))
+    if rc < 0:
+        raise PromError(rc, "prom_block_tile_applies")
+    return rc
 
 
 def prom_block_can_fuse(n: int, h: int, w: int, cin: int, chid: int, cout: int, stride: int) -> bool:

@@ -22,6 +22,9 @@
 #include "prom_pw_stream.h"
 #include "prom_launch.h"
 #include "prom_block_planes.h"
+#include "prom_block_tile.h"
+
+#include <cstring>
 
 #include <mutex>
 #include <vector>
@@ -447,6 +450,71 @@ static bool planes_is_faster(int n, int h, int w, int cin, int chid, int cout, i
     return (long long)n * h * w * chid <= (48LL << 20);
 }
 
+// Whether PROM_BLOCK_AUTO takes the kernel of pixel tiles (plan in `a`), by two estimates in microseconds: its planner's
+// and that of what it would replace -- the plane-resident kernel (planes_cost > 0, that planner's clocks; fitted to the
+// measured times of 989 blocks, error 5 %) or three launches.  At 0.9 times, over 1104 blocks of batch 1 to 256 on maps
+// of 26 to 115, it is slower than what it replaces by more than 3 % on one, and 1.22 times as fast in the geometric mean
+// (of 1.23 with the better of the two on every block); at 1.0 times it is slower by more than 3 % on 78.
+static bool tile_is_faster(prom::TileArgs &a, bool prelu, double planes_cost, size_t &lds, int &grid)
+{
+    // (no kernel has more than 64 channels in or out: spare the planning)
+    if (a.cin > 64 || a.cout > 64 || !prom::plan_tile(a, prelu, lds, grid)) return false;
+#ifdef PROM_TIMELINE
+    if (getenv("PROM_TILE")) return true;
+#endif
+    double other;
+    if (planes_cost > 0) {
+        const double c = planes_cost / 2400.0;
+        other = prelu ? 1.85 + 0.928 * c : 2.62 + 0.751 * c;
+    } else {
+        // 56x56x144 at batch 128 68 us (250 MB through memory), 112x112x96 stride 2 91 us (420 MB)
+        const double px = (double)a.N * a.H * a.W, pxo = (double)a.N * a.Ho * a.Wo;
+        other = 12.0 + (px * (a.cin + 2.0 * a.chid) + pxo * (2.0 * a.chid + a.cout)) / 5.0e6;
+    }
+    return a.us < 0.9 * other;
+}
+
+// What PROM_BLOCK_AUTO runs a shape as, when every pointer is aligned: the plan of one of the two kernels, or neither.
+struct BlockPlan {
+    int key[8] = {};  // n, h, w, cin, chid, cout, stride, prelu (n = 0: empty)
+    bool tile = false, planes = false;
+    prom::TileArgs ta;
+    prom::PlanesArgs pa;
+    size_t lds = 0;
+    int grid = 0, kse = 0;
+};
+
+// Planning prices every kernel and split (4 us of host time a call); a program's blocks come again and again, so each
+// thread keeps the plans of the last shapes it met, by their sizes alone.
+static const BlockPlan &block_plan(int n, int h, int w, int cin, int chid, int cout, int stride, bool prelu)
+{
+    constexpr unsigned kSlots = 32;
+    thread_local BlockPlan slots[kSlots];
+    const int key[8] = {n, h, w, cin, chid, cout, stride, prelu};
+    unsigned hash = 0;
+    for (int k : key) hash = (hash ^ (unsigned)k) * 2654435761u;
+    BlockPlan &p = slots[(hash >> 16) % kSlots];
+#ifndef PROM_TIMELINE
+    if (memcmp(p.key, key, sizeof(key)) == 0) return p;
+#endif
+    p.pa = {};
+    p.ta = {};
+    p.pa.N = p.ta.N = n; p.pa.H = p.ta.H = h; p.pa.W = p.ta.W = w;
+    p.pa.Ho = p.ta.Ho = (h - 1) / stride + 1; p.pa.Wo = p.ta.Wo = (w - 1) / stride + 1;
+    p.pa.cin = p.ta.cin = cin; p.pa.chid = p.ta.chid = chid; p.pa.cout = p.ta.cout = cout; p.pa.stride = p.ta.stride = stride;
+    p.planes = prom::plan_planes(p.pa, p.lds, p.grid, p.kse) && planes_is_faster(n, h, w, cin, chid, cout, stride);
+    size_t lds = 0;
+    int grid = 0;
+    p.tile = tile_is_faster(p.ta, prelu, p.planes ? p.pa.cost : 0.0, lds, grid);
+    if (p.tile) {
+        p.planes = false;
+        p.lds = lds;
+        p.grid = grid;
+    }
+    memcpy(p.key, key, sizeof(key));
+    return p;
+}
+
 static bool dwproj_is_faster(int n, int h, int w, int chid, int cout, int stride)
 {
     (void)n; (void)h; (void)w; (void)chid; (void)cout; (void)stride;
@@ -481,6 +549,15 @@ extern "C" int prom_block_is_fused(int n, int h, int w, int cin, int chid, int c
     if (planes < 0) return planes;
     if (planes == 1 && planes_is_faster(n, h, w, cin, chid, cout, stride)) return 1;
     return fused_query(n, h, w, cin, chid, cout, stride, false);
+}
+
+extern "C" int prom_block_tile_applies(int n, int h, int w, int cin, int chid, int cout, int stride, int prelu)
+{
+    using namespace prom;
+    const int planes = prom_block_planes_applies(n, h, w, cin, chid, cout, stride);
+    if (planes < 0) return planes;
+    const BlockPlan &p = block_plan(n, h, w, cin, chid, cout, stride, prelu != 0);
+    return p.tile ? 1 + p.ta.inst : 0;
 }
 
 extern "C" int prom_block_can_fuse(int n, int h, int w, int cin, int chid, int cout, int stride)
@@ -565,27 +642,44 @@ extern "C" int prom_block_ex(const int8_t *x, int n, int h, int w, int cin, int 
     a.lo_d = rq_dw->act_min; a.hi_d = rq_dw->act_max;
     a.lo_p = rq_project->act_min; a.hi_p = rq_project->act_max;
     if (path == PROM_BLOCK_PLANES || path == PROM_BLOCK_AUTO) {
-        // one kernel, the expanded band resident in LDS as 16-channel planes
-        PlanesArgs pa = {};
-        pa.x = x; pa.y = y;
-        pa.we = a.we; pa.wd = a.wd; pa.wp = a.wp;
-        pa.be = a.be; pa.me = a.me; pa.se = a.se;
-        pa.bd = a.bd; pa.md = a.md; pa.sd = a.sd;
-        pa.bp = a.bp; pa.mp = a.mp; pa.sp = a.sp;
-        pa.ne = a.ne; pa.nd = a.nd; pa.np = a.np;
-        pa.N = n; pa.H = h; pa.W = w; pa.Ho = ho; pa.Wo = wo;
-        pa.cin = cin; pa.chid = chid; pa.cout = cout; pa.stride = stride;
-        pa.add_res = add_residual;
-        pa.lo_e = a.lo_e; pa.hi_e = a.hi_e; pa.lo_d = a.lo_d; pa.hi_d = a.hi_d; pa.lo_p = a.lo_p; pa.hi_p = a.hi_p;
-        size_t plds = 0;
-        int pgrid = 0, kse = 0;
-        // (the per-channel arrays of the first two layers are read four channels at a time)
-        uintptr_t par_bits = (uintptr_t)pa.be | (uintptr_t)pa.me | (uintptr_t)pa.se | (uintptr_t)pa.bd |
-                             (uintptr_t)pa.md | (uintptr_t)pa.sd | (uintptr_t)pa.ne | (uintptr_t)pa.nd;
-        const bool ok = aligned && (par_bits & 15) == 0 && plan_planes(pa, plds, pgrid, kse) &&
-                        (path == PROM_BLOCK_PLANES || planes_is_faster(n, h, w, cin, chid, cout, stride));
-        if (path == PROM_BLOCK_PLANES && !ok) return PROM_EUNSUPPORTED;
-        if (ok) return launch_planes(pa, plds, pgrid, kse, stream);
+        // one kernel: wavefronts that own pixel tiles, or the expanded band resident in LDS as 16-channel planes
+        auto fill = [&](auto &k) {
+            k.x = x; k.y = y;
+            k.we = a.we; k.wd = a.wd; k.wp = a.wp;
+            k.be = a.be; k.me = a.me; k.se = a.se;
+            k.bd = a.bd; k.md = a.md; k.sd = a.sd;
+            k.bp = a.bp; k.mp = a.mp; k.sp = a.sp;
+            k.ne = a.ne; k.nd = a.nd; k.np = a.np;
+            k.N = n; k.H = h; k.W = w; k.Ho = ho; k.Wo = wo;
+            k.cin = cin; k.chid = chid; k.cout = cout; k.stride = stride;
+            k.add_res = add_residual;
+            k.lo_e = a.lo_e; k.hi_e = a.hi_e; k.lo_d = a.lo_d; k.hi_d = a.hi_d; k.lo_p = a.lo_p; k.hi_p = a.hi_p;
+        };
+        // (the plane-resident kernel reads the per-channel arrays of the first two layers four channels at a time)
+        const uintptr_t par_bits = (uintptr_t)a.be | (uintptr_t)a.me | (uintptr_t)a.se | (uintptr_t)a.bd |
+                                   (uintptr_t)a.md | (uintptr_t)a.sd | (uintptr_t)a.ne | (uintptr_t)a.nd;
+        const bool ok = aligned && (par_bits & 15) == 0;
+        if (path == PROM_BLOCK_PLANES) {
+            PlanesArgs pa = {};
+            fill(pa);
+            size_t plds = 0;
+            int pgrid = 0, kse = 0;
+            if (!ok || !plan_planes(pa, plds, pgrid, kse)) return PROM_EUNSUPPORTED;
+            return launch_planes(pa, plds, pgrid, kse, stream);
+        }
+        if (aligned) {
+            const BlockPlan &p = block_plan(n, h, w, cin, chid, cout, stride, a.ne || a.nd);
+            if (p.tile) {
+                TileArgs ta = p.ta;
+                fill(ta);
+                return launch_tile(ta, p.lds, p.grid, stream);
+            }
+            if (p.planes && ok) {
+                PlanesArgs pa = p.pa;
+                fill(pa);
+                return launch_planes(pa, p.lds, p.grid, p.kse, stream);
+            }
+        }
     }
     BlockFn fn = nullptr;
     size_t lds = 0;

@@ -20,6 +20,7 @@ struct PlanesArgs {
     int R, bands, RI;  // output rows per band, bands per image, plane rows = (R-1)*stride + 3
     int add_res;
     int lo_e, hi_e, lo_d, hi_d, lo_p, hi_p;
+    double cost;        // the planner's estimate, in clocks
     int NW;             // wavefronts per workgroup: 8, 12 or 16
     int NP, COT;        // 16-channel planes of the hidden tensor, 16-channel tiles of the output
     int KWe, KWp, KS3;  // packed words per expand / project weight row, k steps of the projection

@@ -618,6 +618,7 @@ bool plan_planes(PlanesArgs &a, size_t &lds, int &grid, int &kse)
     if (best.nw == 0) return false;
     const int R = best.R, G = best.G, nw = best.nw;
     a.NW = nw;
+    a.cost = best.cost;
     a.R = R;
     a.RI = (R - 1) * s + 3;
     a.bands = (a.Ho + R - 1) / R;
@@ -710,6 +711,14 @@ int launch_planes(const PlanesArgs &a, size_t lds, int grid, int kse, void *stre
 }  // namespace prom
 
 #ifdef PROM_TIMELINE
+extern "C" double prom_debug_planes_cost(int n, int h, int w, int cin, int chid, int cout, int stride)
+{
+    prom::PlanesArgs a = {};
+    a.N = n; a.H = h; a.W = w; a.Ho = (h - 1) / stride + 1; a.Wo = (w - 1) / stride + 1;
+    a.cin = cin; a.chid = chid; a.cout = cout; a.stride = stride;
+    size_t lds = 0; int grid = 0, kse = 0;
+    return prom::plan_planes(a, lds, grid, kse) ? a.cost : -1.0;
+}
 extern "C" int prom_debug_pl_stamps(unsigned long long *host)
 {
     if (hipDeviceSynchronize() != hipSuccess) return PROM_EHIP;

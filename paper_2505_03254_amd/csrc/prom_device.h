@@ -146,8 +146,9 @@ __host__ __device__ constexpr int pair_shift_less(int form) { return form == kPa
 
 // a0, a1: the accumulators of two pixels, four channels each; par: the channels' parameters as
 // requant_params made them, the shifts reduced by pair_shift_less(FORM); out0, out1: the packed outputs.
-// BIASED: the bias of a PReLU layer is in the accumulators already.
-template <int FORM, bool BIASED = false>
+// BIASED: the bias of a PReLU layer is in the accumulators already.  MASKED = false: with kPairRelu the top bit of
+// every byte is left undefined, for a caller that masks the outputs anyway.
+template <int FORM, bool BIASED = false, bool MASKED = true>
 __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, const v4i (&par)[4], int lo, int hi,
                                               uint32_t &out0, uint32_t &out1)
 {
@@ -206,8 +207,12 @@ __device__ __forceinline__ void requant_pair4(const v4i &a0, const v4i &a1, cons
         out0 = __builtin_amdgcn_perm(cd, ab, 0x05040100u);
         out1 = __builtin_amdgcn_perm(cd, ab, 0x07060302u);
         if constexpr (FORM == kPairRelu) {
-            out0 = (out0 >> 1) & 0x7f7f7f7fu;
-            out1 = (out1 >> 1) & 0x7f7f7f7fu;
+            out0 >>= 1;
+            out1 >>= 1;
+            if constexpr (MASKED) {
+                out0 &= 0x7f7f7f7fu;
+                out1 &= 0x7f7f7f7fu;
+            }
         }
     }
 }
