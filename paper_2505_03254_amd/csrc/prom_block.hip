@@ -452,26 +452,26 @@ static bool planes_is_faster(int n, int h, int w, int cin, int chid, int cout, i
 
 // Whether PROM_BLOCK_AUTO takes the kernel of pixel tiles (plan in `a`), by two estimates in microseconds: its planner's
 // and that of what it would replace -- the plane-resident kernel (planes_cost > 0, that planner's clocks; fitted to the
-// measured times of 989 blocks, error 5 %) or three launches.  At 0.9 times, over 1104 blocks of batch 1 to 256 on maps
-// of 26 to 115, it is slower than what it replaces by more than 3 % on one, and 1.22 times as fast in the geometric mean
-// (of 1.23 with the better of the two on every block); at 1.0 times it is slower by more than 3 % on 78.
+// measured times of 937 blocks, error 5 %) or three launches.  At 0.9 times, over 1029 blocks of batch 1 to 256 on maps
+// of 11 to 115, it is slower than what it replaces by more than 3 % on two, at 0.95 on 8, at 1.0 on 37; the geometric mean
+// is 1.19 times as fast in all three (1.20 with the better of the two on every block).
 static bool tile_is_faster(prom::TileArgs &a, bool prelu, double planes_cost, size_t &lds, int &grid)
 {
     // (no kernel has more than 64 channels in or out: spare the planning)
     if (a.cin > 64 || a.cout > 64 || !prom::plan_tile(a, prelu, lds, grid)) return false;
-#ifdef PROM_TIMELINE
+#ifdef PROM_PLAN_ENV
     if (getenv("PROM_TILE")) return true;
 #endif
     double other;
     if (planes_cost > 0) {
         const double c = planes_cost / 2400.0;
-        other = prelu ? 1.85 + 0.928 * c : 2.62 + 0.751 * c;
+        other = prelu ? 1.36 + 0.838 * c : 2.13 + 0.691 * c;
     } else {
         // 56x56x144 at batch 128 68 us (250 MB through memory), 112x112x96 stride 2 91 us (420 MB)
         const double px = (double)a.N * a.H * a.W, pxo = (double)a.N * a.Ho * a.Wo;
         other = 12.0 + (px * (a.cin + 2.0 * a.chid) + pxo * (2.0 * a.chid + a.cout)) / 5.0e6;
     }
-    return a.us < 0.9 * other;
+    return a.us < 0.92 * other;
 }
 
 // What PROM_BLOCK_AUTO runs a shape as, when every pointer is aligned: the plan of one of the two kernels, or neither.
@@ -494,7 +494,7 @@ static const BlockPlan &block_plan(int n, int h, int w, int cin, int chid, int c
     unsigned hash = 0;
     for (int k : key) hash = (hash ^ (unsigned)k) * 2654435761u;
     BlockPlan &p = slots[(hash >> 16) % kSlots];
-#ifndef PROM_TIMELINE
+#ifndef PROM_PLAN_ENV
     if (memcmp(p.key, key, sizeof(key)) == 0) return p;
 #endif
     p.pa = {};

@@ -29,6 +29,8 @@ struct PlanesArgs {
     int G3, TPG3;       // phase 3: pixel-tile groups per output tile, pixel tiles per group (1, 2, 4 or 8)
     int slot1, slot2;   // bytes between expansion planes / between depthwise-output planes
     int S3;             // words between rows of the projection's packed codes in LDS
+    uint32_t by_w, by_wo, by_xp, by_kq;  // division by W, Wo, 8-byte pieces of a pixel, pieces of a code row (fast_div)
+    int off_par;        // the first two layers' parameters, made once per channel; 0: LDS has no room, each unit makes its own
     int off_o1, off_o2, off_pp, off_w3, off_wd, off_t1, off_t2;  // LDS byte offsets
 };
 

@@ -27,6 +27,13 @@
 // the hidden tensor takes (planes + 8) slots in all; with fewer planes the pixel tiles of a plane
 // are spread over wavefronts, there is a barrier between phases 1 and 2 and the depthwise output
 // has a region of its own.
+//
+// On few images the kernel is bound by the instructions around the tiles -- 16 wavefronts make one cost 16 clocks --, so:
+// the parameters of the first two layers are made once per channel and kept in LDS where it has room (PARL; each unit
+// made its own, 60 instructions, 16 lanes the same), index tables and copies divide by multiplication, and the
+// prologue's loops of one or two rounds are not unrolled (up to 1.5 us).  Measured at batch 8, replayed from a graph, before and
+// after: 7x7 160-960-160 15.5 -> 13.5 us, 14x14 64-384-64 8.5 -> 7.8, with PReLU 16.8 -> 14.6 and 9.8 -> 8.5; batch 128
+// 18.9 -> 17.1 and 13.4 -> 12.7; 28x28 32-192-64 stride 2 16.6 -> 14.5.
 #include "prom_pw_stream.h"
 #include "prom_launch.h"
 #include "prom_block_planes.h"
@@ -50,13 +57,23 @@ __device__ unsigned long long g_pl_stamps[256 * 8];
 // Epilogue forms (requant_pair4) and tile counts as types.
 template <int MODE> struct PlMode { static constexpr int value = MODE; };
 
+// n / d by multiplication with ceil(2^32 / d): right for n * d < 2^32.  A divisor of 1 has none.
+static inline uint32_t div_magic(int d) { return d > 1 ? (uint32_t)(((1ull << 32) + d - 1) / d) : 0u; }
+// mul24: a product of numbers below 2^24.  (A full 32-bit product with a sum becomes v_mad_u64_u32, whose addend is a
+// register pair; its unused upper half may be where a load in flight will land, and the prologue then waits 1 us for it.)
+__device__ __forceinline__ int mul24(int x, int y) { return (int)__umul24((unsigned)x, (unsigned)y); }
+__device__ __forceinline__ int fast_div(int n, uint32_t magic) { return magic == 0 ? n : (int)__umulhi((uint32_t)n, magic); }
+
 // Bias, multiplier(s) and shift of a lane's four channels (16*plane + 4*g + 0..3) as loaded.
 struct PlRawPar { v4i b, m, n, s; };
 
 // KSE: 64-wide k steps of the expansion (cin <= 64*KSE).  PRELU: the expansion and depthwise
 // epilogues take the PReLU form (a layer of the two without negative-side multipliers runs it with
 // mult_neg = mult, which is the plain form).
-template <int KSE, bool PRELU, int NW>
+// PARL: the parameters of the first two layers are made once per channel and kept in LDS (where it has room); otherwise
+// each unit of work makes its own, 16 lanes the same.  (A template parameter: a choice at run time puts the prologue's
+// loads under a branch, which costs a wait for those in flight, 1 us.)
+template <int KSE, bool PRELU, int NW, bool PARL>
 __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesArgs a)
 {
     constexpr int kPlWaves = NW, kPlThreads = 64 * NW;
@@ -132,8 +149,7 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
         r.b = *reinterpret_cast<const v4i *>(B + c);
         r.m = *reinterpret_cast<const v4i *>(M + c);
         r.s = *reinterpret_cast<const v4i *>(S + c);
-        if (PRELU && Nn) r.n = *reinterpret_cast<const v4i *>(Nn + c);
-        else r.n = r.m;
+        if (PRELU) r.n = *reinterpret_cast<const v4i *>((Nn ? Nn : M) + c);
     };
     auto make_par = [&](const PlRawPar &r, v4i(&par)[4]) __attribute__((always_inline)) {
 #pragma unroll
@@ -141,12 +157,21 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
     };
     uint32_t w1n[KSE];
     PlRawPar rawe, rawd;
-    {
-        const int u = min(wave, units1 - 1);
-        load_w1(u, w1n);
+    v4i *parl = reinterpret_cast<v4i *>(lds + a.off_par);  // [2][chid] parameters of the expansion, of the depthwise layer
+    load_w1(min(wave, units1 - 1), w1n);
+    int qe[4], qd[4];  // a channel of the two layers
+    auto load_q = [&](const unsigned c) __attribute__((always_inline)) {
+        // (one of two pointers, not a load under a condition: that waits for every load in flight)
+        const int32_t *ne = PRELU && a.ne ? a.ne : a.me, *nd = PRELU && a.nd ? a.nd : a.md;
+        qe[0] = a.be[c]; qe[1] = a.me[c]; qe[2] = ne[c]; qe[3] = a.se[c];
+        qd[0] = a.bd[c]; qd[1] = a.md[c]; qd[2] = nd[c]; qd[3] = a.sd[c];
+    };
+    if constexpr (!PARL) {
+        const int u = min(wave, units1 - 1), u2 = min(wave, units2 - 1);
         load_par(a.be, a.me, a.ne, a.se, G1 == 1 ? u : u / G1, rawe);
-        const int u2 = min(wave, units2 - 1);
         load_par(a.bd, a.md, a.nd, a.sd, G2 == 1 ? u2 : u2 / G2, rawd);
+    } else {
+        load_q(min(tid, chid - 1));
     }
     // the projection's parameters: one channel per thread
     int pbp, pmp, pnp, psp;
@@ -162,33 +187,38 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
     uint32_t wdv[NWD];
 #pragma unroll
     for (int q = 0; q < NWD; ++q) wdv[q] = wd4[min(tid + q * kPlThreads, nwd - 1)];
+    asm volatile("" ::: "memory");
 
     {
+        // (loops of one or two rounds: unrolled by the compiler they cost the prologue 4 KB of code and up to 1.5 us)
         // (pixels beyond the band land in a spare cell behind the plane's rows)
+#pragma clang loop unroll(disable) vectorize(disable)
         for (int p = tid; p < nt1 * 16; p += kPlThreads) {
-            const int row = p / W, col = p - row * W;
-            o1[p] = (uint16_t)(p < np1 ? (rv0 + row) * W2 + col + 1 : a.RI * W2);
+            const int row = fast_div(p, a.by_w), col = p - mul24(row, W);
+            o1[p] = (uint16_t)(p < np1 ? mul24(rv0 + row, W2) + col + 1 : a.RI * W2);
         }
+#pragma clang loop unroll(disable) vectorize(disable)
         for (int p = tid; p < nt2 * 16; p += kPlThreads) {
             const int pc = min(p, np2 - 1);
-            const int oy = pc / Wo, ox = pc - oy * Wo;
-            o2[p] = (uint16_t)((oy * s) * W2 + ox * s);
+            const int oy = fast_div(pc, a.by_wo), ox = pc - mul24(oy, Wo);
+            o2[p] = (uint16_t)(mul24(oy * s, W2) + ox * s);
         }
         // zero cells of the expansion planes: the two border columns of every row in use and the
         // rows outside the image
         const int ninv = rib - nvr;
         const int per = 2 * rib + ninv * W;
         const v4i zero4 = {0, 0, 0, 0};
+#pragma clang loop unroll(disable) vectorize(disable)
         for (int e = tid; e < per; e += kPlThreads) {
             int cell;
             if (e < 2 * rib) {
-                cell = (e >> 1) * W2 + ((e & 1) ? W + 1 : 0);
+                cell = mul24(e >> 1, W2) + ((e & 1) ? W + 1 : 0);
             } else {
                 const int q = e - 2 * rib;
-                const int ir = q / W, col = q - ir * W;
+                const int ir = fast_div(q, a.by_w), col = q - mul24(ir, W);
                 // invalid rows: those before rv0, then those from rv0 + nvr on
                 const int row = ir < rv0 ? ir : ir + nvr;
-                cell = row * W2 + col + 1;
+                cell = mul24(row, W2) + col + 1;
             }
             unsigned char *dst = t1 + cell * 16;
             for (int pl = 0; pl < NP; ++pl) *reinterpret_cast<v4i *>(dst + pl * slot1) = zero4;
@@ -200,15 +230,24 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
         for (int q = 0; q < NX; ++q) {
             const int pc = tid + q * kPlThreads;
             if (pc * 8 < xtotal) {
-                const int px = pc / pieces;
-                *reinterpret_cast<v2i *>(xs + px * cinp + 8 * (pc - px * pieces)) = xv[q];
+                const int px = fast_div(pc, a.by_xp);
+                *reinterpret_cast<v2i *>(xs + mul24(px, cinp) + 8 * (pc - mul24(px, pieces))) = xv[q];
             }
         }
+#pragma clang loop unroll(disable) vectorize(disable)
         for (int o = (tid + NX * kPlThreads) * 8; o < xtotal; o += kPlThreads * 8) {
             const v2i v = __builtin_amdgcn_raw_buffer_load_b64(rx, xbase + o, 0, 0);
             const int pc = o >> 3;
-            const int px = pc / pieces;
-            *reinterpret_cast<v2i *>(xs + px * cinp + 8 * (pc - px * pieces)) = v;
+            const int px = fast_div(pc, a.by_xp);
+            *reinterpret_cast<v2i *>(xs + mul24(px, cinp) + 8 * (pc - mul24(px, pieces))) = v;
+        }
+        if constexpr (PARL) {
+#pragma clang loop unroll(disable) vectorize(disable)
+            for (int c = tid; c < chid; c += kPlThreads) {
+                if (c != tid) load_q(c);
+                parl[c] = requant_params(qe[0], qe[1], qe[2], qe[3], PRELU);
+                parl[chid + c] = requant_params(qd[0], qd[1], qd[2], qd[3], PRELU);
+            }
         }
         if (tid < 16 * a.COT) pp[tid] = tid < cout ? requant_params(pbp, pmp, pnp, psp, prelu_p) : v4i{0, 0, 0, 1};
 #pragma unroll
@@ -216,6 +255,7 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
             const int i = tid + q * kPlThreads;
             if (i < nwd) reinterpret_cast<uint32_t *>(wdl)[i] = wdv[q];
         }
+#pragma clang loop unroll(disable) vectorize(disable)
         for (int i = tid + NWD * kPlThreads; i < nwd; i += kPlThreads) reinterpret_cast<uint32_t *>(wdl)[i] = wd4[i];
     }
     __syncthreads();
@@ -232,14 +272,19 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
             v4i A[KSE];
 #pragma unroll
             for (int ks = 0; ks < KSE; ++ks) A[ks] = decode_word(w1n[ks]);
-            v4i par[4];
-            make_par(rawe, par);
             const int pl = G1 == 1 ? u : u / G1;
             const int grp = u - pl * G1;
+            v4i par[4];
+            if constexpr (!PARL) {
+                make_par(rawe, par);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) par[r] = parl[16 * pl + 4 * g + r];
+            }
             {   // the next unit's codes and parameters fly during this one
                 const int un = min(u + kPlWaves, units1 - 1);
                 load_w1(un, w1n);
-                load_par(a.be, a.me, a.ne, a.se, G1 == 1 ? un : un / G1, rawe);
+                if constexpr (!PARL) load_par(a.be, a.me, a.ne, a.se, G1 == 1 ? un : un / G1, rawe);
             }
             unsigned char *t1p = t1 + pl * slot1 + 4 * g;
             const int pt0 = grp * tpg, pt1 = min((grp + 1) * tpg, nt1);
@@ -312,6 +357,7 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
 #pragma unroll
         for (int q = 0; q < NW3; ++q) w3v[q][0] = (int)a.wp[min(tid + q * kPlThreads, n3 - 1)];
     }
+    asm volatile("" ::: "memory");  // (the loads leave here; where registers are short they would sink below the filter)
 
     // ---- phase 2: depthwise 3x3 of the owned planes on the matrix cores ------------------------------
     {
@@ -332,14 +378,17 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
 #pragma unroll
             for (int q = 0; q < 3; ++q) {
                 const int tap = 4 * q + g;
-                const uint32_t wb = tap < 9 ? (uint32_t)(uint8_t)wdl[tap * chid + 16 * pl + li] : 0u;
+                const uint32_t wb = tap < 9 ? (uint32_t)(uint8_t)wdl[mul24(tap, chid) + 16 * pl + li] : 0u;
                 const uint32_t val = wb << (8 * (li & 3));
                 adw[q] = v4i{(li >> 2) == 0 ? (int)val : 0, (li >> 2) == 1 ? (int)val : 0,
                              (li >> 2) == 2 ? (int)val : 0, (li >> 2) == 3 ? (int)val : 0};
             }
             v4i par[4];
-            make_par(rawd, par);
-            {
+            if constexpr (PARL) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) par[r] = parl[chid + 16 * pl + 4 * g + r];
+            } else {
+                make_par(rawd, par);
                 const int un = min(u + kPlWaves, units2 - 1);
                 load_par(a.bd, a.md, a.nd, a.sd, G2 == 1 ? un : un / G2, rawd);
             }
@@ -398,28 +447,31 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
         for (int q = 0; q < NW3; ++q) {
             const int i = tid + q * kPlThreads;
             if (i < n3) {
-                const int row = i / kq3;
-                *reinterpret_cast<v4i *>(w3l + row * S3 + 4 * (i - row * kq3)) = w3v[q];
+                const int row = fast_div(i, a.by_kq);
+                *reinterpret_cast<v4i *>(w3l + mul24(row, S3) + 4 * (i - mul24(row, kq3))) = w3v[q];
             }
         }
+#pragma clang loop unroll(disable) vectorize(disable)
         for (int i = tid + NW3 * kPlThreads; i < n3; i += kPlThreads) {
-            const int row = i / kq3;
-            *reinterpret_cast<v4i *>(w3l + row * S3 + 4 * (i - row * kq3)) = *reinterpret_cast<const v4i *>(a.wp + 4 * (long long)i);
+            const int row = fast_div(i, a.by_kq);
+            *reinterpret_cast<v4i *>(w3l + mul24(row, S3) + 4 * (i - mul24(row, kq3))) = *reinterpret_cast<const v4i *>(a.wp + 4 * (long long)i);
         }
     } else {
 #pragma unroll
         for (int q = 0; q < NW3; ++q) {
             const int i = tid + q * kPlThreads;
             if (i < n3) {
-                const int row = i / KWp;
-                w3l[row * S3 + (i - row * KWp)] = (uint32_t)w3v[q][0];
+                const int row = fast_div(i, a.by_kq);
+                w3l[mul24(row, S3) + (i - mul24(row, KWp))] = (uint32_t)w3v[q][0];
             }
         }
+#pragma clang loop unroll(disable) vectorize(disable)
         for (int i = tid + NW3 * kPlThreads; i < n3; i += kPlThreads) {
-            const int row = i / KWp;
-            w3l[row * S3 + (i - row * KWp)] = a.wp[i];
+            const int row = fast_div(i, a.by_kq);
+            w3l[mul24(row, S3) + (i - mul24(row, KWp))] = a.wp[i];
         }
         // words between the row's end and the next multiple of four are read as codes: zero
+#pragma clang loop unroll(disable) vectorize(disable)
         for (int r = tid; r < cout; r += kPlThreads)
             for (int w = KWp; w < ((KWp + 3) & ~3); ++w) w3l[r * S3 + w] = 0u;
     }
@@ -448,13 +500,13 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
 #pragma unroll
             for (int i = 0; i < TPG; ++i) acc[i] = zero4;
             const unsigned char *bq = t2 + (pt0 * 16 + j) * 16;
-            const uint32_t *wrow = w3l + (16 * ct + j) * S3;
+            const uint32_t *wrow = w3l + mul24(16 * ct + j, S3);
             // One k step ahead: the B operands of the next step and the codes of the next group are
             // on their way while this step's codes are decoded and its MFMAs issue.  Steps past the
             // last plane read the last plane against zero codes (the rows are zero-padded to R4 and
             // groups past R4 take zeros), the reads past the last step go nowhere.
             auto load_b = [&](v4i(&B)[TPG], int plane) __attribute__((always_inline)) {
-                const unsigned char *bp = bq + min(plane, NP - 1) * slot2;
+                const unsigned char *bp = bq + mul24(min(plane, NP - 1), slot2);
 #pragma unroll
                 for (int i = 0; i < TPG; ++i) B[i] = *reinterpret_cast<const v4i *>(bp + i * 256);
             };
@@ -501,7 +553,7 @@ __global__ __launch_bounds__(64 * NW, 1) void block_planes_kernel(const PlanesAr
                         if (a.add_res) {
                             // stride 1 and cin == cout: the block input at the same pixel, still in LDS
                             const uint32_t res = *reinterpret_cast<const uint32_t *>(
-                                xs + ((1 - rv0) * W + min(p, np2 - 1)) * cinp + (cok ? c : 0));
+                                xs + mul24((1 - rv0) * W + min(p, np2 - 1), cinp) + (cok ? c : 0));
                             q[k] = add_sat_i8x4(q[k], res);
                         }
                         __builtin_amdgcn_raw_buffer_store_b32((int)q[k], ry, cok && p < np2 ? (obase + p) * cout + c : kOobOffset, 0, 0);
@@ -628,6 +680,9 @@ bool plan_planes(PlanesArgs &a, size_t &lds, int &grid, int &kse)
     a.KWp = KWp;
     a.KS3 = KS3;
     a.cinp = cinp;
+    a.by_w = div_magic(a.W);
+    a.by_wo = div_magic(a.Wo);
+    a.by_xp = div_magic(cin >> 3);
     a.G1 = a.G2 = G;
     a.G3 = best.G3;
     a.TPG3 = best.TPG3;
@@ -653,6 +708,11 @@ bool plan_planes(PlanesArgs &a, size_t &lds, int &grid, int &kse)
         a.off_t1 = off; off += NP * plane1;
         a.off_t2 = off; off += NP * plane2;
     }
+    a.off_par = 0;
+    if (off + 2 * chid * 16 + 2048 <= kLdsMax) {
+        a.off_par = off;
+        off += 2 * chid * 16;
+    }
     off += 2048;  // phase 3 reads up to 8 pixel tiles from a unit's first one, whatever the band holds
     lds = (size_t)off;
     const long long gsz = (long long)a.N * a.bands;
@@ -661,23 +721,25 @@ bool plan_planes(PlanesArgs &a, size_t &lds, int &grid, int &kse)
     return true;
 }
 
-template <int NW> static PlanesFn planes_fn_nw(int kse, bool prelu)
+template <int NW, bool PARL> static PlanesFn planes_fn_nw(int kse, bool prelu)
 {
     switch (kse) {
-    case 1: return prelu ? &block_planes_kernel<1, true, NW> : &block_planes_kernel<1, false, NW>;
-    case 2: return prelu ? &block_planes_kernel<2, true, NW> : &block_planes_kernel<2, false, NW>;
-    default: return prelu ? &block_planes_kernel<3, true, NW> : &block_planes_kernel<3, false, NW>;
+    case 1: return prelu ? &block_planes_kernel<1, true, NW, PARL> : &block_planes_kernel<1, false, NW, PARL>;
+    case 2: return prelu ? &block_planes_kernel<2, true, NW, PARL> : &block_planes_kernel<2, false, NW, PARL>;
+    default: return prelu ? &block_planes_kernel<3, true, NW, PARL> : &block_planes_kernel<3, false, NW, PARL>;
     }
 }
-static PlanesFn planes_fn(int kse, bool prelu, int nw)
+template <bool PARL> static PlanesFn planes_fn(int kse, bool prelu, int nw)
 {
-    return nw == 16 ? planes_fn_nw<16>(kse, prelu) : nw == 12 ? planes_fn_nw<12>(kse, prelu) : planes_fn_nw<8>(kse, prelu);
+    return nw == 16   ? planes_fn_nw<16, PARL>(kse, prelu)
+           : nw == 12 ? planes_fn_nw<12, PARL>(kse, prelu)
+                      : planes_fn_nw<8, PARL>(kse, prelu);
 }
 
 int launch_planes(const PlanesArgs &a, size_t lds, int grid, int kse, void *stream)
 {
     const bool prelu = a.ne != nullptr || a.nd != nullptr;
-    const PlanesFn fn = planes_fn(kse, prelu, a.NW);
+    const PlanesFn fn = a.off_par ? planes_fn<true>(kse, prelu, a.NW) : planes_fn<false>(kse, prelu, a.NW);
     static std::mutex mu;
     static std::vector<PlanesFn> attr_done;
     {
@@ -697,6 +759,7 @@ int launch_planes(const PlanesArgs &a, size_t lds, int grid, int kse, void *stre
     }
     clear_hip_error();
     PlanesArgs args = a;
+    args.by_kq = div_magic((a.KWp & 3) == 0 && ((uintptr_t)a.wp & 15) == 0 ? a.KWp >> 2 : a.KWp);  // (w3wide in the kernel)
     void *kargs[] = {&args};
     const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(fn), dim3(grid), dim3(64 * a.NW), kargs, lds,
                                          static_cast<hipStream_t>(stream));

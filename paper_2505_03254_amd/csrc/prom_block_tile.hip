@@ -207,6 +207,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void block_tile_kernel(const TileA
         if (tile < a.n_tiles) setup(tile);
         // ---- which forms of the requantisation the layers' shifts allow: each wavefront looks at the ones it holds
         int smin = 31;
+#pragma clang loop unroll(disable)
         for (int c = tid; c < chid; c += nthr) {
             const bool own = c == tid;
             smin = min(smin, own ? min(par.e[3], par.d[3]) : min(a.se[c], a.sd[c]));
@@ -250,6 +251,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void block_tile_kernel(const TileA
         if (tid < 8 * NQ) store_d(tid, wd);
         // what is left of wider blocks, four loads in flight
         constexpr int V = 4;
+#pragma clang loop unroll(disable)
         for (int e0 = tid + U * nthr; e0 < ne; e0 += V * nthr) {
             uint32_t w[V];
 #pragma unroll
@@ -258,6 +260,7 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void block_tile_kernel(const TileA
             for (int u = 0; u < V; ++u)
                 if (e0 + u * nthr < ne) fe[e0 + u * nthr] = decode_word(w[u]);
         }
+#pragma clang loop unroll(disable)
         for (int e0 = tid + U * nthr; e0 < npj; e0 += V * nthr) {
             uint32_t w[V][2];
 #pragma unroll
@@ -266,10 +269,12 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void block_tile_kernel(const TileA
             for (int u = 0; u < V; ++u)
                 if (e0 + u * nthr < npj) store_p(e0 + u * nthr, w[u]);
         }
+#pragma clang loop unroll(disable)
         for (int c = tid + nthr; c < 8 * NQ; c += nthr) {
             load_d(c, wd);
             store_d(c, wd);
         }
+#pragma clang loop unroll(disable)
         for (int c = tid + nthr; c < npar; c += nthr) store_par(c, load_par(c));
     }
     if (form == kPairRelu) {
@@ -537,9 +542,9 @@ static const TileInst kTileInst[] = {
 //
 // Every kernel, S and T is priced in microseconds.  A plane of a wavefront's tile takes the longer of its own chain
 // (lat) and, with k wavefronts on a SIMD, k times the instructions it issues (thr); both grow with the 16-pixel tiles
-// of the expansion and the filter.  Constants: least squares over 65000 plans of 1104 blocks (batch 1 to 256, maps of
-// 26 to 115, up to 64 channels in and out, with and without PReLU), error 10 %; the plan it picks is 2 % behind the
-// best one on average, 14 % at most.
+// of the expansion and the filter.  Constants: least squares over 62771 plans of 1029 blocks (batch 1 to 256, maps of
+// 11 to 115, up to 64 channels in and out, with and without PReLU), error 10 %; the plan it picks is 1.7 % behind the
+// best one on average, 15 % at most.
 bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
 {
     const int s = a.stride;
@@ -552,11 +557,11 @@ bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
     const int TC = s == 1 ? 14 : 7;
     a.cols_n = (a.Wo + TC - 1) / TC;
     int only_inst = -1, only_s = 0, only_t = 0;
-#ifdef PROM_TIMELINE
+#ifdef PROM_PLAN_ENV  // developer build: the plan from the environment
     if (const char *e = getenv("PROM_TILE"))
         if (sscanf(e, "%d,%d,%d", &only_inst, &only_s, &only_t) != 3) return false;
 #endif
-    const double slow = prelu ? 1.6 : 1.0;
+    const double slow = prelu ? 1.62 : 1.0;
     const int np = a.chid / 16;
     double best = 0;
     size_t best_lds = 0;
@@ -576,7 +581,7 @@ bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
         const int off_dw = off_pe + a.NQ * 1024;
         const int off_slot = off_dw + a.NQ * 640;
         const int off_t1 = off_slot + 64;
-        const double lat = (0.124 + 0.031 * (nt1 + nt2)) * slow, thr = (0.069 + 0.0324 * (nt1 + nt2)) * slow;
+        const double lat = (0.102 + 0.0315 * (nt1 + nt2)) * slow, thr = (0.067 + 0.0317 * (nt1 + nt2)) * slow;
         const int fin = nt2 * I.cot;
         for (int S : {1, 2, 3, 4, 6}) {
             if (S > a.NQ || S > I.nw || (only_s && S != only_s)) continue;
@@ -595,16 +600,16 @@ bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
                 const int ne = 2 * a.NQ * 64, npj = a.NQ * I.cot * 64;
                 const int extra = (ne > 2 * thr_wg ? (ne - 2 * thr_wg + 4 * thr_wg - 1) / (4 * thr_wg) : 0) +
                                   (npj > 2 * thr_wg ? (npj - 2 * thr_wg + 4 * thr_wg - 1) / (4 * thr_wg) : 0);
-                const double ent = (double)(ne + npj) / thr_wg, pro = 2.1 + 0.39 * extra;
+                const double ent = (double)(ne + npj) / thr_wg, pro = 1.76 + 0.39 * extra;
                 auto loaded = [](double w) { return w > 1.0 ? w : 1.0; };
                 auto planes = [&](long long k) { return npw * (lat > k * thr ? lat : k * thr); };
-                double us = 2.5;
+                double us = 2.33;
                 if (S == 1) {  // one resident set of workgroups, whose wavefronts walk over the tiles
                     const long long g = wgs < 256 * percu ? wgs : 256 * percu, per = (g + 255) / 256;
-                    us += pro + 0.018 * ent * loaded(per * T / 4.0);
+                    us += pro + 0.026 * ent * loaded(per * T / 4.0);
                     auto round = [&](long long t) {
                         const long long k = (per * t + 3) / 4;
-                        const double e = 1.0 + 0.21 * fin, f = 0.02 * k * fin;
+                        const double e = 0.93 + 0.21 * fin, f = 0.012 * k * fin;
                         return planes(k) + (e > f ? e : f);
                     };
                     const long long full = tiles / (g * T), left = tiles - full * g * T;
@@ -613,8 +618,8 @@ bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
                 } else {  // a workgroup has one round
                     auto round = [&](long long m) {
                         const long long per = (m + 255) / 256, k = (per * S * T + 3) / 4;
-                        const double e = 1.0 + 0.21 * fin / S, f = 0.02 * k * fin / S;
-                        return pro + 0.018 * ent * loaded(per * S * T / 4.0) + planes(k) + (e > f ? e : f) + 0.051 * fin * k;
+                        const double e = 0.93 + 0.21 * fin / S, f = 0.012 * k * fin / S;
+                        return pro + 0.026 * ent * loaded(per * S * T / 4.0) + planes(k) + (e > f ? e : f) + 0.05 * fin * k;
                     };
                     const long long cap = 256 * percu, full = wgs / cap;
                     us += full * round(cap);
