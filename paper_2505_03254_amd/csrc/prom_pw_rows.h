@@ -64,24 +64,18 @@ __device__ __forceinline__ void stage_weights_rows(const PwArgs &a, int cbase, i
             pb[q] = 0; pm[q] = 0; pn[q] = 0; ps[q] = 1;
         }
     }
-    constexpr int U = 8;  // words in flight per thread
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const FragWords<NT> words(a, cbase, tid & 63);
     const unsigned recip = (65536u + (unsigned)KS - 1u) / (unsigned)KS;  // tk / KS == (tk * recip) >> 16 for tk < 1024
-    auto batch = [&](const int base) __attribute__((always_inline)) {
+    auto batch = [&](auto depth, const int base) __attribute__((always_inline)) {
+        constexpr int U = decltype(depth)::value;  // words in flight per thread
         uint32_t word[U];
 #pragma unroll
         for (int q = 0; q < U; ++q) {
-            const int idx = base + q * nthr + tid;
-            const int tk = idx < nfrag ? idx >> 6 : 0;
+            const int tk = min(base / 64 + q * (nthr >> 6) + wave, NTT * KS - 1);  // entry (tile, k step), wave-uniform
             const int tt = (int)(((unsigned)tk * recip) >> 16);
-            const int ks = tk - tt * KS;
             const int cw = tt / NT;
-            const int t = tt - cw * NT;
-            const int i = idx & 15;
-            const int c = cbase + cw * NT * 16 + chan_of<NT>(t, i >> 2, i & 3);
-            const int kw = 4 * ks + ((idx & 63) >> 4);
-            const bool ok = idx < nfrag && c < Nc && kw < a.KW;
-            const uint32_t v = a.wq[ok ? (long long)c * a.KW + kw : 0];
-            word[q] = ok ? v : 0u;
+            word[q] = words.load(cw * NT * 16, tt - cw * NT, tk - tt * KS);
         }
 #pragma unroll
         for (int q = 0; q < U; ++q) {
@@ -89,8 +83,14 @@ __device__ __forceinline__ void stage_weights_rows(const PwArgs &a, int cbase, i
             if (idx < nfrag) frag[idx] = decode_word(word[q]);
         }
     };
-    batch(0);
-    for (int base = nthr * U; base < nfrag; base += nthr * U) batch(base);
+    // (as deep as there are words, see stage_weights)
+    if (nfrag <= 4 * nthr) {
+        batch(Depth<4>{}, 0);
+    } else {
+        batch(Depth<8>{}, 0);
+#pragma clang loop unroll(disable)
+        for (int base = nthr * 8; base < nfrag; base += nthr * 8) batch(Depth<8>{}, base);
+    }
 #pragma unroll
     for (int q = 0; q < PU; ++q) {
         const int s = tid + q * nthr;

@@ -93,6 +93,38 @@ __device__ __forceinline__ v4i decode_word(uint32_t word)
     return f;
 }
 
+// The packed words of the rows from cbase on as a buffer: rows beyond the layer's read zero, and offsets stay far below
+// 2^31 whatever the layer's size (a chunk reads 16 * NT * CW rows of at most 1 KB).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rows(const PwArgs &a, int cbase)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.wq) + (long long)cbase * a.KW, 0,
+                                             min(a.Nc - cbase, 1 << 16) * a.KW * 4, 0x00020000);
+}
+
+// Loads in flight per thread, as a type.
+template <int N> struct Depth { static constexpr int value = N; };
+
+// The packed word of lane (i, kg) of the fragment entry (tile t, k step ks), both wave-uniform, of the group of NT tiles
+// that begins cofs rows behind cbase: zero beyond the layer's rows and words.  Rows and words come out of scalar
+// arithmetic, the lane's part is one product with the size of the tile's group; a load costs a dozen scalar and four
+// vector instructions (35 vector ones with a 64-bit address of its own per lane, and as many scalar ones to step through
+// (t, ks)).
+template <int NT> struct FragWords {
+    __amdgpu_buffer_rsrc_t rsrc;
+    int rows4, rest, kg, KW;
+    __device__ __forceinline__ FragWords(const PwArgs &a, int cbase, int lane)
+        : rsrc(weight_rows(a, cbase)), rows4(16 * ((lane & 15) >> 2) * a.KW),
+          rest((lane & 3) * a.KW * 4 + 4 * (lane >> 4)), kg(lane >> 4), KW(a.KW)
+    {
+    }
+    __device__ __forceinline__ uint32_t load(int cofs, int t, int ks) const
+    {
+        const int first = grp_first<NT>(t), row = cofs + 16 * first + 4 * (t - first);
+        const int off = (int)__umul24((unsigned)rows4, (unsigned)grp_size<NT>(t)) + rest + (row * KW + 4 * ks) * 4;
+        return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rsrc, kg < KW - 4 * ks ? off : 0x7ffff000, 0, 0);
+    }
+};
+
 // Decode the chunk's weights into LDS fragments frag[NT][KS][64 lanes] and the chunk's
 // requantisation parameters into lpar[NT][4 g][4 r] = (C lo, C hi, mult, shift), or
 // (bias, mult, mult_neg, shift) for a PReLU layer.  Ends with the workgroup barrier that
@@ -119,25 +151,36 @@ __device__ __forceinline__ void stage_weights(const PwArgs &a, int cbase, v4i *f
     // 4*ks + kg of the row of channel chan_of(t, i).  The loads of a batch are issued back to back
     // -- the first batch in straight-line code, so that it leaves together with the activation
     // loads issued before this call instead of behind a wait at a loop header -- and decoded as
-    // they arrive.
+    // they arrive.  A first batch is no deeper than there are entries (1, 2 or 4 and 4 or 16 per thread): what is computed
+    // for entries that do not exist is most of a short layer's time (28x28 16 -> 16 at batch 78 7.1 -> 4.3 us).
     const int total = NT * KS;
     if ((a.KW & 3) == 0 && (reinterpret_cast<uintptr_t>(a.wq) & 15) == 0) {
         // Rows of whole 16-byte pieces: a thread fetches the four words of (entry, i) with one
         // load and decodes them for the lanes kg = 0..3 of the entry; 16 threads per entry.
-        constexpr int U = 4;
         const unsigned recip = (65536u + (unsigned)KS - 1u) / (unsigned)KS;  // e / KS == (e * recip) >> 16 for e < 1024
         const int i = tid & 15;
-        auto batch = [&](const int v0) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t rsrc = weight_rows(a, cbase);
+        auto batch = [&](auto depth, const int v0) __attribute__((always_inline)) {
+            constexpr int U = decltype(depth)::value;
             v4i w4[U];
 #pragma unroll
             for (int q = 0; q < U; ++q) {
-                const int e = (v0 + 256 * q + tid) >> 4;
-                const int t = (int)(((unsigned)e * recip) >> 16), ks = e - t * KS;
-                const bool valid = e < total;
-                const int c = cbase + chan_of<NT>(valid ? t : 0, i >> 2, i & 3);
-                const bool ok = valid && c < Nc;
-                const v4i v = *reinterpret_cast<const v4i *>(a.wq + (ok ? (long long)c * a.KW + 4 * ks : 0));
-                w4[q] = ok ? v : v4i{0, 0, 0, 0};
+                if constexpr (U == 4) {
+                    // (64-bit addresses: this batch and its loop take 0.2 us less with them at 2048 -> 1024, 7x7, batch 1;
+                    // ResNeXt-50's sequence at batch 1 46.6 -> 45.4 us plain, 49.5 -> 47.9 us PReLU)
+                    const int e = (v0 + 256 * q + tid) >> 4;
+                    const int t = (int)(((unsigned)e * recip) >> 16), ks = e - t * KS;
+                    const bool valid = e < total;
+                    const int c = cbase + chan_of<NT>(valid ? t : 0, i >> 2, i & 3);
+                    const bool ok = valid && c < Nc;
+                    const v4i v = *reinterpret_cast<const v4i *>(a.wq + (ok ? (long long)c * a.KW + 4 * ks : 0));
+                    w4[q] = ok ? v : v4i{0, 0, 0, 0};
+                } else {
+                    const int e = min((v0 + 256 * q + tid) >> 4, total - 1);
+                    const int t = (int)(__umul24((unsigned)e, recip) >> 16), ks = e - (int)__umul24((unsigned)t, (unsigned)KS);
+                    const unsigned row = (unsigned)chan_of<NT>(t, i >> 2, i & 3);
+                    w4[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(__umul24(row, (unsigned)(a.KW * 4)) + 16u * (unsigned)ks), 0, 0);
+                }
             }
 #pragma unroll
             for (int q = 0; q < U; ++q) {
@@ -148,41 +191,38 @@ __device__ __forceinline__ void stage_weights(const PwArgs &a, int cbase, v4i *f
                 }
             }
         };
-        batch(0);
-        for (int v0 = 256 * U; v0 < total * 16; v0 += 256 * U) batch(v0);
-    } else {
-        // Any row length: one word per lane; wavefront w decodes entries w, w + 4, ... (tile and k
-        // step of an entry are wave-uniform and advance without a division).
-        constexpr int U = 16;
-        const int i = lane & 15, kg = lane >> 4;
-        int t = 0, ks = wave;
-        while (ks >= KS) {
-            ks -= KS;
-            ++t;
+        if (total <= 16) {
+            batch(Depth<1>{}, 0);
+        } else if (total <= 32) {
+            batch(Depth<2>{}, 0);
+        } else {
+            batch(Depth<4>{}, 0);
+            for (int v0 = 1024; v0 < total * 16; v0 += 1024) batch(Depth<4>{}, v0);
         }
-        auto batch = [&](const int e0) __attribute__((always_inline)) {
+    } else {
+        // Any row length: one word per lane; wavefront w decodes entries w, w + 4, ...
+        const FragWords<NT> words(a, cbase, lane);
+        const unsigned recip = (65536u + (unsigned)KS - 1u) / (unsigned)KS;
+        auto batch = [&](auto depth, const int e0) __attribute__((always_inline)) {
+            constexpr int U = decltype(depth)::value;
             uint32_t word[U];
 #pragma unroll
             for (int q = 0; q < U; ++q) {
-                const bool valid = e0 + 4 * q < total;
-                const int c = cbase + chan_of<NT>(valid ? t : 0, i >> 2, i & 3);
-                const int kw = 4 * ks + kg;
-                // clamp instead of branching so that the loads of a batch are issued back to back
-                const bool ok = valid && c < Nc && kw < a.KW;
-                const uint32_t v = a.wq[ok ? (long long)c * a.KW + kw : 0];
-                word[q] = ok ? v : 0u;
-                ks += 4;
-                while (ks >= KS) {
-                    ks -= KS;
-                    ++t;
-                }
+                const int e = min(e0 + 4 * q, total - 1);
+                const int t = (int)(((unsigned)e * recip) >> 16);
+                word[q] = words.load(0, t, e - t * KS);
             }
 #pragma unroll
             for (int q = 0; q < U; ++q)
                 if (e0 + 4 * q < total) frag[(e0 + 4 * q) * 64 + lane] = decode_word(word[q]);
         };
-        batch(wave);
-        for (int e0 = wave + 4 * U; e0 < total; e0 += 4 * U) batch(e0);
+        if (total <= 16) {
+            batch(Depth<4>{}, wave);
+        } else {
+            batch(Depth<16>{}, wave);
+#pragma clang loop unroll(disable)
+            for (int e0 = wave + 64; e0 < total; e0 += 64) batch(Depth<16>{}, e0);
+        }
     }
     if (ptid) lpar[tid] = requant_params(pb, pm, pn, ps, prelu);
     __syncthreads();

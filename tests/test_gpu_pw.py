@@ -452,3 +452,17 @@ def test_sequence_deep_projection_layers_keep_weights_in_registers(P):
     for (c, l) in inplace:
         i = cases.index(c)
         assert_same(l[5].cpu().numpy(), wants[i], f"in-place residual: case {c}")
+
+
+# The depth of the weight staging follows the fragment entries of a chunk (tiles of 16 output channels times steps of 64
+# input channels): 1, 16 and 17, 32 and 33, 64 and more, with rows of whole 16-byte pieces (cin of multiples of 64) and
+# without, and channel counts that leave the last tile ragged.
+@pytest.mark.parametrize("cin,cout", [
+    (64, 16), (64, 12), (64, 160), (128, 128), (128, 132), (192, 96), (256, 64), (320, 100), (576, 32), (704, 48),
+    (1088, 16), (1024, 64), (2048, 36), (4096, 16),
+    (16, 4), (24, 144), (72, 128), (88, 116), (136, 100), (200, 64), (264, 52), (328, 48), (520, 32), (1032, 16),
+    (2056, 36), (4088, 20)])
+@pytest.mark.parametrize("n,h,w,res", [(1, 3, 5, False), (5, 14, 14, True), (9, 28, 28, False)])
+def test_weight_staging_depths(P, cin, cout, n, h, w, res):
+    L = make_pw_layer(7100 + cin * 3 + cout, n, h, w, cin, cout, signed_x=True, act_window=(-128, 127), with_residual=res)
+    assert_same(run_pw(P, L), oracle_pw(oracle, L), f"staging {cin}->{cout} n={n}")
