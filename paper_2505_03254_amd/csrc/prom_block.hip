@@ -431,6 +431,7 @@ static bool plan_fused(BlockArgs &a, BlockFn &fn, size_t &lds, int &grid, bool f
 // graph is slower with it (316 against 291 us at batch 8), because two short kernels cost less there
 // than the serial chunk loop.  The form stays available through PROM_BLOCK_DWPROJ and
 // prom_dw_pw_conv: it moves one intermediate tensor less through HBM.
+
 // Whether PROM_BLOCK_AUTO takes the plane-resident kernel where it applies.  Measured (GPU time per
 // call, MobileNetV2 blocks, one kernel against three launches replayed from a HIP graph): with at least 12
 // planes of hidden channels on maps up to 28x28 the one kernel is ahead (batch 128: 28x28x192 21.6 against
@@ -440,6 +441,8 @@ static bool plan_fused(BlockArgs &a, BlockFn &fn, size_t &lds, int &grid, bool f
 // rows and the vector ALU's requantisation of the expanded tensor cost as much as the three streaming
 // kernels: 56x56x144 69.8 against 69.6 at batch 128 and 39.8 against 40.7 at 64, stride 2 41.0 against 40.8 and 25.0
 // against 29.8; 112x112x96 102 against 93 at batch 128, 58 against 51 at 64, 30.2 against 32.7 at 32.
+// (Measured before the kernel's prologue was shortened, which took another 9 % off it on average.  The large maps among
+// these now go to the kernel of pixel tiles, see tile_is_faster.)
 static bool planes_is_faster(int n, int h, int w, int cin, int chid, int cout, int stride)
 {
     (void)cin; (void)cout; (void)stride;
