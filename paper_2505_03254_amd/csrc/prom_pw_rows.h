@@ -35,11 +35,11 @@ __host__ __device__ constexpr size_t lds_bytes_rows(int nt, int cw, int ks)
 // Fragments frag[CW*NT][KS][64] and parameters lpar[CW*NT][4 g][4 r] of a super-chunk; tile slot
 // cw*NT + t holds the channels base + 16*NT*cw + chan_of<NT>(t, ., .).  Ends with the barrier.
 template <int NT>
-__device__ __forceinline__ void stage_weights_rows(const PwArgs &a, int cbase, int CW, int nthr, bool prelu, v4i *frag,
-                                                   v4i *lpar)
+__device__ __forceinline__ void stage_weights_rows(const PwArgs &a, int cbase, int KS, int CW, int nthr, bool prelu,
+                                                   v4i *frag, v4i *lpar)
 {
     const int tid = threadIdx.x;
-    const int KS = a.KS, Nc = a.Nc;
+    const int Nc = a.Nc;
     const int NTT = CW * NT;
     const int nfrag = NTT * KS * 64;
     // The parameter loads and the first batch of weight loads are issued in straight-line code, so
@@ -67,30 +67,34 @@ __device__ __forceinline__ void stage_weights_rows(const PwArgs &a, int cbase, i
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const FragWords<NT> words(a, cbase, tid & 63);
     const unsigned recip = (65536u + (unsigned)KS - 1u) / (unsigned)KS;  // tk / KS == (tk * recip) >> 16 for tk < 1024
-    auto batch = [&](auto depth, const int base) __attribute__((always_inline)) {
-        constexpr int U = decltype(depth)::value;  // words in flight per thread
+    constexpr int U = 8;  // words in flight per thread
+    auto batch = [&](const int base) __attribute__((always_inline)) {
         uint32_t word[U];
-#pragma unroll
-        for (int q = 0; q < U; ++q) {
-            const int tk = min(base / 64 + q * (nthr >> 6) + wave, NTT * KS - 1);  // entry (tile, k step), wave-uniform
-            const int tt = (int)(((unsigned)tk * recip) >> 16);
+        auto load = [&](const int q) __attribute__((always_inline)) {
+            const int tk = base / 64 + q * (nthr >> 6) + wave;  // entry (tile, k step), wave-uniform
+            const int tt = KS == 1 ? tk : (int)(((unsigned)tk * recip) >> 16);
             const int cw = tt / NT;
-            word[q] = words.load(cw * NT * 16, tt - cw * NT, tk - tt * KS);
+            // An entry that does not exist is no access.  (Reading the last entry once more instead, every workgroup the
+            // same few lines at a time: 28x28 56 -> 384 at batch 12 7.1 -> 7.6 us.)
+            word[q] = words.load(cw * NT * 16, tt - cw * NT, tk < NTT * KS ? tk - tt * KS : 1 << 20);
+            __builtin_amdgcn_sched_barrier(0);  // (leaves before the next load's address is computed)
+        };
+#pragma unroll
+        for (int q = 0; q < U / 2; ++q) load(q);
+        if (nfrag - base > U / 2 * nthr) {  // (the second half only where there are words for it, see stage_weights)
+#pragma unroll
+            for (int q = U / 2; q < U; ++q) load(q);
         }
+        asm volatile("" ::: "memory");  // (all loads leave before the first word is used, see stage_weights)
 #pragma unroll
         for (int q = 0; q < U; ++q) {
             const int idx = base + q * nthr + tid;
             if (idx < nfrag) frag[idx] = decode_word(word[q]);
         }
     };
-    // (as deep as there are words, see stage_weights)
-    if (nfrag <= 4 * nthr) {
-        batch(Depth<4>{}, 0);
-    } else {
-        batch(Depth<8>{}, 0);
+    batch(0);
 #pragma clang loop unroll(disable)
-        for (int base = nthr * 8; base < nfrag; base += nthr * 8) batch(Depth<8>{}, base);
-    }
+    for (int base = nthr * U; base < nfrag; base += nthr * U) batch(base);
 #pragma unroll
     for (int q = 0; q < PU; ++q) {
         const int s = tid + q * nthr;
@@ -176,7 +180,7 @@ __device__ __forceinline__ void pw_rows_body(const PwArgs &a, const int lid, uns
 #pragma unroll
     for (int d = 0; d < D; ++d) load_group(ring[d]);
     PW_STAMP(1);
-    stage_weights_rows<NT>(a, cbase, CW, nthr, prelu, frag, lpar);
+    stage_weights_rows<NT>(a, cbase, KS, CW, nthr, prelu, frag, lpar);
     PW_STAMP(2);
 
     v4i par[NT][4];

@@ -93,12 +93,15 @@ __device__ __forceinline__ v4i decode_word(uint32_t word)
     return f;
 }
 
+constexpr int kBufFlags = 0x00020000;   // raw buffer of dwords, gfx9 family
+constexpr int kOobOffset = 0x7ffff000;  // byte offset beyond any tensor handled here
+
 // The packed words of the rows from cbase on as a buffer: rows beyond the layer's read zero, and offsets stay far below
 // 2^31 whatever the layer's size (a chunk reads 16 * NT * CW rows of at most 1 KB).
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rows(const PwArgs &a, int cbase)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.wq) + (long long)cbase * a.KW, 0,
-                                             min(a.Nc - cbase, 1 << 16) * a.KW * 4, 0x00020000);
+                                             min(a.Nc - cbase, 1 << 16) * a.KW * 4, kBufFlags);
 }
 
 // Loads in flight per thread, as a type.
@@ -121,9 +124,18 @@ template <int NT> struct FragWords {
     {
         const int first = grp_first<NT>(t), row = cofs + 16 * first + 4 * (t - first);
         const int off = (int)__umul24((unsigned)rows4, (unsigned)grp_size<NT>(t)) + rest + (row * KW + 4 * ks) * 4;
-        return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rsrc, kg < KW - 4 * ks ? off : 0x7ffff000, 0, 0);
+        return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rsrc, kg < KW - 4 * ks ? off : kOobOffset, 0, 0);
     }
 };
+
+// At the end of every branch that loads weights: waits for the loads whose words no entry used.  Without it the compiler
+// takes their registers for pending at the head of the branch beside it, and waits there for everything that has been
+// loaded so far, activations and parameters, before the first weight load of that branch leaves.
+__device__ __forceinline__ void weights_landed()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    asm volatile("" ::: "memory");
+}
 
 // Decode the chunk's weights into LDS fragments frag[NT][KS][64 lanes] and the chunk's
 // requantisation parameters into lpar[NT][4 g][4 r] = (C lo, C hi, mult, shift), or
@@ -153,6 +165,9 @@ __device__ __forceinline__ void stage_weights(const PwArgs &a, int cbase, v4i *f
     // loads issued before this call instead of behind a wait at a loop header -- and decoded as
     // they arrive.  A first batch is no deeper than there are entries (1, 2 or 4 and 4 or 16 per thread): what is computed
     // for entries that do not exist is most of a short layer's time (28x28 16 -> 16 at batch 78 7.1 -> 4.3 us).
+    // All loads of a batch leave before the first word is used: the compiler moves a load whose word is used under a
+    // condition only (entry e exists) behind that condition, where it is waited for at once, and with it for all others
+    // (14x14 792 -> 160 at batch 34 8.5 -> 9.6 us; with the empty statements behind the loads below 8.5).
     const int total = NT * KS;
     if ((a.KW & 3) == 0 && (reinterpret_cast<uintptr_t>(a.wq) & 15) == 0) {
         // Rows of whole 16-byte pieces: a thread fetches the four words of (entry, i) with one
@@ -176,12 +191,14 @@ __device__ __forceinline__ void stage_weights(const PwArgs &a, int cbase, v4i *f
                     const v4i v = *reinterpret_cast<const v4i *>(a.wq + (ok ? (long long)c * a.KW + 4 * ks : 0));
                     w4[q] = ok ? v : v4i{0, 0, 0, 0};
                 } else {
-                    const int e = min((v0 + 256 * q + tid) >> 4, total - 1);
+                    const int e = (v0 + 256 * q + tid) >> 4;  // (beyond the chunk: no access, not one more of a hot line)
                     const int t = (int)(__umul24((unsigned)e, recip) >> 16), ks = e - (int)__umul24((unsigned)t, (unsigned)KS);
                     const unsigned row = (unsigned)chan_of<NT>(t, i >> 2, i & 3);
-                    w4[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(__umul24(row, (unsigned)(a.KW * 4)) + 16u * (unsigned)ks), 0, 0);
+                    const int off = (int)(__umul24(row, (unsigned)(a.KW * 4)) + 16u * (unsigned)ks);
+                    w4[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, e < total ? off : kOobOffset, 0, 0);
                 }
             }
+            asm volatile("" ::: "memory");
 #pragma unroll
             for (int q = 0; q < U; ++q) {
                 const int e = (v0 + 256 * q + tid) >> 4;
@@ -193,11 +210,14 @@ __device__ __forceinline__ void stage_weights(const PwArgs &a, int cbase, v4i *f
         };
         if (total <= 16) {
             batch(Depth<1>{}, 0);
+            weights_landed();
         } else if (total <= 32) {
             batch(Depth<2>{}, 0);
+            weights_landed();
         } else {
             batch(Depth<4>{}, 0);
             for (int v0 = 1024; v0 < total * 16; v0 += 1024) batch(Depth<4>{}, v0);
+            weights_landed();
         }
     } else {
         // Any row length: one word per lane; wavefront w decodes entries w, w + 4, ...
@@ -211,17 +231,21 @@ __device__ __forceinline__ void stage_weights(const PwArgs &a, int cbase, v4i *f
                 const int e = min(e0 + 4 * q, total - 1);
                 const int t = (int)(((unsigned)e * recip) >> 16);
                 word[q] = words.load(0, t, e - t * KS);
+                __builtin_amdgcn_sched_barrier(0);  // (leaves before the next load's address is computed)
             }
+            asm volatile("" ::: "memory");
 #pragma unroll
             for (int q = 0; q < U; ++q)
                 if (e0 + 4 * q < total) frag[(e0 + 4 * q) * 64 + lane] = decode_word(word[q]);
         };
         if (total <= 16) {
             batch(Depth<4>{}, wave);
+            weights_landed();
         } else {
             batch(Depth<16>{}, wave);
 #pragma clang loop unroll(disable)
             for (int e0 = wave + 64; e0 < total; e0 += 64) batch(Depth<16>{}, e0);
+            weights_landed();
         }
     }
     if (ptid) lpar[tid] = requant_params(pb, pm, pn, ps, prelu);
@@ -256,9 +280,6 @@ __host__ __device__ constexpr size_t lds_bytes_generic(int nt, int ks)
 {
     return (size_t)nt * ks * 1024 + (size_t)nt * 16 * 16;
 }
-
-constexpr int kBufFlags = 0x00020000;   // raw buffer of dwords, gfx9 family
-constexpr int kOobOffset = 0x7ffff000;  // byte offset beyond any tensor handled here
 
 // ============================================================================================
 // Streaming kernel: cin % 8 == 0, cout % 4 == 0, 4-byte aligned tensors below 2^30 bytes, and

@@ -65,3 +65,37 @@ def test_grouped_kernels_use_no_scratch():
     assert len(found) == 4, sorted(found)
     for name, k in found.items():
         assert k[".private_segment_fixed_size"] == 0, (name, k[".private_segment_fixed_size"])
+
+
+def test_weight_loads_leave_together(tmp_path):
+    """The loads of a batch of the weight staging stand in one basic block, 16 or 4 words per lane, 4 and 4 more in the
+    row kernel, and nothing in that block waits for all loads before the last of them has left."""
+    from paper_2505_03254_amd.build import HIPCC_FLAGS, _hipcc
+    out = str(tmp_path / "weight_loads.s")
+    p = subprocess.run([_hipcc()] + HIPCC_FLAGS + ["--cuda-device-only", "-S", "-x", "hip",
+                                                   os.path.join(ROOT, "tests", "weight_loads.hip"), "-o", out],
+                       capture_output=True, text=True)
+    assert p.returncode == 0, p.stderr
+    runs, name, run, waited = {}, None, 0, False
+    for line in open(out):
+        s = line.strip()
+        if line[0] == "_" and ":" in line:
+            name, run, waited = line.split(":")[0], 0, False
+            runs[name] = []
+        if name is None or not s or s[0] == ";" or (s[0] == "." and ":" not in s):
+            continue
+        op = s.split()[0]
+        if op == "buffer_load_dword":  # a word of codes (activations and parameters have other loads)
+            run += 1
+            assert not waited, (name, s)
+        elif op.endswith(":") or op.startswith(("s_cbranch", "s_branch", "v_mfma")):
+            runs[name] += [run] if run else []
+            run, waited = 0, False
+            if op.startswith("v_mfma"):
+                name = None
+        elif op == "s_waitcnt" and "vmcnt(0)" in s:
+            waited = True
+    stream, = (v for k, v in runs.items() if "pw_stream_kernel" in k)
+    rows, = (v for k, v in runs.items() if "rows_staging" in k)
+    assert sorted(stream) == [4, 16, 16], runs
+    assert sorted(rows) == [4, 4, 4, 4], runs
