@@ -388,13 +388,21 @@ size_t prom_block_workspace_size(int n, int h, int w, int cin, int chid, int cou
 /* The same with the choice between the forms of the block made by the caller: as one kernel whose
  * expanded band stays in LDS as 16-channel planes (PROM_BLOCK_PLANES: any number of hidden
  * channels that is a multiple of 16), as one chunk-interleaved kernel with every weight decoded in
- * LDS (PROM_BLOCK_FUSED: up to 192 hidden channels), as three launches through the workspace, or as
+ * LDS (PROM_BLOCK_FUSED: up to 192 hidden channels), as one kernel whose wavefronts own tiles of output
+ * pixels (PROM_BLOCK_TILE: up to 64 channels in and out), as three launches through the workspace, or as
  * two launches (expand, then depthwise and projection fused: prom_dw_pw_conv; only the expanded
  * tensor goes through the workspace).  prom_block is prom_block_ex with PROM_BLOCK_AUTO, which takes
  * the form measured faster for the shape.  A form returns PROM_EUNSUPPORTED where it does not apply
  * (prom_block_planes_applies with 16-byte aligned parameter arrays of the first two layers,
- * prom_block_can_fuse, prom_dw_pw_can_fuse; x, y, w_dw 8-byte aligned). */
-enum { PROM_BLOCK_AUTO = 0, PROM_BLOCK_FUSED = 1, PROM_BLOCK_UNFUSED = 2, PROM_BLOCK_DWPROJ = 3, PROM_BLOCK_PLANES = 4 };
+ * prom_block_can_fuse, prom_dw_pw_can_fuse; x, y, w_dw 8-byte aligned; PROM_BLOCK_TILE: the limits of
+ * prom_block_tile_applies, whether it is faster or not). */
+enum { PROM_BLOCK_AUTO = 0, PROM_BLOCK_FUSED = 1, PROM_BLOCK_UNFUSED = 2, PROM_BLOCK_DWPROJ = 3, PROM_BLOCK_PLANES = 4,
+       PROM_BLOCK_TILE = 5 };
+/* PROM_BLOCK_TILE with the plan (or parts of it, 0: the library's) chosen by the caller, for tests and measurements:
+ * the variant (1 to 10, as prom_block_tile_applies numbers them: stride 1, up to 32 output channels, tiles of 8, 6, 4, 2
+ * rows; up to 64, 6, 4, 2 rows; stride 2, up to 32, 8, 4 rows; up to 64, 4 rows), the wavefronts that share the hidden
+ * channels of a tile (1, 2, 3, 4, 6) and the tiles of a workgroup.  PROM_EUNSUPPORTED for a plan that does not exist. */
+#define PROM_BLOCK_TILE_PLAN(variant, split, tiles) (PROM_BLOCK_TILE | (variant) << 8 | (split) << 16 | (tiles) << 20)
 int prom_block_ex(const int8_t *x, int n, int h, int w, int cin, int chid, int cout, int stride,
                   const void *w_expand_packed, const prom_requant_t *rq_expand,
                   const int8_t *w_dw, const prom_requant_t *rq_dw,

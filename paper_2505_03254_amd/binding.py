@@ -391,7 +391,7 @@ def prom_gconv3x3(x, w_g, stride: int, rq: Requant, y=None, stream=None, w_frag=
 def prom_block(x, chid: int, cout: int, stride: int, w_expand_packed, rq_expand: Requant,
                w_dw, rq_dw: Requant, w_project_packed, rq_project: Requant, add_residual: bool,
                workspace, y=None, stream=None, path: int = 0):
-    """path: BLOCK_AUTO (0, the library picks), BLOCK_FUSED (1) or BLOCK_UNFUSED (2): prom_block_ex."""
+    """path: BLOCK_AUTO (the library picks) or one of the forms BLOCK_...: prom_block_ex."""
     import torch
     _dev_i8(x, "x")
     _dev_i8(w_dw, "w_dw")
@@ -411,7 +411,12 @@ def prom_block(x, chid: int, cout: int, stride: int, w_expand_packed, rq_expand:
     return y
 
 
-BLOCK_AUTO, BLOCK_FUSED, BLOCK_UNFUSED, BLOCK_DWPROJ, BLOCK_PLANES = 0, 1, 2, 3, 4
+BLOCK_AUTO, BLOCK_FUSED, BLOCK_UNFUSED, BLOCK_DWPROJ, BLOCK_PLANES, BLOCK_TILE = 0, 1, 2, 3, 4, 5
+
+
+def block_tile_plan(variant: int = 0, split: int = 0, tiles: int = 0) -> int:
+    """BLOCK_TILE with (parts of) its plan chosen: PROM_BLOCK_TILE_PLAN."""
+    return BLOCK_TILE | variant << 8 | split << 16 | tiles << 20
 
 
 def prom_dw_pw_conv(x, w_dw, stride: int, rq_dw: Requant, w_project_packed, cout: int, rq_project: Requant,

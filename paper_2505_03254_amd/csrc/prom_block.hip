@@ -462,9 +462,6 @@ static bool tile_is_faster(prom::TileArgs &a, bool prelu, double planes_cost, si
 {
     // (no kernel has more than 64 channels in or out: spare the planning)
     if (a.cin > 64 || a.cout > 64 || !prom::plan_tile(a, prelu, lds, grid)) return false;
-#ifdef PROM_PLAN_ENV
-    if (getenv("PROM_TILE")) return true;
-#endif
     double other;
     if (planes_cost > 0) {
         const double c = planes_cost / 2400.0;
@@ -497,9 +494,7 @@ static const BlockPlan &block_plan(int n, int h, int w, int cin, int chid, int c
     unsigned hash = 0;
     for (int k : key) hash = (hash ^ (unsigned)k) * 2654435761u;
     BlockPlan &p = slots[(hash >> 16) % kSlots];
-#ifndef PROM_PLAN_ENV
     if (memcmp(p.key, key, sizeof(key)) == 0) return p;
-#endif
     p.pa = {};
     p.ta = {};
     p.pa.N = p.ta.N = n; p.pa.H = p.ta.H = h; p.pa.W = p.ta.W = w;
@@ -601,8 +596,13 @@ extern "C" int prom_block_ex(const int8_t *x, int n, int h, int w, int cin, int 
                              int path, void *stream)
 {
     using namespace prom;
+    TileChoice choice = {};
+    if (path > 0 && (path & 0xff) == PROM_BLOCK_TILE) {
+        choice = {(path >> 8) & 0xff, (path >> 16) & 0xf, path >> 20};
+        path = PROM_BLOCK_TILE;
+    }
     if (path != PROM_BLOCK_AUTO && path != PROM_BLOCK_FUSED && path != PROM_BLOCK_UNFUSED &&
-        path != PROM_BLOCK_DWPROJ && path != PROM_BLOCK_PLANES)
+        path != PROM_BLOCK_DWPROJ && path != PROM_BLOCK_PLANES && path != PROM_BLOCK_TILE)
         return PROM_EINVAL;
     if (!x || !y || !w_expand_packed || !w_dw || !w_project_packed || !rq_expand || !rq_dw || !rq_project)
         return PROM_EINVAL;
@@ -644,7 +644,7 @@ extern "C" int prom_block_ex(const int8_t *x, int n, int h, int w, int cin, int 
     a.lo_e = rq_expand->act_min; a.hi_e = rq_expand->act_max;
     a.lo_d = rq_dw->act_min; a.hi_d = rq_dw->act_max;
     a.lo_p = rq_project->act_min; a.hi_p = rq_project->act_max;
-    if (path == PROM_BLOCK_PLANES || path == PROM_BLOCK_AUTO) {
+    if (path == PROM_BLOCK_PLANES || path == PROM_BLOCK_TILE || path == PROM_BLOCK_AUTO) {
         // one kernel: wavefronts that own pixel tiles, or the expanded band resident in LDS as 16-channel planes
         auto fill = [&](auto &k) {
             k.x = x; k.y = y;
@@ -669,6 +669,14 @@ extern "C" int prom_block_ex(const int8_t *x, int n, int h, int w, int cin, int 
             int pgrid = 0, kse = 0;
             if (!ok || !plan_planes(pa, plds, pgrid, kse)) return PROM_EUNSUPPORTED;
             return launch_planes(pa, plds, pgrid, kse, stream);
+        }
+        if (path == PROM_BLOCK_TILE) {
+            TileArgs ta = {};
+            fill(ta);
+            size_t tlds = 0;
+            int tgrid = 0;
+            if (!aligned || !plan_tile(ta, a.ne || a.nd, tlds, tgrid, choice)) return PROM_EUNSUPPORTED;
+            return launch_tile(ta, tlds, tgrid, stream);
         }
         if (aligned) {
             const BlockPlan &p = block_plan(n, h, w, cin, chid, cout, stride, a.ne || a.nd);

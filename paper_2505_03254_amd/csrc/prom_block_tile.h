@@ -31,8 +31,10 @@ struct TileArgs {
     double us;           // the planner's estimate
 };
 
+// A caller's choice, 0 for the planner's: variant 1, 2, ..., wavefronts that share a tile, tiles of a workgroup.
+struct TileChoice { int variant, split, tiles; };
 // Tile, split and LDS layout for the shape in `a`; false if the kernel does not take it.
-bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid);
+bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid, const TileChoice &only = {});
 // Launch; PROM_OK or PROM_EHIP.
 int launch_tile(const TileArgs &a, size_t lds, int grid, void *stream);
 

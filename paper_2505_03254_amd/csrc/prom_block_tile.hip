@@ -32,7 +32,6 @@
 #include "prom_launch.h"
 #include "prom_block_tile.h"
 
-#include <cstdlib>
 #include <mutex>
 #include <vector>
 
@@ -538,14 +537,14 @@ static const TileInst kTileInst[] = {
 #undef TL
 
 // Tile height, split of the hidden channels and workgroup for the shape in `a` (N, H, W, Ho, Wo, cin, chid, cout, stride
-// set; prelu: a layer of the first two has negative-side multipliers).
+// set; prelu: a layer of the first two has negative-side multipliers); of those `only` leaves, if it is given.
 //
 // Every kernel, S and T is priced in microseconds.  A plane of a wavefront's tile takes the longer of its own chain
 // (lat) and, with k wavefronts on a SIMD, k times the instructions it issues (thr); both grow with the 16-pixel tiles
 // of the expansion and the filter.  Constants: least squares over 62771 plans of 1029 blocks (batch 1 to 256, maps of
 // 11 to 115, up to 64 channels in and out, with and without PReLU), error 10 %; the plan it picks is 1.7 % behind the
 // best one on average, 15 % at most.
-bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
+bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid, const TileChoice &only)
 {
     const int s = a.stride;
     if (a.cin % 4 != 0 || a.chid % 16 != 0 || a.cout % 4 != 0) return false;
@@ -556,11 +555,6 @@ bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
     a.KWp = a.chid / 16;
     const int TC = s == 1 ? 14 : 7;
     a.cols_n = (a.Wo + TC - 1) / TC;
-    int only_inst = -1, only_s = 0, only_t = 0;
-#ifdef PROM_PLAN_ENV  // developer build: the plan from the environment
-    if (const char *e = getenv("PROM_TILE"))
-        if (sscanf(e, "%d,%d,%d", &only_inst, &only_s, &only_t) != 3) return false;
-#endif
     const double slow = prelu ? 1.62 : 1.0;
     const int np = a.chid / 16;
     double best = 0;
@@ -568,7 +562,7 @@ bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
     int best_wgs = 0;
     for (int i = 0; i < (int)(sizeof(kTileInst) / sizeof(kTileInst[0])); ++i) {
         const TileInst &I = kTileInst[i];
-        if (I.stride != s || a.cin > 64 || a.cout > 16 * I.cot || (only_inst >= 0 && i != only_inst)) continue;
+        if (I.stride != s || a.cin > 64 || a.cout > 16 * I.cot || (only.variant && i + 1 != only.variant)) continue;
         const int TR = I.tr, nt1 = (TR - 1) * s + 3, nt2 = s == 1 ? TR : TR / 2;
         const long long per_img = (long long)((a.Ho + TR - 1) / TR) * a.cols_n, tiles = per_img * a.N;
         // (tile / per_img is a multiplication, right for tiles * per_img < 2^32)
@@ -584,10 +578,10 @@ bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
         const double lat = (0.102 + 0.0315 * (nt1 + nt2)) * slow, thr = (0.067 + 0.0317 * (nt1 + nt2)) * slow;
         const int fin = nt2 * I.cot;
         for (int S : {1, 2, 3, 4, 6}) {
-            if (S > a.NQ || S > I.nw || (only_s && S != only_s)) continue;
+            if (S > a.NQ || S > I.nw || (only.split && S != only.split)) continue;
             const int npw = S == 1 ? np : 2 * ((a.NQ + S - 1) / S);  // planes of a wavefront
             for (int T = I.nw / S; T >= 1; --T) {
-                if (only_t && T != only_t) continue;
+                if (only.tiles && T != only.tiles) continue;
                 int bytes = off_t1 + S * T * t1_bytes;
                 const int red = I.cot * 256 + S * T * fin * 1024;  // partial sums, in place of the weights
                 if (S > 1 && bytes < red) bytes = red;
@@ -596,6 +590,7 @@ bool plan_tile(TileArgs &a, bool prelu, size_t &lds, int &grid)
                 int percu = I.nw / (S * T);
                 if (percu > 160 * 1024 / bytes) percu = 160 * 1024 / bytes;
                 const long long wgs = (tiles + T - 1) / T;
+                if (S > 1 && wgs * thr_wg >= (1LL << 32)) continue;  // (a launch has fewer threads than that)
                 // rounds of the prologue's loads, and its entries per thread
                 const int ne = 2 * a.NQ * 64, npj = a.NQ * I.cot * 64;
                 const int extra = (ne > 2 * thr_wg ? (ne - 2 * thr_wg + 4 * thr_wg - 1) / (4 * thr_wg) : 0) +
