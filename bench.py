@@ -797,8 +797,7 @@ def chain_leg(P, torch, dev, batch, log):
                 e, d, p = Bk.expand, Bk.dw, Bk.project
                 rq3 = [P.Requant(t(l.bias), t(l.mult), t(l.shift), l.act_min, l.act_max) for l in (e, d, p)]
                 ws_bytes = max(ws_bytes, P.prom_block_workspace_size(batch, hw, hw, b.cin, Bk.chid, b.cout, b.stride))
-                is_fused = P.prom_block_is_fused(batch, hw, hw, b.cin, Bk.chid, b.cout, b.stride)
-                if is_fused:
+                if P.prom_block_form(batch, hw, hw, b.cin, Bk.chid, b.cout, b.stride) != P.BLOCK_UNFUSED:
                     fused.append(b.name)
                 else:
                     mid_bytes += 2 * batch * Bk.chid * (hw * hw + ho * ho)
@@ -952,7 +951,7 @@ def extra_legs(P, torch, dev, batch, log):
     m = B.n * B.h * B.w
     compulsory = m * (B.cin + B.cout)
     out["block_config4"] = {"us": round(dt * 1e6, 1),
-                            "fused": P.prom_block_is_fused(B.n, B.h, B.w, B.cin, B.chid, B.cout, 1),
+                            "fused": P.prom_block_form(B.n, B.h, B.w, B.cin, B.chid, B.cout, 1) != P.BLOCK_UNFUSED,
                             "compulsory_gbs": round(compulsory / dt / 1e9, 1),
                             "pw_gops": round(2 * m * B.cin * B.chid * 2 / dt / 1e9, 1)}
     log(f"[bench] block (config 4): {dt * 1e6:.1f} us per call")

@@ -410,10 +410,15 @@ int prom_block_ex(const int8_t *x, int n, int h, int w, int cin, int chid, int c
                   int add_residual, void *workspace, size_t workspace_bytes,
                   int8_t *y, int path, void *stream);
 
-/* 1 if prom_block (PROM_BLOCK_AUTO) runs this shape as one of the two kernels that keep a band of the
- * expanded tensor in LDS (pointers assumed aligned), 0 if as three launches through the workspace,
- * PROM_EINVAL for bad dimensions -- unless the kernel of pixel tiles takes the shape over
- * (prom_block_tile_applies).  Host only, launches nothing. */
+/* What prom_block (PROM_BLOCK_AUTO) runs this shape as, pointers assumed aligned: PROM_BLOCK_TILE, PROM_BLOCK_PLANES or
+ * PROM_BLOCK_FUSED (one kernel, the expanded tensor never leaves the chip), or PROM_BLOCK_UNFUSED (three launches through
+ * the workspace).  prelu != 0: the expansion or the depthwise layer has negative-side multipliers.  PROM_EINVAL for bad
+ * dimensions, PROM_EUNSUPPORTED beyond 4096 input or hidden channels.  Host only, launches nothing. */
+int prom_block_form(int n, int h, int w, int cin, int chid, int cout, int stride, int prelu);
+
+/* 1 if the library prefers one of the two kernels that keep a band of the expanded tensor in LDS (PROM_BLOCK_PLANES,
+ * PROM_BLOCK_FUSED) to three launches for this shape, 0 if not, PROM_EINVAL for bad dimensions.  Either way the kernel of
+ * pixel tiles may take the shape over: prom_block_form says what runs.  Host only, launches nothing. */
 int prom_block_is_fused(int n, int h, int w, int cin, int chid, int cout, int stride);
 
 /* Positive (which of its variants) if PROM_BLOCK_AUTO takes the kernel whose wavefronts own pixel tiles instead of what

@@ -126,6 +126,8 @@ def load_library():
     lib.prom_dw_pw_can_fuse.argtypes = [ci] * 6
     lib.prom_block_can_fuse.restype = ci
     lib.prom_block_can_fuse.argtypes = [ci] * 7
+    lib.prom_block_form.restype = ci
+    lib.prom_block_form.argtypes = [ci] * 8
     lib.prom_block_tile_applies.restype = ci
     lib.prom_block_tile_applies.argtypes = [ci] * 8
     lib.prom_block_planes_applies.restype = ci
@@ -482,6 +484,14 @@ def prom_block_tile_applies(n: int, h: int, w: int, cin: int, chid: int, cout: i
     rc = load_library().prom_block_tile_applies(n, h, w, cin, chid, cout, stride, int(prelu))
     if rc < 0:
         raise PromError(rc, "prom_block_tile_applies")
+    return rc
+
+
+def prom_block_form(n: int, h: int, w: int, cin: int, chid: int, cout: int, stride: int, prelu: bool = False) -> int:
+    """The form BLOCK_... that prom_block runs a shape as."""
+    rc = load_library().prom_block_form(n, h, w, cin, chid, cout, stride, int(prelu))
+    if rc < 0:
+        raise PromError(rc, "prom_block_form")
     return rc
 
 

@@ -558,6 +558,16 @@ extern "C" int prom_block_tile_applies(int n, int h, int w, int cin, int chid, i
     return p.tile ? 1 + p.ta.inst : 0;
 }
 
+extern "C" int prom_block_form(int n, int h, int w, int cin, int chid, int cout, int stride, int prelu)
+{
+    const int tile = prom_block_tile_applies(n, h, w, cin, chid, cout, stride, prelu);
+    if (tile < 0) return tile;
+    if (cin > 4096 || chid > 4096) return PROM_EUNSUPPORTED;
+    if (tile) return PROM_BLOCK_TILE;
+    if (block_plan(n, h, w, cin, chid, cout, stride, prelu != 0).planes) return PROM_BLOCK_PLANES;
+    return fused_query(n, h, w, cin, chid, cout, stride, false) ? PROM_BLOCK_FUSED : PROM_BLOCK_UNFUSED;
+}
+
 extern "C" int prom_block_can_fuse(int n, int h, int w, int cin, int chid, int cout, int stride)
 {
     return fused_query(n, h, w, cin, chid, cout, stride, true);

@@ -168,6 +168,33 @@ def test_host_side_queries_of_the_launch_forms(P):
     assert P.prom_pw_batch_class(128, 7, 7, 2048, 1024) == 0
 
 
+def test_block_form_says_what_runs(P):
+    """prom_block_form: the kernel of pixel tiles wherever prom_block_tile_applies says so, with and without PReLU,
+    otherwise what prom_block_is_fused stands for."""
+    from workloads import mobilenetv2_blocks
+    assert P.prom_block_form(128, 56, 56, 24, 144, 24, 1) == P.BLOCK_TILE          # three launches without that kernel
+    assert P.prom_block_form(128, 112, 112, 16, 96, 24, 2, prelu=True) == P.BLOCK_TILE
+    assert P.prom_block_form(128, 14, 14, 96, 576, 96, 1) == P.BLOCK_PLANES
+    assert P.prom_block_form(1, 60, 60, 72, 180, 72, 1) == P.BLOCK_UNFUSED         # hidden channels not a multiple of 16
+    assert P.prom_block_form(64, 28, 28, 72, 180, 72, 1) == P.BLOCK_FUSED
+    assert P.prom_block_form(4, 14, 14, 60, 360, 60, 1) == P.BLOCK_UNFUSED
+    shapes = [(n, b.hw_in, b.hw_in, b.cin, b.cin * b.t, b.cout, b.stride)
+              for n in (1, 8, 32, 128) for b in mobilenetv2_blocks() if b.t != 1]
+    seen = set()
+    for s in shapes + [(96, 112, 112, 40, 240, 128, 1), (1, 1448, 1448, 16, 96, 16, 1), (64, 1448, 1448, 16, 96, 16, 1)]:
+        for prelu in (False, True):
+            form = P.prom_block_form(*s, prelu=prelu)
+            assert (form == P.BLOCK_TILE) == (P.prom_block_tile_applies(*s, prelu=prelu) > 0), s
+            if form != P.BLOCK_TILE:
+                assert (form != P.BLOCK_UNFUSED) == P.prom_block_is_fused(*s), s
+            seen.add(form)
+    assert {P.BLOCK_TILE, P.BLOCK_PLANES, P.BLOCK_UNFUSED} <= seen
+    for bad, code in (((0, 7, 7, 16, 96, 16, 1), -1), ((1, 7, 7, 16, 96, 16, 3), -1), ((1, 7, 7, 5000, 96, 16, 1), -2)):
+        with pytest.raises(P.PromError) as e:
+            P.prom_block_form(*bad)
+        assert e.value.code == code
+
+
 def test_binding_fails_loudly_without_library(P, monkeypatch):
     import paper_2505_03254_amd.binding as b
     monkeypatch.setattr(b, "_lib", None)

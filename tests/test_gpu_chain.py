@@ -92,9 +92,10 @@ def test_mobilenetv2_block_chain(P, p_zero, input_hw, n):
 @pytest.mark.parametrize("n", [32, 128])
 def test_mobilenetv2_block_chain_full_size_auto(P, n):
     """The 16 expanding blocks at the network's own sizes (224x224 input) through prom_block with
-    PROM_BLOCK_AUTO, at batches where the library picks different forms: at 32 images every block
-    is one kernel; at 128 the three blocks on the large maps are three launches and the thirteen
-    behind them one kernel each.  Every output of every block against the oracle."""
+    PROM_BLOCK_AUTO, at batches where the library picks different forms: every block is one kernel,
+    the first on the large maps that of pixel tiles, the deep ones the plane-resident one.  At 128
+    images the first three, which would be three launches without the former, are run as three
+    launches too.  Every output of every block against the oracle."""
     torch = torch_cuda()
     blocks = [b for b in mobilenetv2_blocks() if b.t != 1]
     seed = 8800 + n
@@ -102,7 +103,7 @@ def test_mobilenetv2_block_chain_full_size_auto(P, n):
     x_host = SplitMix64(seed).bytes_masked(n * b0.hw_in * b0.hw_in * b0.cin, 0x7F).view(np.int8)
     x_host = x_host.reshape(n, b0.hw_in, b0.hw_in, b0.cin)
     x_dev = dev(x_host)
-    one_kernel = []
+    one_kernel, forms = [], []
     for i, b in enumerate(blocks):
         hw = b.hw_in
         B = make_block(seed + 10 * i, 1, hw, hw, b.cin, b.t, b.cout, b.stride, expand_shift=_pw_shift(b.cin),
@@ -110,20 +111,27 @@ def test_mobilenetv2_block_chain_full_size_auto(P, n):
         ws = torch.empty(P.prom_block_workspace_size(n, hw, hw, b.cin, B.chid, b.cout, b.stride),
                          dtype=torch.int8, device="cuda")
         one_kernel.append(P.prom_block_is_fused(n, hw, hw, b.cin, B.chid, b.cout, b.stride))
-        y_dev = P.prom_block(x_dev, B.chid, b.cout, b.stride,
-                             dev(P.prom_pack_ternary(B.expand.weight)), requant_dev(P, B.expand),
-                             dev(B.dw.weight), requant_dev(P, B.dw),
-                             dev(P.prom_pack_ternary(B.project.weight)), requant_dev(P, B.project),
-                             B.add_residual, ws)
+        forms.append(P.prom_block_form(n, hw, hw, b.cin, B.chid, b.cout, b.stride))
+        args = (x_dev, B.chid, b.cout, b.stride,
+                dev(P.prom_pack_ternary(B.expand.weight)), requant_dev(P, B.expand),
+                dev(B.dw.weight), requant_dev(P, B.dw),
+                dev(P.prom_pack_ternary(B.project.weight)), requant_dev(P, B.project), B.add_residual, ws)
+        y_dev = P.prom_block(*args)
         y_host, _, _ = oracle.block(x_host, _tup(B.expand), _tup(B.dw), _tup(B.project), b.stride, B.add_residual)
         torch.cuda.synchronize()
         assert_same(y_dev.cpu().numpy(), y_host, f"full-size chain batch {n} {b.name}")
-        del ws
+        if not one_kernel[-1]:
+            y_dev.fill_(-77)
+            P.prom_block(*args, y_dev, path=P.BLOCK_UNFUSED)
+            torch.cuda.synchronize()
+            assert_same(y_dev.cpu().numpy(), y_host, f"full-size chain batch {n} {b.name}, three launches")
+        del ws, args
         x_dev, x_host = y_dev, y_host
     if n == 32:
         assert all(one_kernel)
     else:
         assert one_kernel == [False] * 3 + [True] * 13
+    assert forms[:3] == [P.BLOCK_TILE] * 3 and forms[-9:] == [P.BLOCK_PLANES] * 9, forms
 
 
 def test_chain_replays_from_a_captured_graph(P):

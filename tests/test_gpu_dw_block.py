@@ -166,8 +166,9 @@ def test_block_shapes(P, shape):
 
 
 def test_block_forms_and_queries(P):
-    """What prom_block picks: one kernel for deep blocks on small maps and for small problems, three
-    launches for large maps at a large batch; the limits of the two one-kernel forms."""
+    """What the library prefers among the two kernels that keep a band in LDS and three launches: one kernel for deep
+    blocks on small maps and for small problems, three launches for large maps at a large batch (where the kernel of
+    pixel tiles then takes over: prom_block_form); the limits of the two kernels."""
     assert P.prom_block_is_fused(64, 28, 28, 32, 192, 32, 1) and P.prom_block_is_fused(128, 28, 28, 32, 192, 64, 2)
     assert P.prom_block_is_fused(128, 14, 14, 64, 384, 64, 1) and P.prom_block_is_fused(128, 7, 7, 160, 960, 320, 1)
     assert P.prom_block_is_fused(2, 9, 9, 16, 96, 16, 1) and P.prom_block_can_fuse(2, 9, 9, 16, 96, 16, 1)
