@@ -23,9 +23,9 @@
 #include "prom_launch.h"
 #include "prom_block_planes.h"
 #include "prom_block_tile.h"
+#include "prom_recent.h"
 
-#include <cstring>
-
+#include <array>
 #include <mutex>
 #include <vector>
 
@@ -476,7 +476,6 @@ static bool tile_is_faster(prom::TileArgs &a, bool prelu, double planes_cost, si
 
 // What PROM_BLOCK_AUTO runs a shape as, when every pointer is aligned: the plan of one of the two kernels, or neither.
 struct BlockPlan {
-    int key[8] = {};  // n, h, w, cin, chid, cout, stride, prelu (n = 0: empty)
     bool tile = false, planes = false;
     prom::TileArgs ta;
     prom::PlanesArgs pa;
@@ -484,19 +483,15 @@ struct BlockPlan {
     int grid = 0, kse = 0;
 };
 
-// Planning prices every kernel and split (4 us of host time a call); a program's blocks come again and again, so each
-// thread keeps the plans of the last shapes it met, by their sizes alone.
+// Planning prices every kernel and split (4 us of host time a call, more for deep blocks); a program's blocks come again
+// and again, so each thread keeps the plans of the last 32 shapes it met, by their sizes alone.
 static const BlockPlan &block_plan(int n, int h, int w, int cin, int chid, int cout, int stride, bool prelu)
 {
-    constexpr unsigned kSlots = 32;
-    thread_local BlockPlan slots[kSlots];
-    const int key[8] = {n, h, w, cin, chid, cout, stride, prelu};
-    unsigned hash = 0;
-    for (int k : key) hash = (hash ^ (unsigned)k) * 2654435761u;
-    BlockPlan &p = slots[(hash >> 16) % kSlots];
-    if (memcmp(p.key, key, sizeof(key)) == 0) return p;
-    p.pa = {};
-    p.ta = {};
+    thread_local prom::Recent<std::array<int, 8>, BlockPlan, 32> recent;
+    bool found;
+    BlockPlan &p = recent.get({n, h, w, cin, chid, cout, stride, prelu}, &found);
+    if (found) return p;
+    p = {};
     p.pa.N = p.ta.N = n; p.pa.H = p.ta.H = h; p.pa.W = p.ta.W = w;
     p.pa.Ho = p.ta.Ho = (h - 1) / stride + 1; p.pa.Wo = p.ta.Wo = (w - 1) / stride + 1;
     p.pa.cin = p.ta.cin = cin; p.pa.chid = p.ta.chid = chid; p.pa.cout = p.ta.cout = cout; p.pa.stride = p.ta.stride = stride;
@@ -509,7 +504,6 @@ static const BlockPlan &block_plan(int n, int h, int w, int cin, int chid, int c
         p.lds = lds;
         p.grid = grid;
     }
-    memcpy(p.key, key, sizeof(key));
     return p;
 }
 
