@@ -455,9 +455,12 @@ static bool planes_is_faster(int n, int h, int w, int cin, int chid, int cout, i
 
 // Whether PROM_BLOCK_AUTO takes the kernel of pixel tiles (plan in `a`), by two estimates in microseconds: its planner's
 // and that of what it would replace -- the plane-resident kernel (planes_cost > 0, that planner's clocks; fitted to the
-// measured times of 937 blocks, error 5 %) or three launches.  At 0.9 times, over 1029 blocks of batch 1 to 256 on maps
-// of 11 to 115, it is slower than what it replaces by more than 3 % on two, at 0.95 on 8, at 1.0 on 37; the geometric mean
-// is 1.19 times as fast in all three (1.20 with the better of the two on every block).
+// measured times of 937 blocks, error 5 %) or three launches.  The shifts lie in device memory, and a block whose forms
+// of requantisation are slower loses more in this kernel than in the others: against all shifts >= 2 in [0, 127], a shift of
+// 1 or another window costs it 4 % in the mean of 620 blocks, a shift of 0 9 %, with PReLU a shift of 1 9 % (the
+// plane-resident kernel 0 to 3 %).  Hence the line below 1: at 0.94, of these blocks it is slower by more than 2 % than what
+// it replaces on 4 in [0, 127], 13 with a shift of 1, 23 with a shift of 0, none and 11 with PReLU, and faster on 430, 420,
+// 403, 403 and 378; at 1.0 slower on 19, 34, 46, 12 and 33; at 0.92 it forgoes blocks that are up to 1.26 times as fast.
 static bool tile_is_faster(prom::TileArgs &a, bool prelu, double planes_cost, size_t &lds, int &grid)
 {
     // (no kernel has more than 64 channels in or out: spare the planning)
@@ -470,8 +473,9 @@ static bool tile_is_faster(prom::TileArgs &a, bool prelu, double planes_cost, si
         // 56x56x144 at batch 128 68 us (250 MB through memory), 112x112x96 stride 2 91 us (420 MB)
         const double px = (double)a.N * a.H * a.W, pxo = (double)a.N * a.Ho * a.Wo;
         other = 12.0 + (px * (a.cin + 2.0 * a.chid) + pxo * (2.0 * a.chid + a.cout)) / 5.0e6;
+        if (prelu) other *= 1.2;  // (1.24 times as long in the middle of 109 blocks, 1.06 without)
     }
-    return a.us < 0.92 * other;
+    return a.us < 0.94 * other;
 }
 
 // What PROM_BLOCK_AUTO runs a shape as, when every pointer is aligned: the plan of one of the two kernels, or neither.

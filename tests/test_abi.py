@@ -195,6 +195,17 @@ def test_block_form_says_what_runs(P):
         assert e.value.code == code
 
 
+def test_block_form_is_the_faster_one(P):
+    """Blocks whose times lie far apart (measured in microseconds, replayed from a graph): the one kernel with planes in
+    LDS where a tile's workgroup would read many weights, the kernel of pixel tiles instead of three launches."""
+    for s, tile, planes in (((2, 53, 58, 64, 384, 64, 1), 13.9, 11.5), ((3, 56, 56, 64, 384, 48, 1), 13.0, 11.2),
+                            ((4, 56, 56, 64, 512, 64, 1), 16.2, 14.5), ((3, 58, 56, 40, 320, 16, 2), 10.2, 9.2)):
+        assert tile > planes and P.prom_block_form(*s) == P.BLOCK_PLANES, s
+    for s, tile, launches in (((135, 114, 115, 12, 96, 12, 1), 145, 617), ((235, 110, 114, 12, 96, 48, 2), 139, 875),
+                              ((103, 57, 56, 20, 160, 20, 1), 54, 189)):
+        assert tile < launches and P.prom_block_form(*s, prelu=True) == P.BLOCK_TILE, s
+
+
 def test_binding_fails_loudly_without_library(P, monkeypatch):
     import paper_2505_03254_amd.binding as b
     monkeypatch.setattr(b, "_lib", None)
