@@ -470,6 +470,8 @@ static bool tile_is_faster(prom::TileArgs &a, bool prelu, double planes_cost, si
         const double c = planes_cost / 2400.0;
         other = prelu ? 1.36 + 0.838 * c : 2.13 + 0.691 * c;
     } else {
+        // (images or rows that the launches refuse stay refused)
+        if (prom::dw_shape_check(a.N, a.H, a.W, a.chid, a.stride) != PROM_OK) return false;
         // 56x56x144 at batch 128 68 us (250 MB through memory), 112x112x96 stride 2 91 us (420 MB)
         const double px = (double)a.N * a.H * a.W, pxo = (double)a.N * a.Ho * a.Wo;
         other = 12.0 + (px * (a.cin + 2.0 * a.chid) + pxo * (2.0 * a.chid + a.cout)) / 5.0e6;

@@ -206,6 +206,14 @@ def test_block_form_is_the_faster_one(P):
         assert tile < launches and P.prom_block_form(*s, prelu=True) == P.BLOCK_TILE, s
 
 
+def test_block_refuses_what_the_launches_refuse(P):
+    """More than 65535 images or 262140 rows (at stride 1): where the block was three launches, the depthwise layer
+    refuses them, and the kernel of pixel tiles does not take them over."""
+    for n, h, form in ((65535, 12, P.BLOCK_TILE), (65536, 12, P.BLOCK_UNFUSED), (1, 262140, P.BLOCK_TILE), (1, 262141, P.BLOCK_UNFUSED)):
+        assert P.prom_block_form(n, h, 14, 16, 96, 16, 1) == form, (n, h)
+        assert not P.prom_block_is_fused(n, h, 14, 16, 96, 16, 1)
+
+
 def test_binding_fails_loudly_without_library(P, monkeypatch):
     import paper_2505_03254_amd.binding as b
     monkeypatch.setattr(b, "_lib", None)
