@@ -3,8 +3,8 @@
 // tile of output pixels, for blocks with few channels on large maps.
 //
 // Such blocks are bound by the requantisation of the expanded tensor (14 clocks of a SIMD per output and
-// wavefront, twice per hidden element, plus the halo), about 20 us for 56x56x144 at batch 128, as long as
-// nothing else stands in the way: three launches take the expanded tensor through HBM twice each way (68 us),
+// wavefront, twice per hidden element, plus the halo), 13 us for 56x56x144 at batch 128 in tiles of 8 rows (10
+// without the halo), as long as nothing else stands in the way: three launches take the expanded tensor through HBM twice each way (68 us),
 // the kernel with whole planes in LDS fills a CU with one workgroup whose phases follow each other (70 us).
 // Here nothing but the weights is shared:
 //   - the workgroup decodes the weights of the whole block into LDS once and stays resident, walking over
@@ -12,7 +12,7 @@
 //   - a wavefront keeps the input of its tile in registers as MFMA operands (a row of 16 input columns is one
 //     16-pixel tile, straight from the NHWC rows, 14 (7 at stride 2) output columns wide) and walks over the
 //     hidden channels in planes of 16: expansion (1 MFMA per row), requantisation, 256 bytes a row into the
-//     wavefront's own plane of 2 to 5 KB; depthwise filter on the matrix cores (one-hot operands, tap rows in
+//     wavefront's own plane of 1 to 4.6 KB; depthwise filter on the matrix cores (one-hot operands, tap rows in
 //     the k dimension), requantisation; and the outputs of two planes ARE the B operand of a projection MFMA
 //     (v_mfma_i32_16x16x32_i8) -- the projection accumulates in registers.  No barrier, no second pass
 //     through LDS; LDS operations of one wavefront complete in order.
@@ -23,11 +23,18 @@
 //   - small problems: S wavefronts share a tile's planes and add their partial projections in LDS.
 // In the loop the kernel is at its instruction count: 3 wavefronts per SIMD with 10 tiles (4 rows) take 870
 // clocks per plane each, 2 with 18 tiles (8 rows) 1600, where the sum of the instructions' issue times is 870
-// and 1440.  Variants of 8, 6, 4 and 2 rows trade halo rows and per-plane work against registers (2, 2, 3 and 4
-// wavefronts per SIMD); plan_tile prices them.
+// and 1440.  Around it a tile costs 0.9 us and 0.21 per 16 pixels and 16 output channels (projection's
+// requantisation, skip and store: 4.3 us with 8 rows, of which 0.4 are issue), launch and prologue 4 us: the 36 us of
+// 56x56 24-144-24 at batch 128 are two rounds of 11.5 us in the loop and 4.3 behind it.
+// Variants of 8, 6, 4 and 2 rows trade halo rows and per-plane work against registers (2, 2, 3 and 4 wavefronts per
+// SIMD); plan_tile prices them.  With 8 rows the 256 registers do not quite do: the plain kernel of stride 1 spills 3
+// (16 bytes of scratch a lane), that of stride 2 with PReLU 1; written once, read once per tile, not in the loop.
 // Measured (replayed from graphs, us; three launches or the plane-resident kernel before): batch 128,
 // 112x112 16-96-24 stride 2 91 -> 45.4, 56x56 24-144-24 67.3 -> 34.8, 24-144-32 stride 2 42.2 -> 20.9, 28x28
 // 32-192-32 22.1 -> 17.9, 32-192-64 stride 2 16.3 -> 13.1; batch 8, the first two 12.5 -> 9.6 and 10.3 -> 9.1.
+// All shifts >= 2 and windows [0, 127], which every time above is for; the first at batch 128 on another machine 43.4, with
+// one shift of 1 45.8, of 0 53.3, with PReLU 56.4, and one shift of 1 72.1 (the plane-resident kernel 86 in all of these);
+// in the network's chain, whose expansion has shifts of 1 and whose tensors come from memory, up to 53.
 #include "prom_pw_stream.h"
 #include "prom_launch.h"
 #include "prom_block_tile.h"
@@ -223,6 +230,10 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void block_tile_kernel(const TileA
         const int f = slot[min(lane, (nthr >> 6) - 1)];
         const bool ge1 = __builtin_amdgcn_ballot_w64(f & 1) == 0, ge2 = __builtin_amdgcn_ballot_w64(f & 2) == 0;
         const int form_e = pair_form_of(PRELU, ge1, ge2, a.lo_e, a.hi_e), form_d = pair_form_of(PRELU, ge1, ge2, a.lo_d, a.hi_d);
+        // (One choice for both layers and all channels.  A pair of forms, with kPairLow for shifts of 1 and kPairRelu for the
+        // depthwise layer behind them, was built: 112x112 16-96-24 at batch 128 45.8 -> 44.7 us with a shift of 1 and 72.1 ->
+        // 69.1 with PReLU, but 43.4 -> 44.2 and 56.4 -> 57.6 without; over 44 blocks 2.5 % slower with shifts >= 2, 3.7 %
+        // with PReLU and 0.9 % with a shift of 1 -- more registers spill, and the prologue is 0.2 us longer.)
         if (PRELU) form = form_e == form_d ? form_e : kPairPreluAny;
         else form = form_e == kPairRelu && form_d == kPairRelu ? kPairRelu : ge1 ? kPairClamp : kPairAny;
         form_p = a.np ? kPairPreluAny : __builtin_amdgcn_ballot_w64(f & 4) == 0 && a.lo_p == -128 && a.hi_p == 127 ? kPairFull : kPairAny;

@@ -64,8 +64,8 @@ def test_mobilenetv2_block_chain(P, p_zero, input_hw, n):
                            project_shift=_pw_shift(b.cin * b.t))
             ws = torch.empty(P.prom_block_workspace_size(n, hw, hw, b.cin, B.chid, b.cout, b.stride),
                              dtype=torch.int8, device="cuda")
-            # the fused kernel wherever it applies (at these small sizes the library itself would
-            # take the three launches), the three launches elsewhere
+            # the chunk-interleaved kernel wherever it applies (at these sizes the library itself would
+            # take another form), what the library takes elsewhere
             can = P.prom_block_can_fuse(n, hw, hw, b.cin, B.chid, b.cout, b.stride)
             y_dev = P.prom_block(x_dev, B.chid, b.cout, b.stride,
                                  dev(P.prom_pack_ternary(B.expand.weight)), requant_dev(P, B.expand),
@@ -79,7 +79,7 @@ def test_mobilenetv2_block_chain(P, p_zero, input_hw, n):
         assert_same(y_dev.cpu().numpy(), y_host, f"chain p_zero={p_zero} {b.name}")
         assert len(np.unique(y_host)) > 24, f"{b.name}: the chain's activations degenerated"
         x_dev, x_host = y_dev, y_host
-    # the chain must exercise both forms of prom_block
+    # the chain must exercise both
     assert any(fused) and not all(fused)
     hw = x_host.shape[1]
     H = make_pw_layer(seed + 999, n, hw, hw, blocks[-1].cout, 1280, p_zero=p_zero,
