@@ -395,7 +395,7 @@ size_t prom_block_workspace_size(int n, int h, int w, int cin, int chid, int cou
  * the form measured faster for the shape.  A form returns PROM_EUNSUPPORTED where it does not apply
  * (prom_block_planes_applies with 16-byte aligned parameter arrays of the first two layers,
  * prom_block_can_fuse, prom_dw_pw_can_fuse; x, y, w_dw 8-byte aligned; PROM_BLOCK_TILE: the limits of
- * prom_block_tile_applies, whether it is faster or not). */
+ * prom_block_tile_applies, whether it is faster or not and for any number of images). */
 enum { PROM_BLOCK_AUTO = 0, PROM_BLOCK_FUSED = 1, PROM_BLOCK_UNFUSED = 2, PROM_BLOCK_DWPROJ = 3, PROM_BLOCK_PLANES = 4,
        PROM_BLOCK_TILE = 5 };
 /* PROM_BLOCK_TILE with the plan (or parts of it, 0: the library's) chosen by the caller, for tests and measurements:
@@ -423,8 +423,8 @@ int prom_block_is_fused(int n, int h, int w, int cin, int chid, int cout, int st
 
 /* Positive (which of its variants) if PROM_BLOCK_AUTO takes the kernel whose wavefronts own pixel tiles instead of what
  * prom_block_is_fused names (prelu != 0: the expansion or the depthwise layer has negative-side multipliers; pointers
- * assumed 8-byte aligned): cin and cout <= 64 and multiples of 4, chid % 16 == 0, tensors below 2 GiB, and estimated to
- * be faster.  0 if not, PROM_EINVAL for bad dimensions.  Host only. */
+ * assumed 8-byte aligned): cin and cout <= 64 and multiples of 4, chid % 16 == 0, tensors below 2 GiB, decoded weights
+ * that fit in LDS, estimated to be faster, and no more images or rows than the form it replaces takes.  0 if not, PROM_EINVAL for bad dimensions.  Host only. */
 int prom_block_tile_applies(int n, int h, int w, int cin, int chid, int cout, int stride, int prelu);
 
 /* 1 if the chunk-interleaved fused kernel (PROM_BLOCK_FUSED) applies to the shape at all (cin % 8 == 0, chid % 4 == 0, cout % 4 == 0,

@@ -455,7 +455,7 @@ static bool planes_is_faster(int n, int h, int w, int cin, int chid, int cout, i
 
 // Whether PROM_BLOCK_AUTO takes the kernel of pixel tiles (plan in `a`), by two estimates in microseconds: its planner's
 // and that of what it would replace -- the plane-resident kernel (planes_cost > 0, that planner's clocks; fitted to the
-// measured times of 937 blocks, error 5 %) or three launches.  The shifts lie in device memory, and a block whose forms
+// measured times of 937 blocks, error 5 %, over the 620 below 6 %) or three launches.  The shifts lie in device memory, and a block whose forms
 // of requantisation are slower loses more in this kernel than in the others: against all shifts >= 2 in [0, 127], a shift of
 // 1 or another window costs it 4 % in the mean of 620 blocks, a shift of 0 9 %, with PReLU a shift of 1 9 % (the
 // plane-resident kernel 0 to 3 %).  Hence the line below 1: at 0.94, of these blocks it is slower by more than 2 % than what
